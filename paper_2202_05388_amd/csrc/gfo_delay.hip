@@ -30,7 +30,7 @@ __device__ __forceinline__ Snap deferred_snapshot(const Geo& g, const gfo_pick p
   s.j = -1;
   const int j = pk.pixel, e = pk.eps_idx;
   if (j >= 0 && j < g.N && e >= 0 && e < g.n_eps && e != cur) {
-    const double a = g.k0sq * (g.eps[e] - g.eps[cur]);
+    const double a = g.k0sq * (eps_of(g, e) - eps_of(g, cur));
     const double2 den = make_double2(1.0 - a * dj.x, -a * dj.y);
     if (cabs2(den) < 1e-24) {
       s.pad1 = 1;                           // singular: refused, flagged by the next kernel
@@ -72,7 +72,8 @@ __device__ __forceinline__ Snap deferred_snapshot(const Geo& g, const gfo_pick p
 // loads whose range ends at the term count, so that slots past it read as zero
 // without a branch); gather_finish
 // issues the loads that depend on the pick at once (the pixel's scalars, the
-// base entries, and the terms' entries at j, staged once per workgroup in LDS).
+// base entries, and the terms' entries at j, one per lane, read back across
+// lanes).
 // B terms per wave: 16 while the state's delay is at most 64, else 32 (the
 // slots of a term buffer of 4 B); every path of a state uses the same B, so
 // their sums agree bit for bit.
@@ -146,6 +147,21 @@ __device__ __forceinline__ void gather_prefetch(const Geo& g, const int32_t* __r
   gather_prefetch_n<T, B>(g, __builtin_amdgcn_readfirstlane(*count), CUs, Vs, pre);
 }
 
+// Lane k's value of x, uniform (k a constant).
+__device__ __forceinline__ float2 lane_value(float2 x, int k) {
+  return make_float2(__builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x.x), k)),
+                     __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x.y), k)));
+}
+__device__ __forceinline__ double lane_value(double x, int k) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, k);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), k);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ double2 lane_value(double2 x, int k) {
+  return make_double2(lane_value(x.x, k), lane_value(x.y, k));
+}
+
 template <typename T, int B>
 __device__ __forceinline__ void gather_finish(const Geo& g, const gfo_pick pk,
                                               const GatherPre<T, B>& pre, const T* __restrict__ G,
@@ -155,7 +171,6 @@ __device__ __forceinline__ void gather_finish(const Geo& g, const gfo_pick pk,
                                               Snap* __restrict__ snap_out, T* __restrict__ CUs,
                                               T* __restrict__ Vs, T* __restrict__ cu_out,
                                               T* __restrict__ v_out, T* __restrict__ emon) {
-  __shared__ T yj[2][GFO_MAX_DELAY];              // V_s[j] (monitor rows), CU_s[j] (row entries)
   __shared__ double2 part[kGatherParts - 1][kGatherElems];
   const int cnt = pre.cnt;
   const int jc = __builtin_amdgcn_readfirstlane(pk.pixel >= 0 && pk.pixel < g.N ? pk.pixel : 0);
@@ -163,28 +178,37 @@ __device__ __forceinline__ void gather_finish(const Geo& g, const gfo_pick pk,
   const GatherElem el = gather_elem(g);
   const int64_t e = el.e, i = el.i, q = el.q;
   const bool mon = el.mon, live = el.live;
-  // every load that depends on the pick, issued together
-  const int cur = eps_idx[jc];
+  // every load that depends on the pick, issued together: the terms' entries at
+  // j (lane k of wave w: its wave's term k), the base entry, the pixel's scalars
+  const int s0 = w * B;
+  const int ks = s0 + (lane < B ? lane : B - 1);
+  const T* __restrict__ y_src = mon ? Vs : CUs;
+  const T yl = y_src[ks * (mon ? g.ld : (int64_t)g.R) + jc];
+  const int64_t qc = q < g.N ? q : g.N - 1;
+  const T* __restrict__ base_at = G + (mon ? g_mon(g, i - g.N, jc) : g_upper(g, jc, qc));
+  T base = St<T>::from_d(make_double2(0.0, 0.0)), Ei = base;
+  if (w == 0) {
+    base = *base_at;
+    if (mon) Ei = E[i];
+  }
+  const int cur = __builtin_amdgcn_readfirstlane((int)eps_idx[jc]);
   const double2 dj = diag64[jc];
   const T Ej = E[jc];
-  T base = St<T>::from_d(make_double2(0.0, 0.0));
-  if (w == 0) base = mon ? G[g_off(g, i, jc)] : G[g_at(g, jc, q)];
-  if (threadIdx.x < cnt) yj[0][threadIdx.x] = Vs[(int64_t)threadIdx.x * g.ld + jc];
-  if (threadIdx.x >= 64 && threadIdx.x - 64 < cnt)
-    yj[1][threadIdx.x - 64] = CUs[(int64_t)(threadIdx.x - 64) * g.R + jc];
+  __builtin_amdgcn_sched_barrier(0);
+  keep(dj);
+  keep(Ej);
   const Snap sn = deferred_snapshot<T>(g, pk, cur, dj, Ej, cnt);
   if (blockIdx.x == 0 && threadIdx.x == 0) *snap_out = sn;
   const int j = __builtin_amdgcn_readfirstlane(sn.j);
-  __syncthreads();
   // the terms of an entry: design row entries other than the pivot, and the
   // monitor rows except the FOM monitor's
   const bool terms = mon ? (e != g.m0) : (q < g.N && q != j);
-  const int s0 = w * B;
   double2 acc = make_double2(0.0, 0.0);
-  if (j >= 0 && terms) {
+  if (j >= 0) {   // uniform
 #pragma unroll
     for (int k = 0; k < B; ++k)
-      if (s0 + k < cnt) acc = cadd(acc, cmul(St<T>::to_d(pre.a[k]), St<T>::to_d(yj[mon ? 0 : 1][s0 + k])));
+      if (s0 + k < cnt) acc = cadd(acc, cmul(St<T>::to_d(pre.a[k]), St<T>::to_d(lane_value(yl, k))));
+    acc = pick_of(terms, acc, make_double2(0.0, 0.0));
   }
   if (w > 0) part[w - 1][lane] = acc;
   __syncthreads();
@@ -192,14 +216,14 @@ __device__ __forceinline__ void gather_finish(const Geo& g, const gfo_pick pk,
   acc = cadd(cadd(acc, part[0][lane]), cadd(part[1][lane], part[2][lane]));
   const int slot = cnt;
   if (mon) {
-    const double2 u = e != g.m0 ? cadd(St<T>::to_d(base), acc) : St<T>::to_d(base);
+    const double2 u = pick_of(e != g.m0, cadd(St<T>::to_d(base), acc), St<T>::to_d(base));
     const T cu = St<T>::from_d(cmul(sn.c, u));
-    CUs[(int64_t)slot * g.R + i] = e != g.m0 ? cu : St<T>::from_d(make_double2(0.0, 0.0));
+    CUs[(int64_t)slot * g.R + i] = pick_of(e != g.m0, cu, St<T>::from_d(make_double2(0.0, 0.0)));
     cu_out[i] = cu;
-    emon[e] = axpy_st<T>(E[i], cu, sn.Ej);
+    emon[e] = axpy_st<T>(Ei, cu, sn.Ej);
   } else {
     double2 v = make_double2(0.0, 0.0);
-    if (q < g.N) v = q == j ? sn.dj : cadd(St<T>::to_d(base), acc);
+    if (q < g.N) v = pick_of(q == j, sn.dj, cadd(St<T>::to_d(base), acc));
     const T vv = St<T>::from_d(v);
     Vs[(int64_t)slot * g.ld + q] = vv;
     v_out[q] = vv;
@@ -226,7 +250,7 @@ __global__ __launch_bounds__(256) void k_gather_dl(
 // summaries (identical in all of them: the same reads, exact max and min
 // reductions) while its pick-independent gather loads are in flight; workgroup
 // 0 records the pick in `pick_out`.
-template <typename T, int B>
+template <typename T, int B, int PPL>
 __global__ __launch_bounds__(256) void k_select_gather(
     Geo g, const double* __restrict__ scores, const double* __restrict__ partial,
     const int* __restrict__ pfirst, int nblk, double tau, gfo_pick* __restrict__ pick_out,
@@ -236,7 +260,7 @@ __global__ __launch_bounds__(256) void k_select_gather(
     T* __restrict__ v_out, T* __restrict__ emon) {
   // the summaries first: waiting for them then does not wait for the term
   // operands (vector loads complete in issue order)
-  PickPre<> pp;
+  PickPre<PPL> pp;
   pick_wave_load(partial, pfirst, nblk, pp);
   const double fom = cabs2(St<T>::to_d(E[g.N + g.m0]));
   __builtin_amdgcn_sched_barrier(0);
@@ -443,71 +467,86 @@ __device__ __forceinline__ void move_body(
     const int32_t* __restrict__ count, int32_t* __restrict__ flips, int flip_cap,
     int32_t* __restrict__ n_flips, int32_t* __restrict__ status, T* __restrict__ CUs,
     T* __restrict__ Vs) {
-  __shared__ T yj[2][GFO_MAX_DELAY];              // V_s[j] (monitor rows), CU_s[j] (row entries)
   __shared__ double2 part[kGatherParts - 1][kGatherElems];
   const T zero = St<T>::from_d(make_double2(0.0, 0.0));
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   const GatherElem el = gather_elem(g);
   const int64_t e = el.e, i = el.i, q = el.q;
   const bool mon = el.mon, live = el.live;
-  T* __restrict__ grow = G + g_off(g, g.N + g.m0, 0);
-  // loads that need nothing else: the summaries first, then the lane's operand
-  // of every slot of its wave's terms (those past the term count, not known
-  // yet, are not used), then this lane's own values (its pixel, or its
-  // monitor's field)
+  T* __restrict__ grow = G + g_mon(g, g.m0, 0);
+  // First batch, loads that need nothing else: the summaries first, then the
+  // lane's operand of every slot of its wave's terms (those past the term count,
+  // not known yet, are not used), then this lane's own values (its pixel, or its
+  // monitor's field; wave 0 alone uses them)
   PickPre<PPL> pp;
   pick_wave_load(partial_prev, pfirst_prev, nblk_prev, pp);
   GatherPre<T, B> pre;
   gather_prefetch_n<T, B>(g, kGatherParts * B, CUs, Vs, pre);
   const int64_t qc = q < g.N ? q : g.N - 1;
-  const T Eown = E[mon ? i : qc];
-  const double2 dq = diag64[qc];
-  const int curq = eps_idx[qc];
-  const T gq = grow[qc];
-  const T emon_e = has_prev && mon ? emon_prev[live ? e : 0] : Eown;
-  const T em0_prev = has_prev ? emon_prev[g.m0] : E[g.N + g.m0];
+  const T* __restrict__ em_src = has_prev ? emon_prev : E + g.N;
+  const T em0_prev = em_src[g.m0];
+  T Eown = zero, gq = zero;
+  double2 dq = make_double2(0.0, 0.0);
+  int curq = 0, n_moves = 0;
+  if (w == 0) {
+    Eown = mon ? em_src[live ? e : 0] : E[qc];
+    dq = diag64[qc];
+    curq = eps_idx[qc];
+    gq = grow[qc];
+    if (blockIdx.x == 0) n_moves = *n_flips;
+  }
   __builtin_amdgcn_sched_barrier(0);
-  Snap sp;
-  sp.j = -1;
-  sp.cnt_after = 0;
-  if (has_prev) sp = *snap_prev;
+  // the previous move (not used without one: the buffer then holds an older call's)
+  const int sp_j = snap_prev->j, sp_e = snap_prev->e_new, sp_cnt = snap_prev->cnt_after, mem_cnt = *count;
+  const T sp_E = St<T>::from_d(snap_prev->Ej_new), sp_g = St<T>::from_d(snap_prev->gm0_new);
+  const double2 sp_d = snap_prev->dj_new;
   // after a flush the previous move's values are in memory (k_move_finish ran
   // before it, so that the flush saw them)
   const bool carry = has_prev && !flushed;
-  const int cnt = flushed ? 0 : (has_prev ? sp.cnt_after : *count);
+  const int cnt = flushed ? 0 : (has_prev ? sp_cnt : mem_cnt);
   const double fom = cabs2(St<T>::to_d(em0_prev));
   const gfo_pick pk = pick_wave_take(g, fom, pp, scores_prev, tau, false, bpix_prev);
   const int jc = __builtin_amdgcn_readfirstlane(pk.pixel >= 0 && pk.pixel < g.N ? pk.pixel : 0);
-  // the pivot's values before this move (the previous pivot's from its snapshot)
-  const bool ovr = carry && sp.j >= 0 && sp.j == jc;
+  // Second batch, every load that needs the pick, issued together and with no
+  // branch or wait between them (each was a memory round trip of its own while
+  // the terms' entries at j went through LDS): the terms' entries at j (lane k
+  // of wave w holds its wave's term k: V_s[j] for monitor rows, CU_s[j] for row
+  // entries), the base entry, the pivot's values before this move
+  const int s0 = w * B;
+  const int ks = s0 + (lane < B ? lane : B - 1);
+  const T* __restrict__ y_src = mon ? Vs : CUs;
+  const T yl = y_src[ks * (mon ? g.ld : (int64_t)g.R) + jc];
+  T base = zero;
+  const T* __restrict__ base_at = G + (mon ? g_mon(g, i - g.N, jc) : g_upper(g, jc, qc));
+  if (w == 0) base = *base_at;
   int cur = eps_idx[jc];
   double2 dj = diag64[jc];
   T Ej = E[jc], gm0j = grow[jc];
-  if (ovr) {
-    cur = sp.e_new;
-    dj = sp.dj_new;
-    Ej = St<T>::from_d(sp.Ej_new);
-    gm0j = St<T>::from_d(sp.gm0_new);
-  }
-  T base = zero;
-  if (w == 0) base = mon ? (e == g.m0 ? gm0j : G[g_off(g, i, jc)]) : G[g_at(g, jc, q)];
-  if (threadIdx.x < cnt) yj[0][threadIdx.x] = Vs[(int64_t)threadIdx.x * g.ld + jc];
-  if (threadIdx.x >= 64 && threadIdx.x - 64 < cnt)
-    yj[1][threadIdx.x - 64] = CUs[(int64_t)(threadIdx.x - 64) * g.R + jc];
+  double rec_fom = 0.0;
+  if (blockIdx.x == 0 && w == 0 && pk.pixel >= 0) rec_fom = scores_prev[pk.pixel * g.n_eps + pk.eps_idx];
+  __builtin_amdgcn_sched_barrier(0);
+  keep(dj);
+  keep(Ej);
+  // (the previous pivot's values from its snapshot)
+  const bool ovr = carry && sp_j >= 0 && sp_j == jc;
+  cur = __builtin_amdgcn_readfirstlane(ovr ? sp_e : cur);
+  dj = pick_of(ovr, sp_d, dj);
+  Ej = pick_of(ovr, sp_E, Ej);
+  gm0j = pick_of(ovr, sp_g, gm0j);
+  base = pick_of(mon && e == g.m0, gm0j, base);
   const Snap sn = deferred_snapshot<T>(g, pk, cur, dj, Ej, cnt);
   const int j = __builtin_amdgcn_readfirstlane(sn.j);
   const bool moved = j >= 0;
   // the FOM monitor's term entry and field after the move, alike everywhere
   const T cu_m0 = moved ? St<T>::from_d(cmul(sn.c, St<T>::to_d(gm0j))) : zero;
   const T em0_new = moved ? axpy_st<T>(em0_prev, cu_m0, sn.Ej) : em0_prev;
-  __syncthreads();
   const bool terms = moved && (mon ? e != g.m0 : (q < g.N && q != j));
-  const int s0 = w * B;
   double2 acc = make_double2(0.0, 0.0);
-  if (terms) {
+  if (moved) {   // uniform
 #pragma unroll
     for (int k = 0; k < B; ++k)
-      if (s0 + k < cnt) acc = cadd(acc, cmul(St<T>::to_d(pre.a[k]), St<T>::to_d(yj[mon ? 0 : 1][s0 + k])));
+      if (s0 + k < cnt) acc = cadd(acc, cmul(St<T>::to_d(pre.a[k]), St<T>::to_d(lane_value(yl, k))));
+    acc = pick_of(terms, acc, make_double2(0.0, 0.0));
   }
   if (w > 0) part[w - 1][lane] = acc;
   __syncthreads();
@@ -519,12 +558,12 @@ __device__ __forceinline__ void move_body(
   bool bad = false;
   if (mon) {
     if (live) {
-      if (has_prev) E[i] = emon_e;                // the previous move's field (no reader here)
-      T em = emon_e;
+      if (has_prev) E[i] = Eown;                  // the previous move's field (no reader here)
+      T em = Eown;
       if (moved) {
         const double2 u = e != g.m0 ? cadd(St<T>::to_d(base), acc) : St<T>::to_d(base);
         const T cu = St<T>::from_d(cmul(sn.c, u));
-        CUs[(int64_t)slot * g.R + i] = e != g.m0 ? cu : zero;
+        CUs[(int64_t)slot * g.R + i] = pick_of(e != g.m0, cu, zero);
         em = axpy_st<T>(em, cu, sn.Ej);
       }
       emon_next[e] = em;
@@ -533,7 +572,7 @@ __device__ __forceinline__ void move_body(
     T vv = zero, cuq = zero;
     if (moved) {
       double2 v = make_double2(0.0, 0.0);
-      if (q < g.N) v = q == j ? sn.dj : cadd(St<T>::to_d(base), acc);
+      if (q < g.N) v = pick_of(q == j, sn.dj, cadd(St<T>::to_d(base), acc));
       vv = St<T>::from_d(v);
       Vs[(int64_t)slot * g.ld + q] = vv;
       if (q < g.N) {
@@ -543,11 +582,11 @@ __device__ __forceinline__ void move_body(
     }
     if (q < g.N) {
       // pixel q before this move (the previous pivot's values from its snapshot)
-      const bool prevp = carry && sp.j >= 0 && q == sp.j;
-      T Ec = prevp ? St<T>::from_d(sp.Ej_new) : Eown;
-      double2 dc = prevp ? sp.dj_new : dq;
-      int cc = prevp ? sp.e_new : curq;
-      T gc = prevp ? St<T>::from_d(sp.gm0_new) : gq;
+      const bool prevp = carry && sp_j >= 0 && q == sp_j;
+      T Ec = pick_of(prevp, sp_E, Eown);
+      double2 dc = pick_of(prevp, sp_d, dq);
+      int cc = prevp ? sp_e : curq;
+      T gc = pick_of(prevp, sp_g, gq);
       if (moved) {
         Ec = axpy_st<T>(Ec, cuq, sn.Ej);
         if (q == j) {
@@ -592,20 +631,19 @@ __device__ __forceinline__ void move_body(
           cmul(sn.dj, rdiv(1.0, make_double2(1.0 - sn.alpha * sn.dj.x, -sn.alpha * sn.dj.y)));
       snap_out->gm0_new = St<T>::to_d(axpy_st<T>(gm0j, cu_m0, St<T>::to_d(St<T>::from_d(sn.dj))));
       // the history (the term count stays in the snapshots)
-      const int n = *n_flips;
-      if (n < flip_cap) {
-        flips[2 * n] = sn.j;
-        flips[2 * n + 1] = sn.e_new;
+      if (n_moves < flip_cap) {
+        flips[2 * n_moves] = sn.j;
+        flips[2 * n_moves + 1] = sn.e_new;
       } else {
         atomicOr(status, GFO_STATUS_HISTORY_FULL);
       }
-      *n_flips = n + 1;
+      *n_flips = n_moves + 1;
     } else if (sn.pad1) {
       atomicOr(status, GFO_STATUS_SINGULAR);
     }
     gfo_pick rec = pk;
     if (rec.pixel >= 0) {
-      rec.fom_new = scores_prev[rec.pixel * g.n_eps + rec.eps_idx];
+      rec.fom_new = rec_fom;
       rec.dfom = rec.fom_new - fom;
     }
     *pick_out = rec;
@@ -714,7 +752,11 @@ hipError_t launch_fused_move(const Geo& g, gfo_state* st, const Layout& L, int a
     if (e != hipSuccess) return e;
   }
   const int64_t n = (int64_t)gather_mpad(g) + g.ld;
-  hipLaunchKernelGGL((gather_batch(st->delay) == 16 ? k_select_gather<T, 16> : k_select_gather<T, 32>),
+  // summaries per lane: the smallest of 4, 8 and 16 that covers the grid's
+  const bool b16 = gather_batch(st->delay) == 16;
+  hipLaunchKernelGGL((nblk <= 256   ? (b16 ? k_select_gather<T, 16, 4> : k_select_gather<T, 32, 4>)
+                      : nblk <= 512 ? (b16 ? k_select_gather<T, 16, 8> : k_select_gather<T, 32, 8>)
+                                    : (b16 ? k_select_gather<T, 16, 16> : k_select_gather<T, 32, 16>)),
                      dim3((unsigned)((n + kGatherElems - 1) / kGatherElems)),
                      dim3(256), 0, s, g,
                      (const double*)scores, (const double*)partial, (const int*)pfirst, nblk, tau,

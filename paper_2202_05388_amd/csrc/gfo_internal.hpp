@@ -65,6 +65,50 @@ __host__ __device__ __forceinline__ int64_t g_off(const Geo& g, int64_t r, int64
   return g_band_start(1, g.ld, b) + (r & 63) * (g.ld - 64 * b) + (c - 64 * b);
 }
 
+// Offset of design entry (p, q) in deferred mode (upper = 1: the entry at (min,
+// max)), dense or band-packed, without a branch, so that a kernel can issue the
+// load together with others:
+// packed rows of band b start 2048 b (b - 1) + 64 b (r % 64 + 1) entries earlier
+// than dense ones.
+__device__ __forceinline__ int64_t g_upper(const Geo& g, int64_t p, int64_t q) {
+  const int64_t r = p < q ? p : q, c = p < q ? q : p;
+  const int64_t b = g.packed ? r >> 6 : 0;
+  return r * g.ld + c - (2048 * b * (b - 1) + 64 * b * ((r & 63) + 1));
+}
+
+// Permittivity table entry idx (0 <= idx < GFO_MAX_EPS) by selects: an index
+// known only at run time would make each thread read the kernel's arguments
+// from memory (a round trip on the critical path of a move), or, from a local
+// copy of Geo, place that copy in scratch memory.
+// The empty asm keeps each entry a value of its own (the compiler otherwise
+// turns the selects back into one load at a selected address).
+__device__ __forceinline__ double eps_of(const Geo& g, int idx) {
+  double v = 0.0;
+#pragma unroll
+  for (int e = 0; e < GFO_MAX_EPS; ++e) {
+    double x = g.eps[e];
+    asm("" : "+s"(x));
+    v = idx == e ? x : v;
+  }
+  return v;
+}
+// c ? a : b of the members (a conditional between two structs is one between
+// their addresses, which puts them in scratch memory).
+__device__ __forceinline__ float2 pick_of(bool c, float2 a, float2 b) {
+  return make_float2(c ? a.x : b.x, c ? a.y : b.y);
+}
+__device__ __forceinline__ double2 pick_of(bool c, double2 a, double2 b) {
+  return make_double2(c ? a.x : b.x, c ? a.y : b.y);
+}
+// Marks x as used here, so that its load stays in the batch it was written in
+// instead of moving into a later branch that needs it.
+__device__ __forceinline__ void keep(double2 x) { asm volatile("" ::"v"(x.x), "v"(x.y)); }
+__device__ __forceinline__ void keep(float2 x) { asm volatile("" ::"v"(x.x), "v"(x.y)); }
+// Offset of entry (m, c) of the monitor rows.
+__device__ __forceinline__ int64_t g_mon(const Geo& g, int64_t m, int64_t c) {
+  return g.mon_base + m * g.ld + c;
+}
+
 // Offset of entry (p, q) of G; design-block entries (p, q < N) come from the
 // upper triangle when g.upper.
 __device__ __forceinline__ int64_t g_at(const Geo& g, int64_t p, int64_t q) {
@@ -202,12 +246,14 @@ __device__ inline double score_pixel(const Geo& g, int p, int cur, double2 d, do
                                      double2 Em0, uint32_t mask, double* __restrict__ scores,
                                      bool* bad, double (&F)[GFO_MAX_EPS]) {
   double best = -INFINITY;
+  const double eps_cur = eps_of(g, cur);
 #pragma unroll
   for (int e = 0; e < GFO_MAX_EPS; ++e) {
+    F[e] = -INFINITY;
     if (e < g.n_eps) {
       double Fe = -INFINITY;
       if (((mask >> e) & 1u) && e != cur) {
-        const double a = g.k0sq * (g.eps[e] - g.eps[cur]);
+        const double a = g.k0sq * (g.eps[e] - eps_cur);
         const double2 c = rdiv(a, make_double2(1.0 - a * d.x, -a * d.y));   // FP64 denominator
         const double2 En = cadd(Em0, cmul(c, gE));
         Fe = cabs2(En);
@@ -336,13 +382,11 @@ __device__ __forceinline__ void pick_wave_load(const double* __restrict__ partia
   const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int k = 0; k < PPL; ++k) {
-    const int i = lane + 64 * k;
-    pp.pv[k] = -INFINITY;
-    pp.pf[k] = 0x7fffffff;
-    if (i < nblk) {
-      pp.pv[k] = partial[i];
-      pp.pf[k] = pfirst[i];
-    }
+    const int i = lane + 64 * k, ic = i < nblk ? i : nblk - 1;   // no branch around the loads
+    const double v = partial[ic];
+    const int f = pfirst[ic];
+    pp.pv[k] = i < nblk ? v : -INFINITY;
+    pp.pf[k] = i < nblk ? f : 0x7fffffff;
   }
 }
 
