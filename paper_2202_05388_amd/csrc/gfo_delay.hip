@@ -7,6 +7,8 @@
 // pending terms.
 #include "gfo_internal.hpp"
 
+#include <type_traits>
+
 namespace gfo {
 
 // Pending terms are stored slot-major, CUs[s * R + r] and Vs[s * ld + q]: the
@@ -23,14 +25,14 @@ __device__ __forceinline__ T axpy_st(T x, T a, double2 b) {
 // The move's scalars, from the pick and the values at its pixel that no thread
 // of this launch writes (eps_idx[j], diag64[j], E[j], the term count); cur, dj
 // and Ej are read at jc, the pick's pixel clamped into range.
-template <typename T>
+template <typename T, int NE = GFO_MAX_EPS>
 __device__ __forceinline__ Snap deferred_snapshot(const Geo& g, const gfo_pick pk, int cur,
                                                   double2 dj, T Ej, int cnt) {
   Snap s = {};
   s.j = -1;
   const int j = pk.pixel, e = pk.eps_idx;
   if (j >= 0 && j < g.N && e >= 0 && e < g.n_eps && e != cur) {
-    const double a = g.k0sq * (eps_of(g, e) - eps_of(g, cur));
+    const double a = g.k0sq * (eps_of<NE>(g, e) - eps_of<NE>(g, cur));
     const double2 den = make_double2(1.0 - a * dj.x, -a * dj.y);
     if (cabs2(den) < 1e-24) {
       s.pad1 = 1;                           // singular: refused, flagged by the next kernel
@@ -114,14 +116,14 @@ __device__ __forceinline__ GatherElem gather_elem(const Geo& g) {
 }
 
 template <typename T>
-__device__ __forceinline__ T buf_load(__amdgpu_buffer_rsrc_t r, unsigned off);
+__device__ __forceinline__ T buf_load(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff);
 template <>
-__device__ __forceinline__ float2 buf_load<float2>(__amdgpu_buffer_rsrc_t r, unsigned off) {
-  return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+__device__ __forceinline__ float2 buf_load<float2>(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff) {
+  return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, 0));
 }
 template <>
-__device__ __forceinline__ double2 buf_load<double2>(__amdgpu_buffer_rsrc_t r, unsigned off) {
-  return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+__device__ __forceinline__ double2 buf_load<double2>(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff) {
+  return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, 0));
 }
 
 template <typename T, int B>
@@ -134,10 +136,11 @@ __device__ __forceinline__ void gather_prefetch_n(const Geo& g, int cnt, const T
   const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
       (void*)(el.mon ? CUs : Vs), (short)0, (int)(pre.cnt * stride * (int64_t)sizeof(T)), 0x00020000);
   const unsigned off = (unsigned)((el.mon ? el.i : el.q) * (int64_t)sizeof(T));
-  const int s0 = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * B;
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int s0 = w * B;
 #pragma unroll
   for (int k = 0; k < B; ++k)
-    pre.a[k] = buf_load<T>(r, off + (unsigned)((s0 + k) * stride * (int64_t)sizeof(T)));
+    pre.a[k] = buf_load<T>(r, off, (unsigned)((s0 + k) * (unsigned)stride * (unsigned)sizeof(T)));
 }
 
 template <typename T, int B>
@@ -146,6 +149,14 @@ __device__ __forceinline__ void gather_prefetch(const Geo& g, const int32_t* __r
                                                 const T* __restrict__ Vs, GatherPre<T, B>& pre) {
   gather_prefetch_n<T, B>(g, __builtin_amdgcn_readfirstlane(*count), CUs, Vs, pre);
 }
+
+// Sum of a wave's terms s0 + k < cnt (k < B) from zero in slot order: the lane's
+// operands pre.a[k] times the terms' entries at j, lane k of yl.  In groups of
+// four: a group past the count is skipped (uniform), inside a group slots past
+// it count as zero (adding +0 leaves the sum's bits), so that four terms' products
+// are in flight without a branch each.
+template <typename T, int B>
+__device__ __forceinline__ double2 sum_terms(const GatherPre<T, B>& pre, T yl, int s0, int cnt);
 
 // Lane k's value of x, uniform (k a constant).
 __device__ __forceinline__ float2 lane_value(float2 x, int k) {
@@ -160,6 +171,24 @@ __device__ __forceinline__ double lane_value(double x, int k) {
 }
 __device__ __forceinline__ double2 lane_value(double2 x, int k) {
   return make_double2(lane_value(x.x, k), lane_value(x.y, k));
+}
+
+template <typename T, int B>
+__device__ __forceinline__ double2 sum_terms(const GatherPre<T, B>& pre, T yl, int s0, int cnt) {
+  const T zero = St<T>::from_d(make_double2(0.0, 0.0));
+  const T y = pick_of(s0 + (int)(threadIdx.x & 63) < cnt, yl, zero);
+  double2 acc = make_double2(0.0, 0.0);
+#pragma unroll
+  for (int k0 = 0; k0 < B; k0 += 4) {
+    if (s0 + k0 < cnt) {
+#pragma unroll
+      for (int k = k0; k < k0 + 4; ++k) {
+        const T a = pick_of(s0 + k < cnt, pre.a[k], zero);
+        acc = cadd(acc, cmul(St<T>::to_d(a), St<T>::to_d(lane_value(y, k))));
+      }
+    }
+  }
+  return acc;
 }
 
 template <typename T, int B>
@@ -203,13 +232,7 @@ __device__ __forceinline__ void gather_finish(const Geo& g, const gfo_pick pk,
   // the terms of an entry: design row entries other than the pivot, and the
   // monitor rows except the FOM monitor's
   const bool terms = mon ? (e != g.m0) : (q < g.N && q != j);
-  double2 acc = make_double2(0.0, 0.0);
-  if (j >= 0) {   // uniform
-#pragma unroll
-    for (int k = 0; k < B; ++k)
-      if (s0 + k < cnt) acc = cadd(acc, cmul(St<T>::to_d(pre.a[k]), St<T>::to_d(lane_value(yl, k))));
-    acc = pick_of(terms, acc, make_double2(0.0, 0.0));
-  }
+  double2 acc = pick_of(j >= 0 && terms, sum_terms<T, B>(pre, yl, s0, cnt), make_double2(0.0, 0.0));
   if (w > 0) part[w - 1][lane] = acc;
   __syncthreads();
   if (j < 0 || w != 0 || !live) return;
@@ -455,7 +478,28 @@ hipError_t launch_dl_reset(const Geo&, gfo_state* st, const Layout& L, hipStream
 // flush, read it from memory, which k_move_finish brings up to date);
 // snapshots, scores and summaries alternate between two sets of buffers.  The expressions are those of the per-call path (k_gather_dl,
 // k_mon_dl, k_score), so the state and the picks are bit for bit the same.
-template <typename T, int PPL, int B>
+// Five waves per workgroup: wave 4 takes the pick and then computes what is alike
+// everywhere (the snapshot with its divisions, the FOM monitor's term entry and
+// field) while waves 0 to 3 sum the terms (kGatherParts); wave 0 then applies the
+// move to the workgroup's elements and scores them; wave 4 of workgroup 0 keeps
+// the books.  Every wave passes the same two barriers: the pick is in LDS, then
+// the partial sums and the move's scalars are.  NE: 2 when the table has two entries, else GFO_MAX_EPS.
+// What bounds it: latency, one chain per move.  Time stamps in the kernel (128 x
+// 128, 257 workgroups, one wave per SIMD) showed the chain's arithmetic, its
+// instruction fetches and its kernel-argument reads to weigh as much as its memory
+// round trips, hence few instructions on wave 0's path.
+constexpr int kMoveThreads = 64 * (kGatherParts + 1);
+
+template <typename T>
+struct MoveShared {
+  double2 part[kGatherParts - 1][kGatherElems];
+  double2 c, dj, dj_new;     // alpha / (1 - alpha G_jj); G_jj before and after the move
+  double2 Ej;                // E[j] before the move
+  T cu_m0, em0_new, gm0j;    // FOM monitor: its term entry, its field after, its row's entry j
+  int jc, j, e_new;          // the pick's pixel (0 without one), the move's pixel (-1: none), its material
+};
+
+template <typename T, int PPL, int B, int NE>
 __device__ __forceinline__ void move_body(
     const Geo& g, int has_prev, int flushed, const Snap* __restrict__ snap_prev,
     Snap* __restrict__ snap_out, const double* __restrict__ scores_prev,
@@ -467,63 +511,147 @@ __device__ __forceinline__ void move_body(
     const int32_t* __restrict__ count, int32_t* __restrict__ flips, int flip_cap,
     int32_t* __restrict__ n_flips, int32_t* __restrict__ status, T* __restrict__ CUs,
     T* __restrict__ Vs) {
-  __shared__ double2 part[kGatherParts - 1][kGatherElems];
+  __shared__ MoveShared<T> sh;
   const T zero = St<T>::from_d(make_double2(0.0, 0.0));
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-  const GatherElem el = gather_elem(g);
-  const int64_t e = el.e, i = el.i, q = el.q;
-  const bool mon = el.mon, live = el.live;
   T* __restrict__ grow = G + g_mon(g, g.m0, 0);
-  // First batch, loads that need nothing else: the summaries first, then the
-  // lane's operand of every slot of its wave's terms (those past the term count,
-  // not known yet, are not used), then this lane's own values (its pixel, or its
-  // monitor's field; wave 0 alone uses them)
-  PickPre<PPL> pp;
-  pick_wave_load(partial_prev, pfirst_prev, nblk_prev, pp);
-  GatherPre<T, B> pre;
-  gather_prefetch_n<T, B>(g, kGatherParts * B, CUs, Vs, pre);
-  const int64_t qc = q < g.N ? q : g.N - 1;
   const T* __restrict__ em_src = has_prev ? emon_prev : E + g.N;
-  const T em0_prev = em_src[g.m0];
-  T Eown = zero, gq = zero;
-  double2 dq = make_double2(0.0, 0.0);
-  int curq = 0, n_moves = 0;
-  if (w == 0) {
-    Eown = mon ? em_src[live ? e : 0] : E[qc];
-    dq = diag64[qc];
-    curq = eps_idx[qc];
-    gq = grow[qc];
-    if (blockIdx.x == 0) n_moves = *n_flips;
-  }
-  __builtin_amdgcn_sched_barrier(0);
-  // the previous move (not used without one: the buffer then holds an older call's)
+  // the previous move (not used without one: the buffer then holds an older call's);
+  // after a flush its values are in memory (k_move_finish ran before it, so that
+  // the flush saw them)
+  const bool carry = has_prev && !flushed;
   const int sp_j = snap_prev->j, sp_e = snap_prev->e_new, sp_cnt = snap_prev->cnt_after, mem_cnt = *count;
   const T sp_E = St<T>::from_d(snap_prev->Ej_new), sp_g = St<T>::from_d(snap_prev->gm0_new);
   const double2 sp_d = snap_prev->dj_new;
-  // after a flush the previous move's values are in memory (k_move_finish ran
-  // before it, so that the flush saw them)
-  const bool carry = has_prev && !flushed;
   const int cnt = flushed ? 0 : (has_prev ? sp_cnt : mem_cnt);
+  if (w < kGatherParts) {
+    const GatherElem el = gather_elem(g);
+    const int64_t e = el.e, i = el.i, q = el.q;
+    const bool mon = el.mon, live = el.live;
+    // First batch, loads that need nothing else, in flight while wave 4 takes the
+    // pick: the lane's operand of every slot of its wave's terms (those past the
+    // term count are not used), then this lane's own values (its pixel, or its
+    // monitor's field)
+    GatherPre<T, B> pre;
+    gather_prefetch_n<T, B>(g, kGatherParts * B, CUs, Vs, pre);
+    const int64_t qc = q < g.N ? q : g.N - 1;
+    T Eown = zero, gq = zero;
+    double2 dq = make_double2(0.0, 0.0);
+    int curq = 0;
+    if (w == 0) {
+      Eown = mon ? em_src[live ? e : 0] : E[qc];
+      dq = diag64[qc];
+      curq = eps_idx[qc];
+      gq = grow[qc];
+    }
+    __syncthreads();
+    // Second batch, every load that needs the pick, issued together: the terms'
+    // entries at j (lane k of wave w holds its wave's term k: V_s[j] for monitor
+    // rows, CU_s[j] for row entries) and the base entry
+    const int jc = __builtin_amdgcn_readfirstlane(sh.jc);
+    const int s0 = w * B, ks = s0 + (lane < B ? lane : B - 1);
+    const T* __restrict__ y_src = mon ? Vs : CUs;
+    const T yl = y_src[ks * (mon ? g.ld : (int64_t)g.R) + jc];
+    const T* __restrict__ base_at = G + (mon ? g_mon(g, i - g.N, jc) : g_upper(g, jc, qc));
+    T base = zero;
+    if (w == 0) base = *base_at;
+    __builtin_amdgcn_sched_barrier(0);
+    double2 acc = sum_terms<T, B>(pre, yl, s0, cnt);
+    if (w > 0) sh.part[w - 1][lane] = acc;
+    __syncthreads();
+    if (w > 0) return;
+    const int j = __builtin_amdgcn_readfirstlane(sh.j);
+    const bool moved = j >= 0;
+    const double2 c = sh.c, sEj = sh.Ej, sdj = sh.dj;
+    const T cu_m0 = sh.cu_m0;
+    // the terms of an entry: design row entries other than the pivot, and the
+    // monitor rows except the FOM monitor's
+    const bool terms = moved && (mon ? e != g.m0 : (q < g.N && q != j));
+    acc = cadd(cadd(acc, sh.part[0][lane]), cadd(sh.part[1][lane], sh.part[2][lane]));
+    acc = pick_of(terms, acc, make_double2(0.0, 0.0));
+    base = pick_of(mon && e == g.m0, sh.gm0j, base);
+    double best = -INFINITY;
+    double F[NE];
+    bool bad = false;
+    if (mon) {
+      if (live) {
+        if (has_prev) E[i] = Eown;                // the previous move's field (no reader here)
+        T em = Eown;
+        if (moved) {
+          const double2 u = pick_of(e != g.m0, cadd(St<T>::to_d(base), acc), St<T>::to_d(base));
+          const T cu = St<T>::from_d(cmul(c, u));
+          CUs[(int64_t)cnt * g.R + i] = pick_of(e != g.m0, cu, zero);
+          em = axpy_st<T>(em, cu, sEj);
+        }
+        emon_next[e] = em;
+      }
+      return;
+    }
+    if (live) {
+      T vv = zero, cuq = zero;
+      if (moved) {
+        double2 v = make_double2(0.0, 0.0);
+        if (q < g.N) v = pick_of(q == j, sdj, cadd(St<T>::to_d(base), acc));
+        vv = St<T>::from_d(v);
+        Vs[(int64_t)cnt * g.ld + q] = vv;
+        if (q < g.N) {
+          cuq = St<T>::from_d(cmul(c, v));
+          CUs[(int64_t)cnt * g.R + q] = cuq;
+        }
+      }
+      if (q < g.N) {
+        // pixel q before this move (the previous pivot's values from its snapshot)
+        const bool prevp = carry && sp_j >= 0 && q == sp_j;
+        T Ec = pick_of(prevp, sp_E, Eown);
+        double2 dc = pick_of(prevp, sp_d, dq);
+        int cc = prevp ? sp_e : curq;
+        T gc = pick_of(prevp, sp_g, gq);
+        if (moved) {
+          Ec = axpy_st<T>(Ec, cuq, sEj);
+          dc = pick_of(q == j, sh.dj_new, cadd(dc, cmul(St<T>::to_d(cuq), St<T>::to_d(vv))));
+          cc = q == j ? sh.e_new : cc;
+          gc = axpy_st<T>(gc, cu_m0, St<T>::to_d(vv));
+        }
+        if ((moved || prevp) && !(moved && q == j)) {
+          E[q] = Ec;
+          diag64[q] = dc;
+          eps_idx[q] = (uint8_t)cc;
+          grow[q] = gc;
+        }
+        const double2 gE = cmul(St<T>::to_d(gc), St<T>::to_d(Ec));
+        best = score_pixel<NE>(g, (int)q, cc, dc, gE, St<T>::to_d(sh.em0_new), mask, scores_next, &bad, F);
+      }
+    }
+    // this workgroup's pixels: its best score and the lowest index within the
+    // tie band of that best (indices rise with the lane)
+    const double bb = wave_max(best);
+    int f = 0x7fffffff;
+    if (live && q < g.N && bb > -INFINITY) f = first_at_least<NE>(g, (int)q, F, tie_threshold(bb, tau));
+    const uint64_t votes = __ballot(f != 0x7fffffff);
+    const int64_t pb = (int64_t)blockIdx.x - gather_mpad(g) / kGatherElems;
+    if (lane == (votes ? __builtin_ctzll(votes) : 0) && pb * kGatherElems < g.N) {
+      partial_next[pb] = bb;
+      pfirst_next[pb] = f;
+    }
+    if (bad) atomicOr(status, GFO_STATUS_NONFINITE);
+    return;
+  }
+  // wave 4: the pick
+  PickPre<PPL> pp;
+  pick_wave_load(partial_prev, pfirst_prev, nblk_prev, pp);
+  const T em0_prev = em_src[g.m0];
+  const int n_moves = blockIdx.x == 0 ? *n_flips : 0;
   const double fom = cabs2(St<T>::to_d(em0_prev));
   const gfo_pick pk = pick_wave_take(g, fom, pp, scores_prev, tau, false, bpix_prev);
   const int jc = __builtin_amdgcn_readfirstlane(pk.pixel >= 0 && pk.pixel < g.N ? pk.pixel : 0);
-  // Second batch, every load that needs the pick, issued together and with no
-  // branch or wait between them (each was a memory round trip of its own while
-  // the terms' entries at j went through LDS): the terms' entries at j (lane k
-  // of wave w holds its wave's term k: V_s[j] for monitor rows, CU_s[j] for row
-  // entries), the base entry, the pivot's values before this move
-  const int s0 = w * B;
-  const int ks = s0 + (lane < B ? lane : B - 1);
-  const T* __restrict__ y_src = mon ? Vs : CUs;
-  const T yl = y_src[ks * (mon ? g.ld : (int64_t)g.R) + jc];
-  T base = zero;
-  const T* __restrict__ base_at = G + (mon ? g_mon(g, i - g.N, jc) : g_upper(g, jc, qc));
-  if (w == 0) base = *base_at;
+  if (lane == 0) sh.jc = jc;
+  __syncthreads();
+  // the pivot's values before this move
   int cur = eps_idx[jc];
   double2 dj = diag64[jc];
   T Ej = E[jc], gm0j = grow[jc];
   double rec_fom = 0.0;
-  if (blockIdx.x == 0 && w == 0 && pk.pixel >= 0) rec_fom = scores_prev[pk.pixel * g.n_eps + pk.eps_idx];
+  if (blockIdx.x == 0 && pk.pixel >= 0) rec_fom = scores_prev[pk.pixel * g.n_eps + pk.eps_idx];
   __builtin_amdgcn_sched_barrier(0);
   keep(dj);
   keep(Ej);
@@ -533,102 +661,30 @@ __device__ __forceinline__ void move_body(
   dj = pick_of(ovr, sp_d, dj);
   Ej = pick_of(ovr, sp_E, Ej);
   gm0j = pick_of(ovr, sp_g, gm0j);
-  base = pick_of(mon && e == g.m0, gm0j, base);
-  const Snap sn = deferred_snapshot<T>(g, pk, cur, dj, Ej, cnt);
-  const int j = __builtin_amdgcn_readfirstlane(sn.j);
-  const bool moved = j >= 0;
-  // the FOM monitor's term entry and field after the move, alike everywhere
-  const T cu_m0 = moved ? St<T>::from_d(cmul(sn.c, St<T>::to_d(gm0j))) : zero;
-  const T em0_new = moved ? axpy_st<T>(em0_prev, cu_m0, sn.Ej) : em0_prev;
-  const bool terms = moved && (mon ? e != g.m0 : (q < g.N && q != j));
-  double2 acc = make_double2(0.0, 0.0);
-  if (moved) {   // uniform
-#pragma unroll
-    for (int k = 0; k < B; ++k)
-      if (s0 + k < cnt) acc = cadd(acc, cmul(St<T>::to_d(pre.a[k]), St<T>::to_d(lane_value(yl, k))));
-    acc = pick_of(terms, acc, make_double2(0.0, 0.0));
+  const Snap sn = deferred_snapshot<T, NE>(g, pk, cur, dj, Ej, cnt);
+  const bool moved = sn.j >= 0;
+  const T cu_m0 = pick_of(moved, St<T>::from_d(cmul(sn.c, St<T>::to_d(gm0j))), zero);
+  const T em0_new = pick_of(moved, axpy_st<T>(em0_prev, cu_m0, sn.Ej), em0_prev);
+  const double2 dj_new = cmul(sn.dj, rdiv(1.0, make_double2(1.0 - sn.alpha * sn.dj.x, -sn.alpha * sn.dj.y)));
+  if (lane == 0) {
+    sh.c = sn.c;
+    sh.dj = sn.dj;
+    sh.dj_new = dj_new;
+    sh.Ej = sn.Ej;
+    sh.cu_m0 = cu_m0;
+    sh.em0_new = em0_new;
+    sh.gm0j = gm0j;
+    sh.j = sn.j;
+    sh.e_new = sn.e_new;
   }
-  if (w > 0) part[w - 1][lane] = acc;
   __syncthreads();
-  if (w != 0) return;
-  acc = cadd(cadd(acc, part[0][lane]), cadd(part[1][lane], part[2][lane]));
-  const int slot = cnt;
-  double best = -INFINITY;
-  double F[GFO_MAX_EPS];
-  bool bad = false;
-  if (mon) {
-    if (live) {
-      if (has_prev) E[i] = Eown;                  // the previous move's field (no reader here)
-      T em = Eown;
-      if (moved) {
-        const double2 u = e != g.m0 ? cadd(St<T>::to_d(base), acc) : St<T>::to_d(base);
-        const T cu = St<T>::from_d(cmul(sn.c, u));
-        CUs[(int64_t)slot * g.R + i] = pick_of(e != g.m0, cu, zero);
-        em = axpy_st<T>(em, cu, sn.Ej);
-      }
-      emon_next[e] = em;
-    }
-  } else if (live) {
-    T vv = zero, cuq = zero;
-    if (moved) {
-      double2 v = make_double2(0.0, 0.0);
-      if (q < g.N) v = pick_of(q == j, sn.dj, cadd(St<T>::to_d(base), acc));
-      vv = St<T>::from_d(v);
-      Vs[(int64_t)slot * g.ld + q] = vv;
-      if (q < g.N) {
-        cuq = St<T>::from_d(cmul(sn.c, v));
-        CUs[(int64_t)slot * g.R + q] = cuq;
-      }
-    }
-    if (q < g.N) {
-      // pixel q before this move (the previous pivot's values from its snapshot)
-      const bool prevp = carry && sp_j >= 0 && q == sp_j;
-      T Ec = pick_of(prevp, sp_E, Eown);
-      double2 dc = pick_of(prevp, sp_d, dq);
-      int cc = prevp ? sp_e : curq;
-      T gc = pick_of(prevp, sp_g, gq);
-      if (moved) {
-        Ec = axpy_st<T>(Ec, cuq, sn.Ej);
-        if (q == j) {
-          dc = cmul(sn.dj, rdiv(1.0, make_double2(1.0 - sn.alpha * sn.dj.x, -sn.alpha * sn.dj.y)));
-          cc = sn.e_new;
-        } else {
-          dc = cadd(dc, cmul(St<T>::to_d(cuq), St<T>::to_d(vv)));
-        }
-        gc = axpy_st<T>(gc, cu_m0, St<T>::to_d(vv));
-      }
-      if ((moved || prevp) && !(moved && q == j)) {
-        E[q] = Ec;
-        diag64[q] = dc;
-        eps_idx[q] = (uint8_t)cc;
-        grow[q] = gc;
-      }
-      const double2 gE = cmul(St<T>::to_d(gc), St<T>::to_d(Ec));
-      best = score_pixel(g, (int)q, cc, dc, gE, St<T>::to_d(em0_new), mask, scores_next, &bad, F);
-    }
-  }
-  if (!mon) {
-    // this workgroup's pixels: its best score and the lowest index within the
-    // tie band of that best
-    const double bb = wave_max(best);
-    int f = 0x7fffffff;
-    if (live && q < g.N && bb > -INFINITY) f = first_at_least(g, (int)q, F, tie_threshold(bb, tau));
-    f = wave_min(f);
-    const int64_t pb = (int64_t)blockIdx.x - gather_mpad(g) / kGatherElems;
-    if (lane == 0 && pb * kGatherElems < g.N) {
-      partial_next[pb] = bb;
-      pfirst_next[pb] = f;
-    }
-  }
-  if (bad) atomicOr(status, GFO_STATUS_NONFINITE);
   if (blockIdx.x == 0 && lane == 0) {
     *snap_out = sn;
     snap_out->cnt_after = moved ? cnt + 1 : cnt;
     if (moved) {
       const T cuj = St<T>::from_d(cmul(sn.c, sn.dj));
       snap_out->Ej_new = St<T>::to_d(axpy_st<T>(Ej, cuj, sn.Ej));
-      snap_out->dj_new =
-          cmul(sn.dj, rdiv(1.0, make_double2(1.0 - sn.alpha * sn.dj.x, -sn.alpha * sn.dj.y)));
+      snap_out->dj_new = dj_new;
       snap_out->gm0_new = St<T>::to_d(axpy_st<T>(gm0j, cu_m0, St<T>::to_d(St<T>::from_d(sn.dj))));
       // the history (the term count stays in the snapshots)
       if (n_moves < flip_cap) {
@@ -650,8 +706,20 @@ __device__ __forceinline__ void move_body(
   }
 }
 
-template <typename T, int PPL, int B>
-__global__ __launch_bounds__(256) void k_move(
+// Reads one word of each 64-byte line of the N bytes at p (uniform: the kernel's
+// arguments, or a job's table entry) together, so that a kernel waits once for
+// them instead of once per line as the code comes to them.
+template <int N>
+__device__ __forceinline__ void touch_lines(const int* p) {
+  int x[(N + 63) / 64];
+#pragma unroll
+  for (int i = 0; i < (N + 63) / 64; ++i) x[i] = p[16 * i];
+#pragma unroll
+  for (int i = 0; i < (N + 63) / 64; ++i) asm volatile("" ::"s"(x[i]));
+}
+
+template <typename T, int PPL, int B, int NE>
+__global__ __launch_bounds__(kMoveThreads) void k_move(
     Geo g, int has_prev, int flushed, const Snap* __restrict__ snap_prev,
     Snap* __restrict__ snap_out, const double* __restrict__ scores_prev,
     const double* __restrict__ partial_prev, const int* __restrict__ pfirst_prev, int nblk_prev,
@@ -662,10 +730,11 @@ __global__ __launch_bounds__(256) void k_move(
     const int32_t* __restrict__ count, int32_t* __restrict__ flips, int flip_cap,
     int32_t* __restrict__ n_flips, int32_t* __restrict__ status, T* __restrict__ CUs,
     T* __restrict__ Vs) {
-  move_body<T, PPL, B>(g, has_prev, flushed, snap_prev, snap_out, scores_prev, partial_prev,
-                       pfirst_prev, nblk_prev, bpix_prev, scores_next, partial_next, pfirst_next,
-                       emon_prev, emon_next, mask, tau, pick_out, G, E, diag64, eps_idx, count,
-                       flips, flip_cap, n_flips, status, CUs, Vs);
+  touch_lines<sizeof(Geo) + 27 * 8>((const int*)__builtin_amdgcn_kernarg_segment_ptr());
+  move_body<T, PPL, B, NE>(g, has_prev, flushed, snap_prev, snap_out, scores_prev, partial_prev,
+                           pfirst_prev, nblk_prev, bpix_prev, scores_next, partial_next, pfirst_next,
+                           emon_prev, emon_next, mask, tau, pick_out, G, E, diag64, eps_idx, count,
+                           flips, flip_cap, n_flips, status, CUs, Vs);
 }
 
 // After move t of a one-kernel loop (its last, or before a flush): the move's
@@ -792,9 +861,14 @@ hipError_t launch_move(const Geo& g, gfo_state* st, const Layout& L, int t, int 
   // summaries per lane: 4 while the grid has at most 256 of 64 pixels
   const bool small = (g.N + kGatherElems - 1) / kGatherElems <= 4 * 64;
   const bool b16 = gather_batch(st->delay) == 16;
-  hipLaunchKernelGGL((small ? (b16 ? k_move<T, 4, 16> : k_move<T, 4, 32>)
-                            : (b16 ? k_move<T, kPickPerLane, 16> : k_move<T, kPickPerLane, 32>)),
-                     dim3((unsigned)((n + kGatherElems - 1) / kGatherElems)), dim3(256), 0,
+  auto kern = [&](auto ne) {
+    constexpr int NE = decltype(ne)::value;
+    return small ? (b16 ? k_move<T, 4, 16, NE> : k_move<T, 4, 32, NE>)
+                 : (b16 ? k_move<T, kPickPerLane, 16, NE> : k_move<T, kPickPerLane, 32, NE>);
+  };
+  hipLaunchKernelGGL((g.n_eps == 2 ? kern(std::integral_constant<int, 2>{})
+                                   : kern(std::integral_constant<int, GFO_MAX_EPS>{})),
+                     dim3((unsigned)((n + kGatherElems - 1) / kGatherElems)), dim3(kMoveThreads), 0,
                      s, g, t > 0 ? 1 : 0, flushed, (const Snap*)snaps[b], snaps[a],
                      (const double*)scores[a], (const double*)partial[a], (const int*)pfirst[a], nblk,
                      bpix, scores[b], partial[b], pfirst[b], (const T*)emons[b], emons[a], mask, tau,
@@ -899,10 +973,11 @@ __global__ __launch_bounds__(kScoreThreads) void k_mon_score_table(const JobEntr
                     (double*)(w + je->partial), (int*)(w + je->pfirst), je->nblk0);
 }
 
-template <typename T, int PPL, int B>
-__global__ __launch_bounds__(256) void k_move_table(const JobEntry* __restrict__ tab, int t,
+template <typename T, int PPL, int B, int NE>
+__global__ __launch_bounds__(kMoveThreads) void k_move_table(const JobEntry* __restrict__ tab, int t,
                                                     uint64_t flushed_mask) {
   const JobEntry* je = tab + blockIdx.y;
+  touch_lines<sizeof(JobEntry)>((const int*)je);
   if ((int)blockIdx.x >= je->n_move_wg) return;
   const Geo g = je->g;
   char* w = je->work;
@@ -912,7 +987,7 @@ __global__ __launch_bounds__(256) void k_move_table(const JobEntry* __restrict__
   const int64_t sc_a = a ? je->scores2 : je->scores, sc_b = a ? je->scores : je->scores2;
   const int64_t pa_a = a ? je->partial2 : je->partial, pa_b = a ? je->partial : je->partial2;
   const int64_t pf_a = a ? je->pfirst2 : je->pfirst, pf_b = a ? je->pfirst : je->pfirst2;
-  move_body<T, PPL, B>(g, t > 0 ? 1 : 0, (int)((flushed_mask >> blockIdx.y) & 1u),
+  move_body<T, PPL, B, NE>(g, t > 0 ? 1 : 0, (int)((flushed_mask >> blockIdx.y) & 1u),
                        (const Snap*)(w + snap_b), (Snap*)(w + snap_a), (const double*)(w + sc_a),
                        (const double*)(w + pa_a), (const int*)(w + pf_a),
                        t == 0 ? je->nblk0 : je->nblkg, t == 0 ? kScoreThreads : kGatherElems,
@@ -944,13 +1019,17 @@ hipError_t launch_table_scores(const JobEntry* tab, int n_jobs, int max_wg, hipS
 
 template <typename T>
 hipError_t launch_table_move(const JobEntry* tab, int n_jobs, int max_wg, int t, uint64_t flushed,
-                             bool small, int batch, hipStream_t s) {
+                             bool small, int batch, bool two_eps, hipStream_t s) {
   const dim3 grid((unsigned)max_wg, (unsigned)n_jobs);
   const bool b16 = batch == 16;
-  hipLaunchKernelGGL((small ? (b16 ? k_move_table<T, 4, 16> : k_move_table<T, 4, 32>)
-                            : (b16 ? k_move_table<T, kPickPerLane, 16>
-                                   : k_move_table<T, kPickPerLane, 32>)),
-                     grid, dim3(256), 0, s, tab, t, flushed);
+  auto kern = [&](auto ne) {
+    constexpr int NE = decltype(ne)::value;
+    return small ? (b16 ? k_move_table<T, 4, 16, NE> : k_move_table<T, 4, 32, NE>)
+                 : (b16 ? k_move_table<T, kPickPerLane, 16, NE> : k_move_table<T, kPickPerLane, 32, NE>);
+  };
+  hipLaunchKernelGGL((two_eps ? kern(std::integral_constant<int, 2>{})
+                              : kern(std::integral_constant<int, GFO_MAX_EPS>{})),
+                     grid, dim3(kMoveThreads), 0, s, tab, t, flushed);
   return note_hip(hipGetLastError());
 }
 
@@ -963,9 +1042,9 @@ hipError_t launch_table_finish(const JobEntry* tab, int n_jobs, int max_wg, int 
 
 template hipError_t launch_table_scores<float2>(const JobEntry*, int, int, hipStream_t);
 template hipError_t launch_table_scores<double2>(const JobEntry*, int, int, hipStream_t);
-template hipError_t launch_table_move<float2>(const JobEntry*, int, int, int, uint64_t, bool, int,
+template hipError_t launch_table_move<float2>(const JobEntry*, int, int, int, uint64_t, bool, int, bool,
                                               hipStream_t);
-template hipError_t launch_table_move<double2>(const JobEntry*, int, int, int, uint64_t, bool, int,
+template hipError_t launch_table_move<double2>(const JobEntry*, int, int, int, uint64_t, bool, int, bool,
                                                hipStream_t);
 template hipError_t launch_table_finish<float2>(const JobEntry*, int, int, int, hipStream_t);
 template hipError_t launch_table_finish<double2>(const JobEntry*, int, int, int, hipStream_t);

@@ -82,10 +82,12 @@ __device__ __forceinline__ int64_t g_upper(const Geo& g, int64_t p, int64_t q) {
 // copy of Geo, place that copy in scratch memory.
 // The empty asm keeps each entry a value of its own (the compiler otherwise
 // turns the selects back into one load at a selected address).
+// NE: entries looked at (2 where the caller knows n_eps = 2).
+template <int NE = GFO_MAX_EPS>
 __device__ __forceinline__ double eps_of(const Geo& g, int idx) {
   double v = 0.0;
 #pragma unroll
-  for (int e = 0; e < GFO_MAX_EPS; ++e) {
+  for (int e = 0; e < NE; ++e) {
     double x = g.eps[e];
     asm("" : "+s"(x));
     v = idx == e ? x : v;
@@ -240,17 +242,19 @@ struct Layout {
 // Scores of pixel p for every material (eqs. form4-form9 at the FOM monitor):
 // F = |E_m0 + c G[m0, p] E_p|^2 with c = alpha / (1 - alpha G_pp) in FP64; -inf
 // for non-candidates and the current material.  Writes them to `scores` and to
-// F[0 .. n_eps) (a register array: the loop is unrolled over GFO_MAX_EPS), returns
-// the largest and sets *bad on a non-finite one.
+// F[0 .. n_eps) (a register array: the loop is unrolled over NE: 2 where the
+// caller knows n_eps = 2, else GFO_MAX_EPS), returns the largest and sets *bad
+// on a non-finite one.
+template <int NE>
 __device__ inline double score_pixel(const Geo& g, int p, int cur, double2 d, double2 gE,
                                      double2 Em0, uint32_t mask, double* __restrict__ scores,
-                                     bool* bad, double (&F)[GFO_MAX_EPS]) {
+                                     bool* bad, double (&F)[NE]) {
   double best = -INFINITY;
-  const double eps_cur = eps_of(g, cur);
+  const double eps_cur = eps_of<NE>(g, cur);
 #pragma unroll
-  for (int e = 0; e < GFO_MAX_EPS; ++e) {
+  for (int e = 0; e < NE; ++e) {
     F[e] = -INFINITY;
-    if (e < g.n_eps) {
+    if (NE == 2 || e < g.n_eps) {
       double Fe = -INFINITY;
       if (((mask >> e) & 1u) && e != cur) {
         const double a = g.k0sq * (g.eps[e] - eps_cur);
@@ -274,12 +278,12 @@ __device__ inline double score_pixel(const Geo& g, int p, int cur, double2 d, do
 __device__ __forceinline__ double tie_threshold(double m, double tau) { return m - tau * m; }
 
 // Lowest (pixel, material) index of pixel p whose score reaches thr, else INT_MAX.
-__device__ inline int first_at_least(const Geo& g, int p, const double (&F)[GFO_MAX_EPS],
-                                     double thr) {
+template <int NE>
+__device__ inline int first_at_least(const Geo& g, int p, const double (&F)[NE], double thr) {
   int f = 0x7fffffff;
 #pragma unroll
-  for (int e = GFO_MAX_EPS - 1; e >= 0; --e)
-    if (e < g.n_eps && F[e] >= thr) f = p * g.n_eps + e;
+  for (int e = NE - 1; e >= 0; --e)
+    if ((NE == 2 || e < g.n_eps) && F[e] >= thr) f = p * g.n_eps + e;
   return f;
 }
 
@@ -409,13 +413,18 @@ __device__ __forceinline__ gfo_pick pick_wave_take(const Geo& g, double fom, con
   m = wave_max(m);
   if (!(m > fom * (1.0 + tau))) return pk;
   const double thr = tie_threshold(m, tau);
-  int bq = 0x7fffffff;
+  // the lowest workgroup whose best reaches the band: register kb of lane lb
+  // (lane votes and a bit scan; the maximum itself always qualifies)
+  int kb = 0, lb = 0;
 #pragma unroll
-  for (int k = PPL - 1; k >= 0; --k)
-    if (pp.pv[k] >= thr) bq = lane + 64 * k;
-  bq = __builtin_amdgcn_readfirstlane(wave_min(bq));
-  // workgroup bq's summary, from lane bq % 64, register bq / 64
-  const int kb = bq >> 6, lb = bq & 63;
+  for (int k = PPL - 1; k >= 0; --k) {
+    const uint64_t v = __ballot(pp.pv[k] >= thr);
+    if (v) {
+      kb = k;
+      lb = __builtin_ctzll(v);
+    }
+  }
+  const int bq = lb + 64 * kb;
   double pvb = -INFINITY;
   int pfb = 0x7fffffff;
 #pragma unroll
@@ -447,7 +456,7 @@ __device__ __forceinline__ gfo_pick pick_wave_take(const Geo& g, double fom, con
   }
   first = __builtin_amdgcn_readfirstlane(first);
   if (first == 0x7fffffff) return pk;
-  pk.pixel = first / g.n_eps;
+  pk.pixel = g.n_eps == 2 ? first >> 1 : first / g.n_eps;
   pk.eps_idx = first - pk.pixel * g.n_eps;
   if (with_score) {
     pk.fom_new = scores[first];
@@ -613,7 +622,7 @@ template <typename T>
 hipError_t launch_table_scores(const JobEntry* tab, int n_jobs, int max_wg, hipStream_t s);
 template <typename T>
 hipError_t launch_table_move(const JobEntry* tab, int n_jobs, int max_wg, int t, uint64_t flushed,
-                             bool small, int batch, hipStream_t s);
+                             bool small, int batch, bool two_eps, hipStream_t s);
 template <typename T>
 hipError_t launch_table_finish(const JobEntry* tab, int n_jobs, int max_wg, int t, hipStream_t s);
 int gather_move_workgroups(const Geo& g);

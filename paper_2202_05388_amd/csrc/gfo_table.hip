@@ -82,11 +82,13 @@ extern "C" int gfo_greedy_steps_table(const gfo_problem* probs, gfo_state* state
   const bool small = move_small_grid(g0);
   const int batch = states[0].delay <= 64 ? 16 : 32;
   int wg_score = 0, wg_move = 0, wg_finish = 0;
+  bool two_eps = true;   // every job's table has two entries
   for (int i = 0; i < n_jobs; ++i) {
     const JobEntry je = make_job_entry(geos[i], &states[i], lays[i], 0, 0.0);
     wg_score = je.n_score_wg > wg_score ? je.n_score_wg : wg_score;
     wg_move = je.n_move_wg > wg_move ? je.n_move_wg : wg_move;
     wg_finish = je.n_finish_wg > wg_finish ? je.n_finish_wg : wg_finish;
+    two_eps = two_eps && geos[i].n_eps == 2;
   }
   // the call's first scores, for every job
   if ((c64 ? launch_table_scores<float2>(tab, n_jobs, wg_score, stream)
@@ -107,8 +109,8 @@ extern "C" int gfo_greedy_steps_table(const gfo_problem* probs, gfo_state* state
       st->pending_calls = 0;
       flushed |= (uint64_t)1 << i;
     }
-    if ((c64 ? launch_table_move<float2>(tab, n_jobs, wg_move, t, flushed, small, batch, stream)
-             : launch_table_move<double2>(tab, n_jobs, wg_move, t, flushed, small, batch, stream)) !=
+    if ((c64 ? launch_table_move<float2>(tab, n_jobs, wg_move, t, flushed, small, batch, two_eps, stream)
+             : launch_table_move<double2>(tab, n_jobs, wg_move, t, flushed, small, batch, two_eps, stream)) !=
         hipSuccess)
       return GFO_EHIP;
     for (int i = 0; i < n_jobs; ++i) ++states[i].pending_calls;
