@@ -91,7 +91,6 @@ Layout make_layout(const gfo_problem* p, int64_t ld, int32_t kmax) {
   L.pfirst2 = take(kScoreMaxBlocks * 4);
   L.rk_S = take(4096);
   L.rk_M = take(K * K * 16);
-  L.rk_U64 = take(R * K * 16);
   L.rk_A = take(R * 2 * K * 4);
   L.rk_B = take(2 * 2 * K * (size_t)ld * 4);
   L.rk_Abf = take(R * 2 * K * 2);

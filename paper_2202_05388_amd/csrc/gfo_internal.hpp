@@ -195,6 +195,7 @@ constexpr int kScoreMaxBlocks = 1024;
 // pending terms, up to GFO_MAX_DELAY terms.
 constexpr int kSplitUnits = 12 * (GFO_MAX_DELAY / 16);
 constexpr int kSelectThreads = 1024;
+constexpr int kTopkThreads = 256;   // spaced top-k from the workgroup summaries
 
 // ------------------------------------------------------------------ workspace layout
 struct Layout {
@@ -214,7 +215,6 @@ struct Layout {
   // rank-k
   size_t rk_S;      // header of the accepted set (pixels, contrasts, M E[S])
   size_t rk_M;      // K x K double2 (FP64 Woodbury core)
-  size_t rk_U64;    // R x K double2: G[:, S] in FP64
   size_t rk_A;      // R x 2K float  A operand [Re U | Im U] (U = G[:, S])
   size_t rk_B;      // 2 x 2K x ld float: B operands for the re and im outputs
   size_t rk_Abf;    // R x 2K bf16

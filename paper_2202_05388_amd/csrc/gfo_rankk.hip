@@ -44,82 +44,89 @@ __global__ __launch_bounds__(256) void k_rk_prepare(Geo g, const gfo_pick* __res
                                                     int32_t* __restrict__ status,
                                                     RkHdr* __restrict__ hdr,
                                                     double2* __restrict__ Mout) {
-  __shared__ double2 aug[KR][2 * KR + 1];
-  __shared__ double2 fcol[KR];
-  __shared__ int S[KR], en[KR];
+  // two buffers: a step reads one and writes the other, one barrier per step
+  __shared__ double2 augs[2][KR][2 * KR + 1];
+  __shared__ int S[KR], en[KR], pj[KR], pe[KR], pc0[KR];
   __shared__ double al[KR];
-  __shared__ int ns, piv, bad;
+  __shared__ double2 sE[KR];
+  __shared__ int ns;
+  if ((int)threadIdx.x < k) {   // the records and their pixels' materials, one per thread
+    const gfo_pick pk = picks[threadIdx.x];
+    const bool ok = pk.pixel >= 0 && pk.pixel < g.N && pk.eps_idx >= 0 && pk.eps_idx < g.n_eps;
+    const int cur = eps_idx[ok ? pk.pixel : 0];
+    pj[threadIdx.x] = ok && pk.eps_idx != cur ? pk.pixel : -1;
+    pe[threadIdx.x] = pk.eps_idx;
+    pc0[threadIdx.x] = cur;
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
     int s = 0;
     for (int t = 0; t < k; ++t) {
-      const gfo_pick pk = picks[t];
-      const int j = pk.pixel, e = pk.eps_idx;
-      if (j < 0 || j >= g.N || e < 0 || e >= g.n_eps || e == (int)eps_idx[j]) continue;
-      bool dup = false;
-      for (int q = 0; q < s; ++q) dup |= (S[q] == j);
-      if (dup) continue;
+      const int j = pj[t];
+      bool skip = j < 0;
+      for (int q = 0; q < s; ++q) skip |= S[q] == j;   // a pixel's first record counts
+      if (skip) continue;
       S[s] = j;
-      en[s] = e;
-      al[s] = g.k0sq * (g.eps[e] - g.eps[eps_idx[j]]);
+      en[s] = pe[t];
+      pc0[s] = pc0[t];   // s <= t
       ++s;
     }
     ns = s;
-    bad = 0;
   }
   __syncthreads();
   const int s = ns;
+  if ((int)threadIdx.x < s) {
+    al[threadIdx.x] = g.k0sq * (eps_of(g, en[threadIdx.x]) - eps_of(g, pc0[threadIdx.x]));
+    sE[threadIdx.x] = St<T>::to_d(E[S[threadIdx.x]]);
+  }
+  __syncthreads();
   // [I - B_S G_SS | B_S]
   for (int idx = threadIdx.x; idx < s * 2 * s; idx += blockDim.x) {
     const int a = idx / (2 * s), b = idx - (idx / (2 * s)) * 2 * s;
     double2 v;
     if (b < s) {
-      const double2 gab = (a == b) ? diag64[S[a]] : St<T>::to_d(G[g_at(g, S[a], S[b])]);
+      double2 gab;
+      if (a == b) gab = diag64[S[a]];
+      else gab = St<T>::to_d(G[g_at(g, S[a], S[b])]);
       v = make_double2((a == b ? 1.0 : 0.0) - al[a] * gab.x, -al[a] * gab.y);
     } else {
       v = make_double2(b - s == a ? al[a] : 0.0, 0.0);
     }
-    aug[a][b] = v;
+    augs[0][a][b] = v;
   }
   __syncthreads();
+  // Gauss-Jordan, partial pivoting (the lowest row of largest modulus).  Step c
+  // on the rows as swapped: row c takes the pivot row p times 1 / a[p][c], row p
+  // the old row c, and every row but c loses its column c.  Every wave finds the
+  // pivot itself, so a step has one barrier (it had five, and a serial search by
+  // one thread: 39 us at 16 pixels).
+  bool bad = false;
   for (int c = 0; c < s; ++c) {
-    if (threadIdx.x == 0) {
-      int p = c;
-      double best = cabs2(aug[c][c]);
-      for (int r = c + 1; r < s; ++r) {
-        const double m = cabs2(aug[r][c]);
-        if (m > best) {
-          best = m;
-          p = r;
-        }
-      }
-      if (!(best > 1e-24)) bad = 1;
-      piv = p;
-    }
-    __syncthreads();
-    const int p = piv;
-    if (p != c)
-      for (int j = threadIdx.x; j < 2 * s; j += blockDim.x) {
-        const double2 t = aug[c][j];
-        aug[c][j] = aug[p][j];
-        aug[p][j] = t;
-      }
-    __syncthreads();
-    const double2 inv = rdiv(1.0, aug[c][c]);
-    __syncthreads();
-    for (int j = threadIdx.x; j < 2 * s; j += blockDim.x) aug[c][j] = cmul(aug[c][j], inv);
-    for (int r = threadIdx.x; r < s; r += blockDim.x) fcol[r] = aug[r][c];
-    __syncthreads();
+    double2 (*aug)[2 * KR + 1] = augs[c & 1];
+    double2 (*out)[2 * KR + 1] = augs[(c + 1) & 1];
+    const int lane = threadIdx.x & 63;
+    const double m = lane >= c && lane < s ? cabs2(aug[lane][c]) : -1.0;
+    const double best = wave_max(m);
+    const double d = cabs2(aug[c][c]);
+    // a comparison with NaN is false: the diagonal then stays the pivot
+    const uint64_t at = __ballot(m == best && m > d);
+    const int p = at ? __builtin_ctzll(at) : c;
+    if (!(cabs2(aug[p][c]) > 1e-24)) bad = true;
+    const double2 inv = rdiv(1.0, aug[p][c]);
     for (int idx = threadIdx.x; idx < s * 2 * s; idx += blockDim.x) {
       const int r = idx / (2 * s), j = idx - (idx / (2 * s)) * 2 * s;
+      const double2 pc = cmul(aug[p][j], inv);
+      double2 v = pc;
       if (r != c) {
-        const double2 f = fcol[r];
-        const double2 pc = aug[c][j];
-        aug[r][j] = make_double2(aug[r][j].x - (f.x * pc.x - f.y * pc.y),
-                                 aug[r][j].y - (f.x * pc.y + f.y * pc.x));
+        const int rs = r == p ? c : r;
+        const double2 f = aug[rs][c], x = aug[rs][j];
+        v = make_double2(x.x - (f.x * pc.x - f.y * pc.y), x.y - (f.x * pc.y + f.y * pc.x));
       }
+      out[r][j] = v;
     }
     __syncthreads();
   }
+  double2 (*aug)[2 * KR + 1] = augs[s & 1];
   if (threadIdx.x == 0 && bad) atomicOr(status, GFO_STATUS_SINGULAR);
   const int sv = bad ? 0 : s;
   for (int idx = threadIdx.x; idx < KR * KR; idx += blockDim.x) {
@@ -130,7 +137,7 @@ __global__ __launch_bounds__(256) void k_rk_prepare(Geo g, const gfo_pick* __res
     const int a = threadIdx.x;
     double2 y = make_double2(0.0, 0.0);
     if (a < sv)
-      for (int b = 0; b < sv; ++b) y = cadd(y, cmul(aug[a][s + b], St<T>::to_d(E[S[b]])));
+      for (int b = 0; b < sv; ++b) y = cadd(y, cmul(aug[a][s + b], sE[b]));
     hdr->y[a] = y;
     hdr->S[a] = a < sv ? S[a] : 0;
     hdr->e_new[a] = a < sv ? en[a] : 0;
@@ -154,153 +161,114 @@ __global__ __launch_bounds__(256) void k_rk_prepare(Geo g, const gfo_pick* __res
   }
 }
 
-// ------------------------------------------------------------------ RK2: rows (U = G[:, S])
-// One thread per row in 64-thread workgroups (a few hundred workgroups at
-// 128 x 128); the s <= 32 loads of a row are unrolled, so all of them are in
-// flight together.  Writes U64 (R x KR, FP64, for the diagonal in RK3) and the
-// A operand row-major [r][kappa], kappa < KP: Re U, kappa >= KP: Im U, in FP32
-// (Af) or BF16 (Abf), with 16-byte stores; E[r] += U[r, :] y.
-typedef __bf16 bf16x8v __attribute__((ext_vector_type(8)));
-template <typename T>
-__global__ __launch_bounds__(64) void k_rk_rows(Geo g, const RkHdr* __restrict__ hdr,
-                                                const T* __restrict__ G,
-                                                const double2* __restrict__ diag64,
-                                                T* __restrict__ E, double2* __restrict__ U64,
-                                                float* __restrict__ Af, __bf16* __restrict__ Abf,
-                                                int bf16) {
-  __shared__ int S[KR];
-  __shared__ double2 y[KR];
+// ------------------------------------------------------------------ RK2: operand panels
+// U = G[:, S] (R rows) and W = M G[S, :] (ld columns) with the O(R) and O(N)
+// updates, one pass: index q < N is design row q and design column q, the later
+// ones monitor rows (U) or padding columns (W = 0).  A workgroup of four waves
+// takes 64 indices, one per lane; wave w computes the rows a = w, w + 4, ... of
+// W and the entries a of U, and the partial sums of U y and U W meet in LDS.
+//   A operand, row-major [r][kappa]: kappa < KP: Re U, kappa >= KP: Im U;
+//   B operands per column [q][out][kappa]: out 0 (real part of the product):
+//   [Re W ; -Im W], out 1 (imaginary part): [Im W ; Re W]; FP32 or BF16.
+//   E[r] += U[r, :] y,  diag64[q] += U[q, :] W[:, q].
+// M is read uniformly (scalar loads).  Bound by latency at these sizes: 11 MB of
+// scattered reads of G's columns.  One thread per row and then one per column, with U
+// in FP64 through memory between them, took 24 + 34 us at 128 x 128 and 16 pixels
+// (one wave per compute unit).
+typedef __bf16 bf16x4v __attribute__((ext_vector_type(4)));
+template <typename T, int KP>
+__global__ __launch_bounds__(256) void k_rk_panels(Geo g, const RkHdr* __restrict__ hdr,
+                                                   const double2* __restrict__ M,
+                                                   const T* __restrict__ G, T* __restrict__ E,
+                                                   double2* __restrict__ diag64,
+                                                   float* __restrict__ Af, __bf16* __restrict__ Abf,
+                                                   float* __restrict__ Bf, __bf16* __restrict__ Bbf,
+                                                   int bf16) {
   const int s = hdr->s;
-  if (s == 0) return;
-  const int KP = hdr->kp;
-  if (threadIdx.x < KR) {
-    S[threadIdx.x] = hdr->S[threadIdx.x];
-    y[threadIdx.x] = hdr->y[threadIdx.x];
+  if (s == 0 || hdr->kp != KP) return;
+  constexpr int NA = KP / 4;   // entries per wave: a = 4 i4 + ..., see below
+  __shared__ double2 pe[3][64], pd[3][64];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t q = (int64_t)blockIdx.x * 64 + lane;
+  const bool row = q < g.R, col = q < g.ld, design = q < g.N;
+  const int64_t qc = design ? q : 0, rc = row ? q : 0;
+  // wave w: entries a in [w NA, (w + 1) NA)
+  const int a0 = w * NA;
+  T ur[NA], gr[KP];
+#pragma unroll
+  for (int i = 0; i < NA; ++i)
+    ur[i] = G[g_at(g, rc, hdr->S[a0 + i])];
+#pragma unroll
+  for (int b = 0; b < KP; ++b) gr[b] = G[g_at(g, hdr->S[b], qc)];
+  const double2 dq = diag64[qc];
+  const T Eq = E[rc];
+  double2 u[NA], wv[NA];
+  double2 acc = make_double2(0.0, 0.0), dsum = make_double2(0.0, 0.0);
+#pragma unroll
+  for (int i = 0; i < NA; ++i) {
+    const int c = hdr->S[a0 + i];
+    u[i] = pick_of(design && q == c, dq, St<T>::to_d(ur[i]));
+    u[i] = pick_of(row && a0 + i < s, u[i], make_double2(0.0, 0.0));
+    acc = cadd(acc, cmul(u[i], hdr->y[a0 + i]));
+    wv[i] = make_double2(0.0, 0.0);
+  }
+#pragma unroll
+  for (int b = 0; b < KP; ++b) {
+    if (b < s) {   // uniform
+      double2 gb = pick_of(q == hdr->S[b], dq, St<T>::to_d(gr[b]));
+      gb = pick_of(design, gb, make_double2(0.0, 0.0));
+#pragma unroll
+      for (int i = 0; i < NA; ++i) wv[i] = cadd(wv[i], cmul(M[(a0 + i) * KR + b], gb));   // M is zero beyond s
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NA; ++i) dsum = cadd(dsum, cmul(u[i], wv[i]));
+  if (w > 0) {
+    pe[w - 1][lane] = acc;
+    pd[w - 1][lane] = dsum;
+  }
+#pragma unroll
+  for (int i = 0; i < NA; i += 4) {
+    const f32x4v ure = {(float)u[i].x, (float)u[i + 1].x, (float)u[i + 2].x, (float)u[i + 3].x};
+    const f32x4v uim = {(float)u[i].y, (float)u[i + 1].y, (float)u[i + 2].y, (float)u[i + 3].y};
+    const f32x4v wre = {(float)wv[i].x, (float)wv[i + 1].x, (float)wv[i + 2].x, (float)wv[i + 3].x};
+    const f32x4v wim = {(float)wv[i].y, (float)wv[i + 1].y, (float)wv[i + 2].y, (float)wv[i + 3].y};
+    const int at = a0 + i;
+    if (bf16) {
+      auto cvt = [](f32x4v x) { return bf16x4v{(__bf16)x[0], (__bf16)x[1], (__bf16)x[2], (__bf16)x[3]}; };
+      if (row) {
+        __bf16* ap = Abf + q * 2 * KP + at;
+        *reinterpret_cast<bf16x4v*>(ap) = cvt(ure);
+        *reinterpret_cast<bf16x4v*>(ap + KP) = cvt(uim);
+      }
+      if (col) {
+        __bf16* bp = Bbf + q * 4 * KP + at;
+        *reinterpret_cast<bf16x4v*>(bp) = cvt(wre);
+        *reinterpret_cast<bf16x4v*>(bp + KP) = cvt(-wim);
+        *reinterpret_cast<bf16x4v*>(bp + 2 * KP) = cvt(wim);
+        *reinterpret_cast<bf16x4v*>(bp + 3 * KP) = cvt(wre);
+      }
+    } else {
+      if (row) {
+        float* ap = Af + q * 2 * KP + at;
+        *reinterpret_cast<f32x4v*>(ap) = ure;
+        *reinterpret_cast<f32x4v*>(ap + KP) = uim;
+      }
+      if (col) {
+        float* bp = Bf + q * 4 * KP + at;
+        *reinterpret_cast<f32x4v*>(bp) = wre;
+        *reinterpret_cast<f32x4v*>(bp + KP) = -wim;
+        *reinterpret_cast<f32x4v*>(bp + 2 * KP) = wim;
+        *reinterpret_cast<f32x4v*>(bp + 3 * KP) = wre;
+      }
+    }
   }
   __syncthreads();
-  const int r = blockIdx.x * 64 + threadIdx.x;
-  if (r >= g.R) return;
-  double2 u[KR];
-#pragma unroll
-  for (int a = 0; a < KR; ++a) {
-    u[a] = make_double2(0.0, 0.0);
-    if (a < s) {
-      const int c = S[a];
-      u[a] = (r == c) ? diag64[r] : St<T>::to_d(G[g_at(g, r, c)]);
-    }
-  }
-  double2 acc = make_double2(0.0, 0.0);
-#pragma unroll
-  for (int a = 0; a < KR; ++a)
-    if (a < s) acc = cadd(acc, cmul(u[a], y[a]));
-  double2* urow = U64 + (int64_t)r * KR;
-#pragma unroll
-  for (int a = 0; a < KR; ++a) urow[a] = u[a];
-  if (bf16) {
-    __bf16* arow = Abf + (int64_t)r * 2 * KP;
-#pragma unroll
-    for (int a0 = 0; a0 < KR; a0 += 8) {
-      if (a0 < KP) {
-        bf16x8v re, im;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          re[i] = (__bf16)(float)u[a0 + i].x;
-          im[i] = (__bf16)(float)u[a0 + i].y;
-        }
-        *reinterpret_cast<bf16x8v*>(arow + a0) = re;
-        *reinterpret_cast<bf16x8v*>(arow + KP + a0) = im;
-      }
-    }
-  } else {
-    float* arow = Af + (int64_t)r * 2 * KP;
-#pragma unroll
-    for (int a0 = 0; a0 < KR; a0 += 4) {
-      if (a0 < KP) {
-        const f32x4v re = {(float)u[a0].x, (float)u[a0 + 1].x, (float)u[a0 + 2].x, (float)u[a0 + 3].x};
-        const f32x4v im = {(float)u[a0].y, (float)u[a0 + 1].y, (float)u[a0 + 2].y, (float)u[a0 + 3].y};
-        *reinterpret_cast<f32x4v*>(arow + a0) = re;
-        *reinterpret_cast<f32x4v*>(arow + KP + a0) = im;
-      }
-    }
-  }
-  E[r] = St<T>::from_d(cadd(St<T>::to_d(E[r]), acc));
-}
-
-// ------------------------------------------------------------------ RK3: columns (W = M G[S, :])
-// One thread per column in 64-thread workgroups; M (FP64, KR x KR) is staged
-// in LDS and read as a broadcast.  B operands per column [q][out][kappa]: out 0
-// (real part of the product): [Re W ; -Im W], out 1 (imaginary part):
-// [Im W ; Re W], written with 16-byte stores.  diag64 += diag(U W).
-template <typename T>
-__global__ __launch_bounds__(64) void k_rk_cols(Geo g, const RkHdr* __restrict__ hdr,
-                                                const double2* __restrict__ M,
-                                                const T* __restrict__ G,
-                                                double2* __restrict__ diag64,
-                                                const double2* __restrict__ U64,
-                                                float* __restrict__ Bf, __bf16* __restrict__ Bbf,
-                                                int bf16) {
-  __shared__ double2 sM[KR * KR];
-  __shared__ int S[KR];
-  const int s = hdr->s;
-  if (s == 0) return;
-  const int KP = hdr->kp;
-  for (int i = threadIdx.x; i < KR * KR; i += 64) sM[i] = M[i];
-  if (threadIdx.x < KR) S[threadIdx.x] = hdr->S[threadIdx.x];
-  __syncthreads();
-  const int64_t q = (int64_t)blockIdx.x * 64 + threadIdx.x;
-  if (q >= g.ld) return;
-  double2 gs[KR];
-#pragma unroll
-  for (int b = 0; b < KR; ++b) {
-    gs[b] = make_double2(0.0, 0.0);
-    if (b < s && q < g.N) {
-      const int c = S[b];
-      gs[b] = (q == c) ? diag64[c] : St<T>::to_d(G[g_at(g, c, q)]);
-    }
-  }
-  double2 dsum = make_double2(0.0, 0.0);
-  const int64_t base = q * 4 * KP;
-#pragma unroll
-  for (int a0 = 0; a0 < KR; a0 += 8) {
-    if (a0 < KP) {
-      double2 w[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        w[i] = make_double2(0.0, 0.0);
-        if (a0 + i < s) {
-#pragma unroll
-          for (int b = 0; b < KR; ++b)
-            if (b < s) w[i] = cadd(w[i], cmul(sM[(a0 + i) * KR + b], gs[b]));
-          if (q < g.N) dsum = cadd(dsum, cmul(U64[q * KR + a0 + i], w[i]));
-        }
-      }
-      if (bf16) {
-        bf16x8v wr, wi, nwi;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          wr[i] = (__bf16)(float)w[i].x;
-          wi[i] = (__bf16)(float)w[i].y;
-          nwi[i] = (__bf16)(float)(-w[i].y);
-        }
-        *reinterpret_cast<bf16x8v*>(Bbf + base + a0) = wr;
-        *reinterpret_cast<bf16x8v*>(Bbf + base + KP + a0) = nwi;
-        *reinterpret_cast<bf16x8v*>(Bbf + base + 2 * KP + a0) = wi;
-        *reinterpret_cast<bf16x8v*>(Bbf + base + 3 * KP + a0) = wr;
-      } else {
-#pragma unroll
-        for (int j = 0; j < 8; j += 4) {
-          const f32x4v wr = {(float)w[j].x, (float)w[j + 1].x, (float)w[j + 2].x, (float)w[j + 3].x};
-          const f32x4v wi = {(float)w[j].y, (float)w[j + 1].y, (float)w[j + 2].y, (float)w[j + 3].y};
-          const f32x4v nwi = {-wi[0], -wi[1], -wi[2], -wi[3]};
-          *reinterpret_cast<f32x4v*>(Bf + base + a0 + j) = wr;
-          *reinterpret_cast<f32x4v*>(Bf + base + KP + a0 + j) = nwi;
-          *reinterpret_cast<f32x4v*>(Bf + base + 2 * KP + a0 + j) = wi;
-          *reinterpret_cast<f32x4v*>(Bf + base + 3 * KP + a0 + j) = wr;
-        }
-      }
-    }
-  }
-  if (q < g.N) diag64[q] = cadd(diag64[q], dsum);
+  if (w > 0) return;
+  acc = cadd(cadd(acc, pe[0][lane]), cadd(pe[1][lane], pe[2][lane]));
+  dsum = cadd(cadd(dsum, pd[0][lane]), cadd(pd[1][lane], pd[2][lane]));
+  if (row) E[q] = St<T>::from_d(cadd(St<T>::to_d(Eq), acc));
+  if (design) diag64[q] = cadd(dq, dsum);
 }
 
 // ------------------------------------------------------------------ RK4: MFMA update
@@ -313,110 +281,6 @@ __device__ __forceinline__ bool rk_below_diagonal(int r0, int nr, int64_t c_end,
   return skip_below > 0 && r0 + nr <= skip_below && c_end <= r0;
 }
 
-
-// Workgroup: 4 waves over a 64 x 64 complex tile per iteration (wave w: column
-// tile w & 1, row tile w >> 1), RBLK row blocks of 64 rows per workgroup.  The
-// A rows of the iteration are staged in LDS and shared by the two column waves;
-// each wave keeps its B fragment in registers for the whole workgroup.
-// 32x32 accumulator layout: element e of lane l is row 8*(e/4) + 4*(l/32) + e%4,
-// column l%32.
-constexpr int kRkRowBlocks = 8;
-
-template <int KP, bool BF16>
-__global__ __launch_bounds__(256) void k_rk_mfma(int R, int64_t ld, int skip_below,
-                                                 const int32_t* __restrict__ gate_count,
-                                                 const int32_t* __restrict__ gate_kp,
-                                                 const float* __restrict__ Af,
-                                                 const float* __restrict__ Bf,
-                                                 const __bf16* __restrict__ Abf,
-                                                 const __bf16* __restrict__ Bbf,
-                                                 float2* __restrict__ G) {
-  // gate_count: number of active terms (0 = nothing to do); gate_kp: the rank
-  // padding chosen on the device (the instantiation that does not match exits)
-  if (*gate_count == 0 || (gate_kp != nullptr && *gate_kp != KP)) return;
-  constexpr int K2 = 2 * KP;
-  constexpr int PADF = BF16 ? 4 : 1;   // LDS row padding (floats): 16-B rows for BF16, odd stride for FP32
-  __shared__ __attribute__((aligned(16))) float sA[64 * (K2 + PADF)];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int ncg = (int)(ld / 64);
-  int cg, rg;
-  ut_group(blockIdx.x, ncg, skip_below / (64 * kRkRowBlocks), 64 * kRkRowBlocks, 64, rg, cg);
-  const int q = cg * 64 + (w & 1) * 32 + (lane & 31);
-  const int h = lane >> 5;
-  // B fragments for this lane's column
-  constexpr int NB = BF16 ? K2 / 16 : KP;                 // MFMA instructions per output
-  float bre[BF16 ? 1 : KP], bim[BF16 ? 1 : KP];
-  bf16x8 bre8[BF16 ? NB : 1], bim8[BF16 ? NB : 1];
-  if constexpr (BF16) {
-#pragma unroll
-    for (int t = 0; t < NB; ++t) {
-      bre8[t] = *reinterpret_cast<const bf16x8*>(Bbf + (int64_t)q * 2 * K2 + 16 * t + 8 * h);
-      bim8[t] = *reinterpret_cast<const bf16x8*>(Bbf + (int64_t)q * 2 * K2 + K2 + 16 * t + 8 * h);
-    }
-  } else {
-#pragma unroll
-    for (int t = 0; t < KP; ++t) {
-      bre[t] = Bf[(int64_t)q * 2 * K2 + h * KP + t];
-      bim[t] = Bf[(int64_t)q * 2 * K2 + K2 + h * KP + t];
-    }
-  }
-  for (int rb = 0; rb < kRkRowBlocks; ++rb) {
-    const int r0 = (rg * kRkRowBlocks + rb) * 64;
-    if (r0 >= R) break;
-    __syncthreads();
-    // stage A rows [r0, r0 + 64) in LDS (FP32 or BF16 bits, K2 values per row)
-    if constexpr (BF16) {
-      constexpr int per_row = K2 / 8;                     // 16-byte chunks per row
-      for (int c = threadIdx.x; c < 64 * per_row; c += 256) {
-        const int rr = c / per_row, cc = c - (c / per_row) * per_row;
-        const int r = r0 + rr;
-        f32x4v v = {0.f, 0.f, 0.f, 0.f};
-        if (r < R) v = *reinterpret_cast<const f32x4v*>(Abf + (int64_t)r * K2 + 8 * cc);
-        *reinterpret_cast<f32x4v*>(&sA[rr * (K2 + PADF) + 4 * cc]) = v;
-      }
-    } else {
-      for (int c = threadIdx.x; c < 64 * K2; c += 256) {
-        const int rr = c / K2, cc = c - (c / K2) * K2;
-        const int r = r0 + rr;
-        sA[rr * (K2 + PADF) + cc] = (r < R) ? Af[(int64_t)r * K2 + cc] : 0.f;
-      }
-    }
-    __syncthreads();
-    const int rt = r0 + (w >> 1) * 32;
-    // load the G tile into the accumulators
-    f32x16 accr, acci;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int r = rt + 8 * (e >> 2) + 4 * h + (e & 3);
-      float2 gv = make_float2(0.f, 0.f);
-      if (r < R) gv = G[(int64_t)r * ld + q];
-      accr[e] = gv.x;
-      acci[e] = gv.y;
-    }
-    const float* arow = &sA[((w >> 1) * 32 + (lane & 31)) * (K2 + PADF)];
-    if constexpr (BF16) {
-#pragma unroll
-      for (int t = 0; t < NB; ++t) {
-        const bf16x8 a8 = *reinterpret_cast<const bf16x8*>(
-            reinterpret_cast<const __bf16*>(arow) + 16 * t + 8 * h);
-        accr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a8, bre8[t], accr, 0, 0, 0);
-        acci = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a8, bim8[t], acci, 0, 0, 0);
-      }
-    } else {
-#pragma unroll
-      for (int t = 0; t < KP; ++t) {
-        const float a = arow[h * KP + t];
-        accr = __builtin_amdgcn_mfma_f32_32x32x2f32(a, bre[t], accr, 0, 0, 0);
-        acci = __builtin_amdgcn_mfma_f32_32x32x2f32(a, bim[t], acci, 0, 0, 0);
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int r = rt + 8 * (e >> 2) + 4 * h + (e & 3);
-      if (r < R) G[(int64_t)r * ld + q] = make_float2(accr[e], acci[e]);
-    }
-  }
-}
 
 // ------------------------------------------------------------------ RK4': streaming MFMA update
 // Workgroup: 4 waves side by side over 128 columns (wave w: columns
@@ -589,11 +453,137 @@ __global__ __launch_bounds__(256, (!BF16 && TM == 1 && KP == 16 && RB <= 4) ? 3 
   }
 }
 
-// Update variants (autotuner): the 64 x 64 form that accumulates the products
-// onto G (k_rk_mfma) and the streaming forms above with 4 or 8 row blocks per
-// workgroup.  The streaming forms sum the products from zero in the same order
-// and add G once, so they agree with each other bit for bit; against the
-// accumulating form they differ by FP32 rounding.
+// ------------------------------------------------------------------ RK4'': streaming update onto G
+// The products accumulated onto G in the order of kappa, in the streaming form's
+// layout: four waves side by side over 128 columns, RB blocks of 32 rows, the
+// workgroup's A rows in LDS once, B fragments in registers, no barrier in the row
+// loop.  A wave requests the next block's G before the current block's products,
+// which need theirs: the loads are in flight during the products of the block
+// before.  Bound by HBM (G read and written once, non-temporal).  128 x 128, whole
+// matrix, 4.31 GB: FP32 763 us at rank 16, 872 us at rank 32; BF16 746 and 734 us;
+// with one 64 x 64 tile per workgroup and step and G waited for in each (the same
+// bits) 916, 1711, 838 and 827 us.
+template <int KP, bool BF16, int RB>
+__global__ __launch_bounds__(256, KP == 16 ? 3 : 2) void k_rk_accum(int R, int64_t ld, int skip_below,
+                                                  const int32_t* __restrict__ gate_count,
+                                                  const int32_t* __restrict__ gate_kp,
+                                                  const float* __restrict__ Af,
+                                                  const float* __restrict__ Bf,
+                                                  const __bf16* __restrict__ Abf,
+                                                  const __bf16* __restrict__ Bbf,
+                                                  float2* __restrict__ G) {
+  if (*gate_count == 0 || *gate_kp != KP) return;
+  constexpr int K2 = 2 * KP;
+  constexpr int AW = BF16 ? K2 / 2 + 4 : K2 + 1;    // LDS row width (floats), as in k_rk_stream
+  __shared__ __attribute__((aligned(16))) float sA[RB * 32 * AW];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, h = lane >> 5;
+  const int ncg = (int)((ld + 127) / 128);
+  int cg, rg;
+  ut_group(blockIdx.x, ncg, skip_below / (RB * 32), RB * 32, 128, rg, cg);
+  const int rbase = rg * RB * 32;
+  const int64_t q = (int64_t)cg * 128 + 32 * w + (lane & 31);
+  const bool qok = q < ld;                          // alike in a wave (ld is a multiple of 64)
+  const int64_t qc = qok ? q : 0;
+  if constexpr (BF16) {
+    constexpr int per_row = K2 / 8;                 // 16-byte chunks per row
+    for (int c = threadIdx.x; c < RB * 32 * per_row; c += 256) {
+      const int rr = c / per_row, cc = c - (c / per_row) * per_row;
+      const int r = rbase + rr;
+      f32x4v v = {0.f, 0.f, 0.f, 0.f};
+      if (r < R) v = *reinterpret_cast<const f32x4v*>(Abf + (int64_t)r * K2 + 8 * cc);
+      *reinterpret_cast<f32x4v*>(&sA[rr * AW + 4 * cc]) = v;
+    }
+  } else {
+    for (int c = threadIdx.x; c < RB * 32 * (K2 / 4); c += 256) {
+      const int rr = c / (K2 / 4), cc = c - (c / (K2 / 4)) * (K2 / 4);
+      const int r = rbase + rr;
+      f32x4v v = {0.f, 0.f, 0.f, 0.f};
+      if (r < R) v = *reinterpret_cast<const f32x4v*>(Af + (int64_t)r * K2 + 4 * cc);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sA[rr * AW + 4 * cc + i] = v[i];
+    }
+  }
+  constexpr int NB = BF16 ? K2 / 16 : KP;           // matrix instructions per output
+  float bre[BF16 ? 1 : KP], bim[BF16 ? 1 : KP];
+  bf16x8 bre8[BF16 ? NB : 1], bim8[BF16 ? NB : 1];
+  if constexpr (BF16) {
+#pragma unroll
+    for (int t = 0; t < NB; ++t) {
+      bre8[t] = *reinterpret_cast<const bf16x8*>(Bbf + qc * 2 * K2 + 16 * t + 8 * h);
+      bim8[t] = *reinterpret_cast<const bf16x8*>(Bbf + qc * 2 * K2 + K2 + 16 * t + 8 * h);
+    }
+  } else {
+#pragma unroll
+    for (int t = 0; t < KP; t += 4) {
+      const f32x4v vr = *reinterpret_cast<const f32x4v*>(Bf + qc * 2 * K2 + h * KP + t);
+      const f32x4v vi = *reinterpret_cast<const f32x4v*>(Bf + qc * 2 * K2 + K2 + h * KP + t);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        bre[t + i] = vr[i];
+        bim[t + i] = vi[i];
+      }
+    }
+  }
+  __syncthreads();
+  if (!qok) return;                                 // no barrier below
+  f32x2v ga[16], gb[16];
+  auto load = [&](int rb, f32x2v(&gv)[16]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int r = rbase + rb * 32 + 8 * (e >> 2) + 4 * h + (e & 3);
+      gv[e] = __builtin_nontemporal_load(reinterpret_cast<const f32x2v*>(G + (int64_t)(r < R ? r : R - 1) * ld + q));
+    }
+  };
+  auto block = [&](int rb, f32x2v(&gv)[16]) __attribute__((always_inline)) {
+    f32x16 accr, acci;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      accr[e] = gv[e][0];
+      acci[e] = gv[e][1];
+    }
+    const float* arow = &sA[(rb * 32 + (lane & 31)) * AW];
+    if constexpr (BF16) {
+#pragma unroll
+      for (int t = 0; t < NB; ++t) {
+        const bf16x8 a8 = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const __bf16*>(arow) + 16 * t + 8 * h);
+        accr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a8, bre8[t], accr, 0, 0, 0);
+        acci = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a8, bim8[t], acci, 0, 0, 0);
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < KP; ++t) {
+        const float av = arow[h * KP + t];
+        accr = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bre[t], accr, 0, 0, 0);
+        acci = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bim[t], acci, 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int r = rbase + rb * 32 + 8 * (e >> 2) + 4 * h + (e & 3);
+      if (r < R)
+        __builtin_nontemporal_store(f32x2v{accr[e], acci[e]}, reinterpret_cast<f32x2v*>(G + (int64_t)r * ld + q));
+    }
+  };
+  static_assert(RB % 2 == 0, "two register sets alternate");
+  load(0, ga);
+#pragma unroll
+  for (int rb = 0; rb < RB; rb += 2) {
+    if (rbase + rb * 32 >= R) break;
+    load(rb + 1, gb);
+    __builtin_amdgcn_sched_barrier(0);
+    block(rb, ga);
+    if (rbase + (rb + 1) * 32 >= R) break;
+    if (rb + 2 < RB) load(rb + 2, ga);
+    __builtin_amdgcn_sched_barrier(0);
+    block(rb + 1, gb);
+  }
+}
+
+// Update variants (autotuner): the form that accumulates the products onto G
+// (acc64, k_rk_accum, the default) and the streaming forms above with 4 or 8 row
+// blocks per workgroup.  The streaming forms sum the products from zero in the
+// same order and add G once, so they agree with each other bit for bit; against
+// the accumulating form they differ by FP32 rounding.
 static const char* const kRkNames[] = {"acc64",     "pre128_r4",   "pre128_r8",  "lds128_r4",
                                        "lds128_r8", "pre128t2_r2", "pre128t2_r4"};
 constexpr int kRkCount = (int)(sizeof(kRkNames) / sizeof(kRkNames[0]));
@@ -607,17 +597,53 @@ int rk_set_variant(int i) {
 }
 int rk_get_variant() { return g_rk_sel.load(); }
 
-template <bool BF16, int RB, bool LDSEPI, int TM = 1>
-static void launch_rk_stream(const Geo& g, RkHdr* hdr, const float* Af, const float* Bf,
-                             const __bf16* Abf, const __bf16* Bbf, float2* G, hipStream_t s) {
+// Operands and grid data of one update launch.
+struct RkArgs {
+  RkHdr* hdr;
+  const float *Af, *Bf;
+  const __bf16 *Abf, *Bbf;
+  float2* G;
+  hipStream_t s;
+};
+
+template <int KP, bool BF16, int RB, bool LDSEPI, int TM = 1>
+static void launch_rk_stream(const Geo& g, const RkArgs& a) {
   const int ncg = (int)((g.ld + 127) / 128);
   const int H = 32 * TM * RB, nrg = (g.R + H - 1) / H;
   const int skip = g.upper ? g.N : 0;
   const dim3 grid((unsigned)ut_group_count(nrg, ncg, skip / H, H, 128));
-  hipLaunchKernelGGL((k_rk_stream<16, BF16, RB, LDSEPI, TM>), grid, dim3(256), 0, s, g.R, g.ld, skip,
-                     &hdr->s, &hdr->kp, Af, Bf, Abf, Bbf, G);
-  hipLaunchKernelGGL((k_rk_stream<32, BF16, RB, LDSEPI, TM>), grid, dim3(256), 0, s, g.R, g.ld, skip,
-                     &hdr->s, &hdr->kp, Af, Bf, Abf, Bbf, G);
+  hipLaunchKernelGGL((k_rk_stream<KP, BF16, RB, LDSEPI, TM>), grid, dim3(256), 0, a.s, g.R, g.ld, skip,
+                     &a.hdr->s, &a.hdr->kp, a.Af, a.Bf, a.Abf, a.Bbf, a.G);
+}
+
+// workgroups of the accumulating update with H rows each
+static int64_t rk_accum_groups(const Geo& g, int H) {
+  return ut_group_count((g.R + H - 1) / H, (int)((g.ld + 127) / 128), (g.upper ? g.N : 0) / H, H, 128);
+}
+
+template <int KP, bool BF16, int RB>
+static void launch_rk_accum(const Geo& g, const RkArgs& a) {
+  hipLaunchKernelGGL((k_rk_accum<KP, BF16, RB>), dim3((unsigned)rk_accum_groups(g, 32 * RB)), dim3(256), 0, a.s,
+                     g.R, g.ld, g.upper ? g.N : 0, &a.hdr->s, &a.hdr->kp, a.Af, a.Bf, a.Abf, a.Bbf, a.G);
+}
+
+template <int KP, bool BF16>
+static void launch_rk_update(const Geo& g, const RkArgs& a) {
+  switch (rk_get_variant()) {
+    case 1: launch_rk_stream<KP, BF16, 4, false>(g, a); break;
+    case 2: launch_rk_stream<KP, BF16, 8, false>(g, a); break;
+    case 3: launch_rk_stream<KP, BF16, 4, true>(g, a); break;
+    case 4: launch_rk_stream<KP, BF16, 8, true>(g, a); break;
+    case 5: launch_rk_stream<KP, BF16, 2, false, 2>(g, a); break;
+    case 6: launch_rk_stream<KP, BF16, 4, false, 2>(g, a); break;
+    // 128 rows per workgroup; 256 for FP32 operands of rank 32 once that leaves
+    // four workgroups per compute unit (128 x 128: 872 against 946 us, the B
+    // operands being read half as often; 64 x 64, upper triangle, 270 workgroups:
+    // 70 against 57 us)
+    default:
+      if (KP == 32 && !BF16 && rk_accum_groups(g, 256) >= 1024) launch_rk_accum<KP, BF16, 8>(g, a);
+      else launch_rk_accum<KP, BF16, 4>(g, a);
+  }
 }
 
 hipError_t launch_rank_k(const Geo& g, gfo_state* st, const Layout& L, const gfo_pick* picks, int k,
@@ -626,7 +652,6 @@ hipError_t launch_rank_k(const Geo& g, gfo_state* st, const Layout& L, const gfo
   char* w = (char*)st->work;
   RkHdr* hdr = (RkHdr*)(w + L.rk_S);
   double2* M = (double2*)(w + L.rk_M);
-  double2* U64 = (double2*)(w + L.rk_U64);
   float* Af = (float*)(w + L.rk_A);
   float* Bf = (float*)(w + L.rk_B);
   __bf16* Abf = (__bf16*)(w + L.rk_Abf);
@@ -636,64 +661,25 @@ hipError_t launch_rank_k(const Geo& g, gfo_state* st, const Layout& L, const gfo
   hipLaunchKernelGGL(k_rk_prepare<float2>, dim3(1), dim3(256), 0, s, g, picks, k,
                      (const float2*)G, (const float2*)st->E, (const double2*)st->diag64,
                      st->eps_idx, st->flips, st->flip_cap, st->n_flips, st->status, hdr, M);
-  hipLaunchKernelGGL(k_rk_rows<float2>, dim3((g.R + 63) / 64), dim3(64), 0, s, g,
-                     (const RkHdr*)hdr, (const float2*)G, (const double2*)st->diag64,
-                     (float2*)st->E, U64, Af, Abf, bf);
-  hipLaunchKernelGGL(k_rk_cols<float2>, dim3((unsigned)((g.ld + 63) / 64)), dim3(64), 0, s, g,
-                     (const RkHdr*)hdr, (const double2*)M, (const float2*)G,
-                     (double2*)st->diag64, (const double2*)U64, Bf, Bbf, bf);
+  // the rank padding (16 or 32) is decided on the device (sentinels and repeated
+  // pixels do not count): for k > 16 both instantiations are launched and the one
+  // that does not match exits at once
+  const int64_t np = g.R > g.ld ? (int64_t)g.R : g.ld;
+  const dim3 pgrid((unsigned)((np + 63) / 64));
+  hipLaunchKernelGGL((k_rk_panels<float2, 16>), pgrid, dim3(256), 0, s, g, (const RkHdr*)hdr, (const double2*)M,
+                     (const float2*)G, (float2*)st->E, (double2*)st->diag64, Af, Abf, Bf, Bbf, bf);
+  if (k > 16)
+    hipLaunchKernelGGL((k_rk_panels<float2, 32>), pgrid, dim3(256), 0, s, g, (const RkHdr*)hdr, (const double2*)M,
+                       (const float2*)G, (float2*)st->E, (double2*)st->diag64, Af, Abf, Bf, Bbf, bf);
   hipEvent_t before, after;
   k1_take_timing(&before, &after);
   if (hipError_t er = record_event(before, s)) return note_hip(er);
-  // the rank padding (16 or 32) is decided on the device; both instantiations are
-  // launched and the one that does not match exits at once
-  const float* cAf = Af;
-  const float* cBf = Bf;
-  const __bf16* cAbf = Abf;
-  const __bf16* cBbf = Bbf;
-  switch (rk_get_variant()) {
-    case 1:
-      if (bf) launch_rk_stream<true, 4, false>(g, hdr, cAf, cBf, cAbf, cBbf, G, s);
-      else launch_rk_stream<false, 4, false>(g, hdr, cAf, cBf, cAbf, cBbf, G, s);
-      break;
-    case 2:
-      if (bf) launch_rk_stream<true, 8, false>(g, hdr, cAf, cBf, cAbf, cBbf, G, s);
-      else launch_rk_stream<false, 8, false>(g, hdr, cAf, cBf, cAbf, cBbf, G, s);
-      break;
-    case 3:
-      if (bf) launch_rk_stream<true, 4, true>(g, hdr, cAf, cBf, cAbf, cBbf, G, s);
-      else launch_rk_stream<false, 4, true>(g, hdr, cAf, cBf, cAbf, cBbf, G, s);
-      break;
-    case 4:
-      if (bf) launch_rk_stream<true, 8, true>(g, hdr, cAf, cBf, cAbf, cBbf, G, s);
-      else launch_rk_stream<false, 8, true>(g, hdr, cAf, cBf, cAbf, cBbf, G, s);
-      break;
-    case 5:
-      if (bf) launch_rk_stream<true, 2, false, 2>(g, hdr, cAf, cBf, cAbf, cBbf, G, s);
-      else launch_rk_stream<false, 2, false, 2>(g, hdr, cAf, cBf, cAbf, cBbf, G, s);
-      break;
-    case 6:
-      if (bf) launch_rk_stream<true, 4, false, 2>(g, hdr, cAf, cBf, cAbf, cBbf, G, s);
-      else launch_rk_stream<false, 4, false, 2>(g, hdr, cAf, cBf, cAbf, cBbf, G, s);
-      break;
-    default: {
-      const int ncg = (int)(g.ld / 64);
-      const int H = 64 * kRkRowBlocks, nrg = (g.R + H - 1) / H;
-      const int skip = g.upper ? g.N : 0;
-      const dim3 grid((unsigned)ut_group_count(nrg, ncg, skip / H, H, 64));
-      if (bf) {
-        hipLaunchKernelGGL((k_rk_mfma<16, true>), grid, dim3(256), 0, s, g.R, g.ld, skip, &hdr->s,
-                           &hdr->kp, cAf, cBf, cAbf, cBbf, G);
-        hipLaunchKernelGGL((k_rk_mfma<32, true>), grid, dim3(256), 0, s, g.R, g.ld, skip, &hdr->s,
-                           &hdr->kp, cAf, cBf, cAbf, cBbf, G);
-      } else {
-        hipLaunchKernelGGL((k_rk_mfma<16, false>), grid, dim3(256), 0, s, g.R, g.ld, skip, &hdr->s,
-                           &hdr->kp, cAf, cBf, cAbf, cBbf, G);
-        hipLaunchKernelGGL((k_rk_mfma<32, false>), grid, dim3(256), 0, s, g.R, g.ld, skip, &hdr->s,
-                           &hdr->kp, cAf, cBf, cAbf, cBbf, G);
-      }
-      break;
-    }
+  const RkArgs ra{hdr, Af, Bf, Abf, Bbf, G, s};
+  if (bf) launch_rk_update<16, true>(g, ra);
+  else launch_rk_update<16, false>(g, ra);
+  if (k > 16) {
+    if (bf) launch_rk_update<32, true>(g, ra);
+    else launch_rk_update<32, false>(g, ra);
   }
   if (hipError_t er = record_event(after, s)) return note_hip(er);
   return note_hip(hipGetLastError());

@@ -42,7 +42,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_score(
 // Single workgroup.  Greedy rule with the relative tie band tau and the
 // lowest-(pixel, material) winner, repeated topk times with the spacing
 // exclusion.  Modifies `scores` (marks excluded candidates -inf).
-template <typename T>
+template <typename T, int NE>
 __global__ __launch_bounds__(kSelectThreads) void k_select(
     Geo g, const T* __restrict__ E, double* __restrict__ scores, const double* __restrict__ partial,
     const int* __restrict__ pfirst, int nblk, double tau, int topk, int spacing,
@@ -57,114 +57,162 @@ __global__ __launch_bounds__(kSelectThreads) void k_select(
     return;
   }
   const int total = g.N * g.n_eps;
-  const int win = spacing > 1 ? spacing - 1 : 0;
+  const int win = spacing > 1 ? min(spacing - 1, max(g.ny, g.nx)) : 0;   // (a larger one covers the grid)
   int t = 0;
-  if (nblk * kScoreThreads >= g.N && blockDim.x == kSelectThreads) {
+  if (nblk * kScoreThreads >= g.N) {
     // One pixel per score thread: workgroup b's scores are [b span, b span + span),
     // partial[b] their maximum and pfirst[b] the lowest index within the tie band
     // of that maximum.  Both summaries stay in LDS.  A pick takes the first chunk
     // whose maximum reaches the band; if that chunk holds the global maximum its
     // summary is the winner (the same decision as greedy_pick_block), otherwise
-    // (a near-tie across chunks) the chunk is scanned.  After the exclusion the
-    // chunks it touched are summarised again, two at a time, 512 threads and at
-    // most kSelVals scores per thread each.
-    static_assert(kSelectThreads == 1024, "two groups of eight waves");
-    constexpr int kSelVals = kScoreThreads * GFO_MAX_EPS / 512;
+    // (a near-tie across chunks) the chunk is scanned.  Every wave takes the pick
+    // on its own (lane votes, no barrier); then each chunk that the excluded
+    // window touches is summarised again by one wave, its pixels checked against
+    // the windows of the picks so far.  The marks in `scores` and the records are
+    // written at the end, so that no pick waits for a store: one read of a chunk
+    // and two barriers per pick (with whole-workgroup reductions, and with marks
+    // written and read back at every pick, 16 picks took 60 us at 128 x 128).
+    // Four waves, one per SIMD: a pick is a chain of instructions that every wave
+    // runs, and its window touches few chunks.
+    static_assert(kScoreThreads == 256, "four pixels per lane");
+    constexpr int kWaves = kTopkThreads / 64;
     __shared__ double spart[kScoreMaxBlocks];
     __shared__ int sfirst[kScoreMaxBlocks];
-    __shared__ double gm[kSelectThreads / 64];
-    __shared__ int gf[kSelectThreads / 64];
-    const int span = kScoreThreads * g.n_eps;
+    __shared__ int picked[GFO_MAX_RANK_K], pky[GFO_MAX_RANK_K], pkx[GFO_MAX_RANK_K];
+    const int n_eps = NE == 2 ? 2 : g.n_eps, span = kScoreThreads * n_eps;
+    // p / nx for p < 2^22 (here p < 2^18): (p + 1/2) / nx is at least 1 / (2 nx) away
+    // from an integer, more than the rounding of the product
+    const float inv_nx = 1.0f / (float)g.nx;
+    auto row_of = [&](int p) { return (int)(((float)p + 0.5f) * inv_nx); };
     for (int i = threadIdx.x; i < nblk; i += blockDim.x) {
       spart[i] = partial[i];
       sfirst[i] = pfirst[i];
     }
     __syncthreads();
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int grp = threadIdx.x >> 9, gi = threadIdx.x & 511;   // two groups of eight waves
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    // whether pixel (py, px) lies in the excluded window of the pick at (ky, kx)
+    auto in_window = [&](int py, int px, int ky, int kx) {
+      return py >= ky - win && py <= ky + win && px >= kx - win && px <= kx + win;
+    };
     for (; t < topk; ++t) {
       double m = -INFINITY;
-      for (int i = threadIdx.x; i < nblk; i += blockDim.x) m = fmax(m, spart[i]);
-      m = block_max(m, shd);
+      for (int i = lane; i < nblk; i += 64) m = fmax(m, spart[i]);
+      m = wave_max(m);
       if (!(m > fom * (1.0 + tau))) break;
       const double thr = tie_threshold(m, tau);
       int bq = 0x7fffffff;
-      for (int i = threadIdx.x; i < nblk; i += blockDim.x)
-        if (spart[i] >= thr) {
-          bq = i;
+      for (int i0 = 0; i0 < nblk; i0 += 64) {
+        const uint64_t v = __ballot(i0 + lane < nblk && spart[i0 + lane < nblk ? i0 + lane : 0] >= thr);
+        if (v) {
+          bq = i0 + __builtin_ctzll(v);
           break;
         }
-      bq = block_min(bq, shi);
+      }
       if (bq == 0x7fffffff) break;                    // non-finite scores
       int first = sfirst[bq];
       if (!(spart[bq] == m) || first == 0x7fffffff) {
         const int lo = bq * span, hi = min(lo + span, total);
-        int f = 0x7fffffff;
-        for (int i = lo + threadIdx.x; i < hi; i += blockDim.x)
-          if (scores[i] >= thr) {
-            f = i;
+        first = 0x7fffffff;
+        for (int i0 = lo; i0 < hi; i0 += 64) {
+          const int i = i0 + lane < hi ? i0 + lane : lo;
+          const int p = i / n_eps, py = row_of(p), px = p - py * g.nx;
+          bool ok = i0 + lane < hi && scores[i] >= thr;
+          for (int q = 0; q < t; ++q) ok = ok && !in_window(py, px, pky[q], pkx[q]);
+          const uint64_t v = __ballot(ok);
+          if (v) {
+            first = i0 + __builtin_ctzll(v);
             break;
           }
-        first = block_min(f, shi);
-      }
-      if (first == 0x7fffffff) break;
-      const int j = first / g.n_eps;
-      if (threadIdx.x == 0) {
-        gfo_pick pk;
-        pk.pixel = j;
-        pk.eps_idx = first - j * g.n_eps;
-        pk.fom_new = scores[first];
-        pk.dfom = pk.fom_new - fom;
-        out[t] = pk;
-      }
-      if (t + 1 < topk) {   // exclude the pick's window, then summarise the chunks it touched
-        const int iy = j / g.nx, ix = j - (j / g.nx) * g.nx;
-        const int w = 2 * win + 1;
-        __syncthreads();
-        for (int k = threadIdx.x; k < w * w * g.n_eps; k += blockDim.x) {
-          const int e = k % g.n_eps, cell = k / g.n_eps;
-          const int yy = iy - win + cell / w, xx = ix - win + cell % w;
-          if (yy >= 0 && yy < g.ny && xx >= 0 && xx < g.nx)
-            scores[(int64_t)(yy * g.nx + xx) * g.n_eps + e] = -INFINITY;
         }
-        __syncthreads();
+      }
+      first = __builtin_amdgcn_readfirstlane(first);
+      if (first == 0x7fffffff) break;
+      __syncthreads();      // every wave has read the summaries
+      const int j = first / n_eps, iy = row_of(j), ix = j - iy * g.nx;
+      if (threadIdx.x == 0) {
+        picked[t] = first;
+        pky[t] = iy;
+        pkx[t] = ix;
+      }
+      if (t + 1 < topk) {
         const int b_lo = (max(iy - win, 0) * g.nx + max(ix - win, 0)) / kScoreThreads;
         const int b_hi = min((min(iy + win, g.ny - 1) * g.nx + min(ix + win, g.nx - 1)) / kScoreThreads, nblk - 1);
-        for (int b0 = b_lo; b0 <= b_hi; b0 += 2) {       // uniform
-          const int b = b0 + grp;
-          const bool live = b <= b_hi;
-          const int lo = b * span, hi = live ? min(lo + span, total) : lo;
-          double v[kSelVals];
+        for (int b = b_lo + ((wv - b_lo) & (kWaves - 1)); b <= b_hi; b += kWaves) {
+          double v[4][NE];
+          int py[4], px[4];
+          bool out[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int p = b * kScoreThreads + 64 * u + lane, pc = p < g.N ? p : g.N - 1;
+#pragma unroll
+            for (int e = 0; e < NE; ++e)
+              if (NE == 2 || e < g.n_eps) v[u][e] = scores[(int64_t)pc * n_eps + e];
+            py[u] = row_of(p);
+            px[u] = p - py[u] * g.nx;
+            out[u] = p >= g.N || in_window(py[u], px[u], iy, ix);
+          }
+          // earlier picks whose window reaches this chunk (lane q looks at pick q)
+          const int qy = lane < t ? pky[lane] : 0, qx = lane < t ? pkx[lane] : 0;
+          uint64_t reach = __ballot(lane < t &&
+                                    (int64_t)(qy + win) * g.nx + qx + win >= (int64_t)b * kScoreThreads &&
+                                    (int64_t)(qy - win) * g.nx + qx - win < ((int64_t)b + 1) * kScoreThreads);
+          while (reach) {
+            const int q = __builtin_ctzll(reach);
+            reach &= reach - 1;
+            const int ky = __builtin_amdgcn_readlane(qy, q), kx = __builtin_amdgcn_readlane(qx, q);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) out[u] = out[u] || in_window(py[u], px[u], ky, kx);
+          }
           double mb = -INFINITY;
 #pragma unroll
-          for (int q = 0; q < kSelVals; ++q) {
-            const int i = lo + gi + 512 * q;
-            v[q] = i < hi ? scores[i] : -INFINITY;
-            mb = fmax(mb, v[q]);
-          }
-          mb = wave_max(mb);
-          if (lane == 0) gm[wv] = mb;
-          __syncthreads();
-          mb = -INFINITY;
+          for (int u = 0; u < 4; ++u)
 #pragma unroll
-          for (int q = 0; q < 8; ++q) mb = fmax(mb, gm[8 * grp + q]);
+            for (int e = 0; e < NE; ++e)
+              if (NE == 2 || e < g.n_eps) {
+                v[u][e] = out[u] ? -INFINITY : v[u][e];
+                mb = fmax(mb, v[u][e]);
+              }
+          mb = wave_max(mb);
           const double tb = tie_threshold(mb, tau);
           int fb = 0x7fffffff;
 #pragma unroll
-          for (int q = kSelVals - 1; q >= 0; --q)
-            if (mb > -INFINITY && v[q] >= tb) fb = lo + gi + 512 * q;
-          fb = wave_min(fb);
-          if (lane == 0) gf[wv] = fb;
-          __syncthreads();
-          if (live && gi == 0) {
-            int f = 0x7fffffff;
+          for (int u = 3; u >= 0; --u) {
+            int e_lo = NE;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) f = min(f, gf[8 * grp + q]);
+            for (int e = NE - 1; e >= 0; --e)
+              if ((NE == 2 || e < g.n_eps) && mb > -INFINITY && v[u][e] >= tb) e_lo = e;
+            const uint64_t votes = __ballot(e_lo < NE);
+            if (votes) {
+              const int l = __builtin_ctzll(votes);
+              fb = (b * kScoreThreads + 64 * u + l) * n_eps + __builtin_amdgcn_readlane(e_lo, l);
+            }
+          }
+          if (lane == 0) {
             spart[b] = mb;
-            sfirst[b] = f;
+            sfirst[b] = fb;
           }
         }
-        __syncthreads();
+      }
+      __syncthreads();
+    }
+    // the records, then the marks of every pick that another could have followed
+    if ((int)threadIdx.x < t) {
+      const int first = picked[threadIdx.x];
+      gfo_pick pk;
+      pk.pixel = first / n_eps;
+      pk.eps_idx = first - pk.pixel * n_eps;
+      pk.fom_new = scores[first];
+      pk.dfom = pk.fom_new - fom;
+      out[threadIdx.x] = pk;
+    }
+    __syncthreads();
+    for (int q = 0; q < t && q + 1 < topk; ++q) {
+      const int iy = pky[q], ix = pkx[q];
+      const int y0 = max(iy - win, 0), x0 = max(ix - win, 0);
+      const int wx = min(ix + win, g.nx - 1) - x0 + 1, cells = (min(iy + win, g.ny - 1) - y0 + 1) * wx;
+      for (int k = threadIdx.x; k < cells * n_eps; k += blockDim.x) {
+        const int cell = k / n_eps, row = cell / wx;
+        scores[(int64_t)((y0 + row) * g.nx + x0 + cell - row * wx) * n_eps + (k - cell * n_eps)] = -INFINITY;
       }
     }
   } else {
@@ -354,10 +402,11 @@ static hipError_t score_typed(const Geo& g, const gfo_state* st, const ScoreBufs
   hipLaunchKernelGGL(k_score<T>, dim3(nblk), dim3(kScoreThreads), 0, s, g, (const T*)st->G,
                      (const T*)st->E, (const double2*)st->diag64, (const uint8_t*)st->eps_idx, mask,
                      tau, b.scores, b.partial, b.pfirst, st->status);
-  // the greedy pick reads the workgroup summaries (one wave); the spaced top-k
-  // rescans every score after each pick
-  const int sel_threads = topk == 1 ? 64 : kSelectThreads;
-  hipLaunchKernelGGL(k_select<T>, dim3(1), dim3(sel_threads), 0, s, g, (const T*)st->E, b.scores,
+  // the greedy pick reads the workgroup summaries (one wave), as does the spaced
+  // top-k where each score thread took one pixel; larger grids rescan every score
+  // after each pick
+  const int sel_threads = topk == 1 ? 64 : nblk * kScoreThreads >= g.N ? kTopkThreads : kSelectThreads;
+  hipLaunchKernelGGL((g.n_eps == 2 ? k_select<T, 2> : k_select<T, GFO_MAX_EPS>), dim3(1), dim3(sel_threads), 0, s, g, (const T*)st->E, b.scores,
                      (const double*)b.partial, (const int*)b.pfirst, nblk, tau, topk, spacing, out);
   return note_hip(hipGetLastError());
 }
