@@ -158,21 +158,6 @@ __device__ __forceinline__ void gather_prefetch(const Geo& g, const int32_t* __r
 template <typename T, int B>
 __device__ __forceinline__ double2 sum_terms(const GatherPre<T, B>& pre, T yl, int s0, int cnt);
 
-// Lane k's value of x, uniform (k a constant).
-__device__ __forceinline__ float2 lane_value(float2 x, int k) {
-  return make_float2(__builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x.x), k)),
-                     __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x.y), k)));
-}
-__device__ __forceinline__ double lane_value(double x, int k) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, x);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, k);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), k);
-  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
-}
-__device__ __forceinline__ double2 lane_value(double2 x, int k) {
-  return make_double2(lane_value(x.x, k), lane_value(x.y, k));
-}
-
 template <typename T, int B>
 __device__ __forceinline__ double2 sum_terms(const GatherPre<T, B>& pre, T yl, int s0, int cnt) {
   const T zero = St<T>::from_d(make_double2(0.0, 0.0));

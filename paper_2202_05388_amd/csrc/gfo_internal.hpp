@@ -102,6 +102,21 @@ __device__ __forceinline__ float2 pick_of(bool c, float2 a, float2 b) {
 __device__ __forceinline__ double2 pick_of(bool c, double2 a, double2 b) {
   return make_double2(c ? a.x : b.x, c ? a.y : b.y);
 }
+// Lane k's value of x, uniform (k a constant).
+__device__ __forceinline__ float2 lane_value(float2 x, int k) {
+  return make_float2(__builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x.x), k)),
+                     __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x.y), k)));
+}
+__device__ __forceinline__ double lane_value(double x, int k) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, k);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), k);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ double2 lane_value(double2 x, int k) {
+  return make_double2(lane_value(x.x, k), lane_value(x.y, k));
+}
+
 // Marks x as used here, so that its load stays in the batch it was written in
 // instead of moving into a later branch that needs it.
 __device__ __forceinline__ void keep(double2 x) { asm volatile("" ::"v"(x.x), "v"(x.y)); }
@@ -194,6 +209,9 @@ constexpr int kScoreMaxBlocks = 1024;
 // 16-byte units per index of the split-product flush's operands: 12 per 16
 // pending terms, up to GFO_MAX_DELAY terms.
 constexpr int kSplitUnits = 12 * (GFO_MAX_DELAY / 16);
+// Rows of the refresh's Z region at least: two 32-column panel buffers and a
+// 16-column one live there before Z.
+constexpr size_t kGjWork = 80;
 constexpr int kSelectThreads = 1024;
 constexpr int kTopkThreads = 256;   // spaced top-k from the workgroup summaries
 
@@ -230,8 +248,8 @@ struct Layout {
   size_t rf_A;      // 2 kp^2 double2: two kp x kp buffers of the in-place Gauss-Jordan inverse
                     // of diag(1/alpha) - G0[V,V], then M
   size_t rf_piv;    // 16 kp + 64 bytes: the steps' pivot candidates, the pivots, the used rows
-  size_t rf_Z;      // R x kp double2: G0[:, V] M; before it, the blocked inverse's panel buffers
-  size_t rf_x;      // kp double2: M Einc[V]
+  size_t rf_Z;      // max(R, kGjWork) x kp double2: G0[:, V] M; before it, the inverse's panel buffers
+  size_t rf_x;      // kp double2: Einc[V]
   // split-product flush (complex64 storage only): the pending terms as BF16
   // parts, kSplitUnits units of 16 bytes per row (R rows of CU) and per column
   // (ld columns of V)

@@ -50,38 +50,35 @@ __device__ __forceinline__ double2 incident(const Geo& g, const double* __restri
 
 // ------------------------------------------------------------------ flipped list
 // Single workgroup of 1024 threads: ordered compaction of {p : eps_idx[p] != bg}.
-// V[N] receives the count.
+// Each thread counts and then writes a contiguous share of the pixels, with one
+// scan over the workgroup between (a scan per 1024 pixels took 23 us at 128 x
+// 128, three barriers each).  V[N] receives the count.
 __global__ __launch_bounds__(1024) void k_rf_list(Geo g, const uint8_t* __restrict__ eps_idx,
                                                   int32_t* __restrict__ V) {
   __shared__ int wsum[16];
-  __shared__ int base;
-  if (threadIdx.x == 0) base = 0;
-  __syncthreads();
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  for (int p0 = 0; p0 < g.N; p0 += 1024) {
-    const int p = p0 + threadIdx.x;
-    const int f = (p < g.N && eps_idx[p] != g.bg_idx) ? 1 : 0;
-    // inclusive scan within the wave
-    int x = f;
+  const int share = (g.N + 1023) / 1024;
+  const int64_t p0 = (int64_t)threadIdx.x * share, p1 = p0 + share < g.N ? p0 + share : g.N;
+  int f = 0;
+#pragma unroll 8
+  for (int64_t p = p0; p < p1; ++p) f += eps_idx[p] != g.bg_idx ? 1 : 0;
+  int x = f;                                  // inclusive scan within the wave
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      int y = __shfl_up(x, o, 64);
-      if (lane >= o) x += y;
-    }
-    if (lane == 63) wsum[w] = x;
-    __syncthreads();
-    int before = base;
-    for (int i = 0; i < w; ++i) before += wsum[i];
-    if (f) V[before + x - 1] = p;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      int t = 0;
-      for (int i = 0; i < 16; ++i) t += wsum[i];
-      base += t;
-    }
-    __syncthreads();
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
   }
-  if (threadIdx.x == 0) V[g.N] = base;
+  if (lane == 63) wsum[w] = x;
+  __syncthreads();
+  int at = x - f, total = 0;
+  for (int i = 0; i < 16; ++i) {
+    if (i < w) at += wsum[i];
+    total += wsum[i];
+  }
+  if (f > 0)
+    for (int64_t p = p0; p < p1; ++p)
+      if (eps_idx[p] != g.bg_idx) V[at++] = (int32_t)p;
+  if (threadIdx.x == 0) V[g.N] = total;
 }
 
 __global__ void k_rf_overflow(int32_t* status) {
@@ -115,12 +112,19 @@ struct GjPart {
 };
 constexpr int kGjRows = 8;   // rows per workgroup of a step
 
-// Core A in W (row-major, ld kp) and the pivot flags cleared.
+// Core A in W (row-major, ld kp), the pivot flags cleared, x = Einc[V].
 __global__ void k_rf_build_core(Geo g, const uint8_t* __restrict__ eps_idx,
+                                const double* __restrict__ mon_xy,
                                 const int32_t* __restrict__ V, const double2* __restrict__ U, int k,
-                                int kp, double2* __restrict__ W, int32_t* __restrict__ used) {
+                                int kp, double2* __restrict__ W, int32_t* __restrict__ used,
+                                double2* __restrict__ x) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < kp) used[t] = 0;
+  if (t < kp) {
+    used[t] = 0;
+    double2 v = make_double2(0.0, 0.0);
+    if (t < k) v = incident(g, mon_xy, V[t]);
+    x[t] = v;
+  }
   if (t >= (int64_t)kp * kp) return;
   const int a = (int)(t / kp), b = (int)(t - (int64_t)a * kp);
   double2 v = make_double2(0.0, 0.0);
@@ -168,82 +172,6 @@ __device__ __forceinline__ void gj_argmax(double& m, int& row) {
   __syncthreads();
 }
 
-// Step c: S -> D.  Grid: kGjRows rows (blockIdx.x) x 256 columns (blockIdx.y)
-// per workgroup, one column per thread.  The pivot of column c comes from the
-// previous step's candidates, one per row group (part_in, n_in), or for c = 0
-// from column 0 itself.  The thread that holds column c + 1 leaves its row
-// group's best unused row for the next step; the workgroup (group of p_c, 0)
-// records the pivot (piv[c], used).
-__global__ __launch_bounds__(256) void k_gj_step(const double2* __restrict__ S, double2* __restrict__ D,
-                                                 int kp, int c, const GjPart* __restrict__ part_in,
-                                                 int n_in, GjPart* __restrict__ part_out,
-                                                 int32_t* __restrict__ piv, int32_t* __restrict__ used,
-                                                 int32_t* __restrict__ status) {
-  double best = -1.0;
-  int bi = 0x7fffffff;
-  if (part_in != nullptr) {
-    for (int q = threadIdx.x; q < n_in; q += blockDim.x) {
-      const GjPart pq = part_in[q];
-      if (pq.m > best || (pq.m == best && pq.row < bi)) {
-        best = pq.m;
-        bi = pq.row;
-      }
-    }
-  } else {
-    for (int r = threadIdx.x; r < kp; r += blockDim.x) {
-      if (used[r] != 0) continue;
-      const double2 v = S[(int64_t)r * kp + c];
-      double m = v.x * v.x + v.y * v.y;
-      if (!(m >= 0.0)) m = 0.0;   // a NaN row stays a candidate: some row is always chosen
-      if (m > best) {
-        best = m;
-        bi = r;
-      }
-    }
-  }
-  gj_argmax(best, bi);
-  const int p = bi;
-  const int r0 = blockIdx.x * kGjRows;
-  if (threadIdx.x == 0 && blockIdx.y == 0) {
-    if (blockIdx.x == 0 && !(best > 0.0)) atomicOr(status, GFO_STATUS_SINGULAR);
-    if (p >= r0 && p < r0 + kGjRows) {
-      piv[c] = p;
-      used[p] = c + 1;
-    }
-  }
-  const int j = blockIdx.y * blockDim.x + threadIdx.x;
-  if (j >= kp) return;
-  const double2 d = S[(int64_t)p * kp + c];
-  const double n = d.x * d.x + d.y * d.y;
-  const double2 inv = n > 0.0 ? make_double2(d.x / n, -d.y / n) : make_double2(1.0, 0.0);
-  const double2 pc = j == c ? inv : cmul(S[(int64_t)p * kp + j], inv);
-  double nb = -1.0;
-  int ni = 0x7fffffff;
-#pragma unroll
-  for (int rr = 0; rr < kGjRows; ++rr) {
-    const int r = r0 + rr;
-    if (r < kp) {
-      double2 out = pc;
-      if (r != p) {
-        const double2 fr = S[(int64_t)r * kp + c];
-        const double2 v = j == c ? make_double2(0.0, 0.0) : S[(int64_t)r * kp + j];
-        out = make_double2(v.x - (fr.x * pc.x - fr.y * pc.y), v.y - (fr.x * pc.y + fr.y * pc.x));
-      }
-      D[(int64_t)r * kp + j] = out;
-      // a candidate pivot of column c + 1: not p, not used before this step
-      if (j == c + 1 && r != p && used[r] == 0) {
-        double m = out.x * out.x + out.y * out.y;
-        if (!(m >= 0.0)) m = 0.0;
-        if (m > nb) {   // rows in increasing order: the lowest row wins ties
-          nb = m;
-          ni = r;
-        }
-      }
-    }
-  }
-  if (j == c + 1) part_out[blockIdx.x] = GjPart{nb, ni, 0};
-}
-
 // M = A^-1 from the in-place result X: M[c][p_d] = X[p_c][d].
 __global__ void k_gj_unpermute(const double2* __restrict__ X, double2* __restrict__ M,
                                const int32_t* __restrict__ piv, int kp) {
@@ -253,15 +181,19 @@ __global__ void k_gj_unpermute(const double2* __restrict__ X, double2* __restric
   M[(int64_t)c * kp + piv[d]] = X[(int64_t)piv[c] * kp + d];
 }
 
-// Blocked form (k > 64): panels of kGjPanel columns.  A panel's columns are
-// copied to a k x kGjPanel buffer and its steps run there (the same pivot rule,
-// the same updates restricted to the panel's columns, two buffers); the
-// panel's transformation T = prod of its steps then reaches every other
-// column j at once: X'[:, j] = X[:, j] + (T[:, P] - I[:, P]) X[P, j], P the
-// panel's pivot rows, whose columns T[:, P] the panel buffer now holds (column
-// c for pivot p_c).  That is a rank-kGjPanel FP64 product on the matrix cores,
-// its pivot rows read from a copy taken before; in the pivot rows the -1
-// cancels the old value.  used[r] = c + 1 records the column r pivoted.
+// The steps run in panels.  A panel's steps act on its own columns only (the same
+// pivot rule, the same updates); the panel's transformation T = prod of its steps
+// then reaches every other column j at once: X'[:, j] = X[:, j] + (T[:, P] -
+// I[:, P]) X[P, j], P the panel's pivot rows, whose columns T[:, P] the panel now
+// holds (column c for pivot p_c).  That is a product of the panel's rank on the
+// FP64 matrix cores; in the pivot rows the -1 cancels the old value.  It reads one
+// buffer and writes the other, so the pivot rows are read where they are.
+// used[r] = c + 1 records the column that row r pivoted.
+//   up to 512 rows: panels of 16 columns, each factored by one workgroup
+//     (k_gj_panel: its rows in registers);
+//   up to 2048 rows: panels of 32 columns in a k x 32 buffer, factored in
+//     subpanels of 8;
+//   beyond: panels of 32 columns, one launch per column (k_gj_panel_step).
 constexpr int kGjPanel = 32;
 
 __global__ void k_gj_panel_copy(const double2* __restrict__ X, double2* __restrict__ Pn, int kp, int c0,
@@ -339,32 +271,207 @@ __global__ __launch_bounds__(256) void k_gj_panel_step(const double2* __restrict
   if (threadIdx.x == 0) part_out[blockIdx.x] = GjPart{nb, ni, 0};
 }
 
-// The pivot rows of the panel before it: Prow[i][j] = X[p_(c0 + i)][j].
-__global__ void k_gj_pivot_rows(const double2* __restrict__ X, double2* __restrict__ Prow,
-                                const int32_t* __restrict__ piv, int kp, int c0, int qn) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (int64_t)qn * kp) return;
-  const int i = (int)(t / kp), j = (int)(t - (int64_t)i * kp);
-  Prow[t] = X[(int64_t)piv[c0 + i] * kp + j];
+// All PW steps of a panel in one workgroup of up to 512 threads (as few waves as the
+// rows need): columns [col0, col0 + qn) of S (kp x *, ld lds) to T (kp x PW).
+// Thread t holds the rows t, t + blockDim, ... (RT of them) in registers.  A step:
+// every wave finds its best unused row and leaves it in LDS with its modulus;
+// after one barrier every wave picks the best of them, takes that row through one
+// LDS read and cross-lane reads, and updates its own rows.  The factor of a row is
+// scaled by 1 / pivot once instead of the pivot row.  Bound by the instructions of
+// a step: two waves per SIMD of four rows rather than four of two, as the pivot
+// search and the division are per wave (1024 threads: 3.6 to 4.6 us a step).
+struct __attribute__((aligned(16))) GjBest {
+  double m;
+  int row, pad;
+};
+template <int RT, int PW>
+__global__ __launch_bounds__(512) void k_gj_panel(const double2* __restrict__ S, int lds, int col0,
+                                                  double2* __restrict__ T, int kp, int c0, int qn,
+                                                  int32_t* __restrict__ piv, int32_t* __restrict__ used,
+                                                  int32_t* __restrict__ status) {
+  __shared__ GjBest cand[2][8];
+  __shared__ double2 crow[2][8][PW];
+  __shared__ int spiv[PW];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int nt = (int)blockDim.x;
+  if (threadIdx.x < 16) cand[threadIdx.x >> 3][threadIdx.x & 7] = GjBest{-2.0, 0x7fffffff, 0};   // waves not launched
+  bool singular = false;
+  double2 a[RT][PW];
+  bool open[RT];                                    // a row of the matrix not yet used
+#pragma unroll
+  for (int q = 0; q < RT; ++q) {
+    const int r = (int)threadIdx.x + nt * q, rc = r < kp ? r : 0;
+    open[q] = r < kp && used[rc] == 0;
+#pragma unroll
+    for (int i = 0; i < PW; ++i) a[q][i] = S[(int64_t)rc * lds + col0 + (i < qn ? i : 0)];
+  }
+  __syncthreads();
+  // One step's code for all steps: column 0 is the step's, and the columns move one
+  // place down as they are written, its result to the end.  No global store inside
+  // (a barrier would wait for it: 1.6 and 4 us a step).
+#pragma unroll 1
+  for (int c = 0; c < qn; ++c) {
+    const int buf = c & 1;
+    double m = -1.0;
+    int mq = 0;
+#pragma unroll
+    for (int q = 0; q < RT; ++q) {
+      // (fmax: a NaN row stays a candidate, some row is always chosen; an overflow counts as the largest number)
+      const double v = fmin(fmax(a[q][0].x * a[q][0].x + a[q][0].y * a[q][0].y, 0.0), 1.7976931348623157e308);
+      if (open[q] && v > m) {                       // rows rise with q: the lowest wins ties
+        m = v;
+        mq = q;
+      }
+    }
+    const double wbest = wave_max(m);
+    const int row = (int)threadIdx.x + nt * mq;
+    uint64_t votes = __ballot(m == wbest);
+    if (votes & (votes - 1)) {                      // a tie: the lowest row (wave_min with every lane active)
+      const int lowest = wave_min(m == wbest ? row : 0x7fffffff);
+      votes = __ballot(m == wbest && row == lowest);
+    }
+    const int src = __builtin_ctzll(votes), sq = __builtin_amdgcn_readlane(mq, src);
+    if (lane == src) {
+      cand[buf][w] = GjBest{wbest, row, 0};
+#pragma unroll
+      for (int q = 0; q < RT; ++q)
+        if (q == sq)                                // uniform
+#pragma unroll
+          for (int i = 0; i < PW; ++i) crow[buf][w][i] = a[q][i];
+    }
+    __syncthreads();
+    double best = -2.0;
+    int p = 0x7fffffff, at = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const GjBest x = cand[buf][i];
+      const bool better = (x.m > best) | ((x.m == best) & (x.row < p));   // no branch
+      best = better ? x.m : best;
+      p = better ? x.row : p;
+      at = better ? i : at;
+    }
+    p = __builtin_amdgcn_readfirstlane(p);
+    at = __builtin_amdgcn_readfirstlane(at);
+    const double2 pl = crow[buf][at][lane < PW ? lane : 0];
+    const double2 d = lane_value(pl, 0);
+    const double n = d.x * d.x + d.y * d.y;
+    const double2 inv = pick_of(n > 0.0, make_double2(d.x / n, -d.y / n), make_double2(1.0, 0.0));
+    singular = singular || !(best > 0.0);
+    if (threadIdx.x == 0) spiv[c] = p;
+    double2 f[RT];
+#pragma unroll
+    for (int q = 0; q < RT; ++q) f[q] = cmul(a[q][0], inv);
+    // the pivot row becomes its entries times 1 / pivot: 0 - (-1 / pivot) times them
+    const int pq = (p >= nt) + (p >= 2 * nt) + (p >= 3 * nt), pt = p - pq * nt;   // uniform, RT <= 4
+    if (pt >> 6 == w && lane == (pt & 63)) {
+#pragma unroll
+      for (int q = 0; q < RT; ++q)
+        if (q == pq) {
+          open[q] = false;
+          f[q] = make_double2(-inv.x, -inv.y);
+#pragma unroll
+          for (int i = 1; i < PW; ++i) a[q][i] = make_double2(0.0, 0.0);
+        }
+    }
+#pragma unroll
+    for (int i = 1; i < PW; ++i) {
+      const double2 pr = lane_value(pl, i);
+#pragma unroll
+      for (int q = 0; q < RT; ++q) {
+        const double2 x = a[q][i];
+        a[q][i - 1] = make_double2(fma(-f[q].x, pr.x, fma(f[q].y, pr.y, x.x)),
+                                   fma(-f[q].x, pr.y, fma(-f[q].y, pr.x, x.y)));
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < RT; ++q) a[q][PW - 1] = make_double2(-f[q].x, -f[q].y);
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < qn) {
+    piv[c0 + threadIdx.x] = spiv[threadIdx.x];
+    used[spiv[threadIdx.x]] = c0 + (int)threadIdx.x + 1;
+  }
+  if (threadIdx.x == 0 && singular) atomicOr(status, GFO_STATUS_SINGULAR);
+#pragma unroll
+  for (int q = 0; q < RT; ++q) {
+    const int r = (int)threadIdx.x + nt * q;
+    if (r < kp)
+#pragma unroll
+      for (int i = 0; i < PW; ++i) {
+        const int col = i + qn < PW ? i + qn : i + qn - PW;   // the column now in place i
+        if (col < qn) T[(int64_t)r * PW + col] = a[q][i];
+      }
+  }
 }
 
-// Epilogue of the panel's product v = (T[:, P] X[P, :])[m][n]: the panel's
-// columns take T[:, P]; a pivot row of the panel takes v; every other entry adds v.
-struct EpiGJ {
-  double2* X;
-  const double2* Pn;
-  const int32_t* used;
-  int kp, c0, qn;
-  __device__ void operator()(int m, int n, double2 v) const {
-    double2* x = X + (int64_t)m * kp + n;
-    if (n >= c0 && n < c0 + qn) {
-      *x = Pn[(int64_t)m * kGjPanel + (n - c0)];
-    } else {
-      const int u = used[m];
-      *x = (u > c0 && u <= c0 + qn) ? v : cadd(*x, v);
+// The panel's product on the other columns (the comment above): D[m][n] = S[m][n]
+// + sum_i T[m][i] S[piv[i]][n], without S[m][n] in the panel's pivot rows; columns
+// [col0, col0 + qn) take T.  S and D: kp x n_cols, ld lds; ranks up to 4 KQ.  A
+// wave takes 16 TM x 16 TN outputs (tile operands as in k_zgemm_f64) and requests
+// every operand before its first product; bound by those loads at small kp, by
+// reading S and writing D beyond.
+template <int TM, int TN, int KQ>
+__global__ __launch_bounds__(256) void k_gj_update(int kp, int n_cols, int lds, const double2* __restrict__ S,
+                                                   double2* __restrict__ D, const double2* __restrict__ T, int ldt,
+                                                   const int32_t* __restrict__ piv, const int32_t* __restrict__ used,
+                                                   int c0, int qn, int col0) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int li = lane & 15, lk = lane >> 4;
+  const int m0 = (int)blockIdx.y * 32 * TM + (w >> 1) * 16 * TM, n0 = (int)blockIdx.x * 32 * TN + (w & 1) * 16 * TN;
+  double2 a[KQ][TM], b[KQ][TN];
+#pragma unroll
+  for (int s = 0; s < KQ; ++s) {
+    const int k = 4 * s + lk, kc = k < qn ? k : 0;
+    const int64_t pr = piv[kc];
+#pragma unroll
+    for (int t = 0; t < TM; ++t) {
+      const int r = m0 + 16 * t + li;
+      a[s][t] = T[(int64_t)(r < kp ? r : 0) * ldt + kc];
+      a[s][t] = pick_of(k < qn, a[s][t], make_double2(0.0, 0.0));
+    }
+#pragma unroll
+    for (int u = 0; u < TN; ++u) {
+      const int n = n0 + 16 * u + li;
+      b[s][u] = S[pr * lds + (n < n_cols ? n : 0)];
+      b[s][u] = pick_of(k < qn, b[s][u], make_double2(0.0, 0.0));
     }
   }
-};
+  f64x4 re[TM][TN], im[TM][TN];
+#pragma unroll
+  for (int t = 0; t < TM; ++t)
+#pragma unroll
+    for (int u = 0; u < TN; ++u) re[t][u] = im[t][u] = (f64x4){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int s = 0; s < KQ; ++s)
+#pragma unroll
+    for (int t = 0; t < TM; ++t)
+#pragma unroll
+      for (int u = 0; u < TN; ++u) {
+        re[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s][t].x, b[s][u].x, re[t][u], 0, 0, 0);
+        re[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[s][t].y, b[s][u].y, re[t][u], 0, 0, 0);
+        im[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s][t].x, b[s][u].y, im[t][u], 0, 0, 0);
+        im[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s][t].y, b[s][u].x, im[t][u], 0, 0, 0);
+      }
+#pragma unroll
+  for (int t = 0; t < TM; ++t)
+#pragma unroll
+    for (int u = 0; u < TN; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = m0 + 16 * t + lk + 4 * e, n = n0 + 16 * u + li;
+        if (r >= kp || n >= n_cols) continue;
+        const double2 v = make_double2(re[t][u][e], im[t][u][e]);
+        const int us = used[r];
+        double2 out;
+        if (n >= col0 && n < col0 + qn)
+          out = T[(int64_t)r * ldt + (n - col0)];
+        else if (us > c0 && us <= c0 + qn)
+          out = v;
+        else
+          out = cadd(S[(int64_t)r * lds + n], v);
+        D[(int64_t)r * lds + n] = out;
+      }
+}
 
 // ------------------------------------------------------------------ FP64 MFMA complex GEMM
 // C(m, n) = sum_k A(m, k) B(k, n), complex FP64, A row-major (lda).
@@ -375,10 +482,16 @@ struct EpiGJ {
 // Operand layout of the 16x16x4 FP64 instruction (one value per lane):
 //   A(i, k): i = lane % 16, k = lane / 16;  B(k, j): j = lane % 16, k = lane / 16;
 //   D(i, j): j = lane % 16, i = lane / 16 + 4 * element  (checked on gfx950).
+// An epilogue prepares a thread's rows and columns once (row, col) and then takes
+// each entry: a G0 entry needs the grid coordinates of both pixels, and four integer
+// divisions per entry were a sixth of the refresh product's time at 180 flipped
+// pixels.
 struct EpiStoreZ {
   double2* Z;
   int64_t ldz;
-  __device__ void operator()(int m, int n, double2 v) const { Z[(int64_t)m * ldz + n] = v; }
+  __device__ int64_t row(int m) const { return m * ldz; }
+  __device__ int col(int n) const { return n; }
+  __device__ void operator()(int64_t r, int n, double2 v) const { Z[r + n] = v; }
 };
 
 template <typename T>
@@ -388,22 +501,52 @@ struct EpiG0 {
   const double* mon_xy;
   T* G;
   double2* diag64;
-  __device__ void operator()(int m, int n, double2 v) const {
-    // band-packed storage holds no entry left of a design row's band
-    if (g.packed && m < g.N && n < (m & ~63)) return;
-    const double2 g0 = g0_entry(g, table, mon_xy, m, n);
+  struct Pixel {
+    int p, iy, ix;
+  };
+  struct RowAt {
+    Pixel at;
+    int64_t base;       // offset of column 0 (packed: of the column before the band's first by 64 b)
+  };
+  __device__ Pixel pixel(int p) const {
+    const int iy = p / g.nx;
+    return Pixel{p, iy, p - iy * g.nx};
+  }
+  __device__ RowAt row(int m) const {
+    if (m >= g.N) return RowAt{Pixel{m, 0, 0}, g_mon(g, m - g.N, 0)};
+    return RowAt{pixel(m), g_off(g, m, m & ~63) - (m & ~63)};
+  }
+  __device__ Pixel col(int n) const { return pixel(n); }
+  __device__ void operator()(const RowAt& r, const Pixel& c, double2 v) const {
+    double2 g0;
+    if (r.at.p < g.N) {
+      // band-packed storage holds no entry left of a design row's band
+      if (g.packed && c.p < (r.at.p & ~63)) return;
+      g0 = table[abs(r.at.iy - c.iy) * g.nx + abs(r.at.ix - c.ix)];
+    } else {
+      g0 = g0_entry(g, table, mon_xy, r.at.p, c.p);
+    }
     const double2 val = make_double2(g0.x + v.x, g0.y + v.y);
-    G[g_off(g, m, n)] = St<T>::from_d(val);
-    if (m == n) diag64[m] = val;
+    G[r.base + c.p] = St<T>::from_d(val);
+    if (r.at.p == c.p) diag64[c.p] = val;
   }
 };
 
 struct EpiAddG {
   Geo g;
   double2* G;
-  __device__ void operator()(int m, int n, double2 v) const {
-    if (g.packed && m < g.N && n < (m & ~63)) return;
-    double2* p = G + g_off(g, m, n);
+  struct RowAt {
+    int m;
+    int64_t base;
+  };
+  __device__ RowAt row(int m) const {
+    if (m >= g.N) return RowAt{m, g_mon(g, m - g.N, 0)};
+    return RowAt{m, g_off(g, m, m & ~63) - (m & ~63)};
+  }
+  __device__ int col(int n) const { return n; }
+  __device__ void operator()(const RowAt& r, int n, double2 v) const {
+    if (g.packed && r.m < g.N && n < (r.m & ~63)) return;
+    double2* p = G + r.base + n;
     *p = cadd(*p, v);
   }
 };
@@ -468,13 +611,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int e = 0; e < 4; ++e) {
+      const int row = m0 + 16 * t + lk + 4 * e;
+      if (row >= M) continue;
+      const auto ra = epi.row(row);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int row = m0 + 16 * t + lk + 4 * e;
+      for (int u = 0; u < 2; ++u) {
         const int col = n0 + 16 * u + li;
-        if (row < M && col < N) epi(row, col, make_double2(re[t][u][e], im[t][u][e]));
+        if (col < N) epi(ra, epi.col(col), make_double2(re[t][u][e], im[t][u][e]));
       }
+    }
 }
 
 // The same product with a 128 x 128 output tile per workgroup of 512 threads
@@ -501,7 +647,9 @@ __global__ __launch_bounds__(512) void k_zgemm_f64_t128(int M, int N, int K, con
                                                         int64_t ldb, const int32_t* __restrict__ kdev,
                                                         Epi epi, int skip_below) {
   int by = (int)blockIdx.y, bx = (int)blockIdx.x;
-  if (skip_below > 0) ut_group(blockIdx.x, (N + kZgT - 1) / kZgT, skip_below / kZgT, kZgT, kZgT, by, bx);
+  // (the last tiles first: the monitor rows' are the longest, their G0 entries being evaluated)
+  if (skip_below > 0)
+    ut_group(gridDim.x - 1 - blockIdx.x, (N + kZgT - 1) / kZgT, skip_below / kZgT, kZgT, kZgT, by, bx);
   __shared__ double2 As[2][kZgKC][kZgPitch], Bs[2][kZgKC][kZgPitch];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int tm0 = by * kZgT, tn0 = bx * kZgT;
@@ -586,38 +734,35 @@ __global__ __launch_bounds__(512) void k_zgemm_f64_t128(int M, int N, int K, con
     __syncthreads();
   }
   if (idle) return;
+  const int cn0 = tn0 + wn + li, cn1 = cn0 + 16;
+  const auto ca0 = epi.col(cn0 < N ? cn0 : 0), ca1 = epi.col(cn1 < N ? cn1 : 0);
 #pragma unroll
   for (int t = 0; t < 4; ++t)
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int row = tm0 + wm + 16 * t + lk + 4 * e;
-        const int col = tn0 + wn + 16 * u + li;
-        if (row < M && col < N) epi(row, col, make_double2(re[t][u][e], im[t][u][e]));
-      }
+    for (int e = 0; e < 4; ++e) {
+      const int row = tm0 + wm + 16 * t + lk + 4 * e;
+      if (row >= M) continue;
+      const auto ra = epi.row(row);
+      if (cn0 < N) epi(ra, ca0, make_double2(re[t][0][e], im[t][0][e]));
+      if (cn1 < N) epi(ra, ca1, make_double2(re[t][1][e], im[t][1][e]));
+    }
 }
 
-// x = M Einc[V] (k-vector), then E[r] = Einc[r] + sum_i U[r, i] x_i.
-__global__ void k_rf_xE(Geo g, const double* __restrict__ mon_xy, const int32_t* __restrict__ V,
-                        const double2* __restrict__ M, int k, int kp, double2* __restrict__ x) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= kp) return;
-  double2 s = make_double2(0.0, 0.0);
-  if (i < k)
-    for (int j = 0; j < k; ++j)
-      s = cadd(s, cmul(M[(int64_t)i * kp + j], incident(g, mon_xy, V[j])));
-  x[i] = s;
-}
-
+// E = Einc + Z x with x = Einc[V] (Z = U M), one wave per row.  (As x = M Einc[V]
+// and then U x, one thread per row each, the two took 0.8 ms at 1500 flipped
+// pixels.)
 template <typename T>
-__global__ void k_rf_field(Geo g, const double* __restrict__ mon_xy, const double2* __restrict__ U,
-                           const double2* __restrict__ x, int k, int kp, T* __restrict__ E) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(256) void k_rf_field(Geo g, const double* __restrict__ mon_xy,
+                                                  const double2* __restrict__ Z, const double2* __restrict__ x,
+                                                  int k, int kp, T* __restrict__ E) {
+  const int r = blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (r >= g.R) return;
-  double2 s = incident(g, mon_xy, r);
-  for (int i = 0; i < k; ++i) s = cadd(s, cmul(U[(int64_t)r * kp + i], x[i]));
-  E[r] = St<T>::from_d(s);
+  double2 s = make_double2(0.0, 0.0);
+#pragma unroll 4
+  for (int i = lane; i < k; i += 64) s = cadd(s, cmul(Z[(int64_t)r * kp + i], x[i]));
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s = cadd(s, make_double2(__shfl_xor(s.x, o, 64), __shfl_xor(s.y, o, 64)));
+  if (lane == 0) E[r] = St<T>::from_d(cadd(incident(g, mon_xy, r), s));
 }
 
 // Flipped list V (in the workspace) and its length k, read back to the host
@@ -636,6 +781,19 @@ int launch_refresh_count(const Geo& g, gfo_state* st, const Layout& L, hipStream
 hipError_t launch_refresh_overflow(gfo_state* st, hipStream_t s) {
   hipLaunchKernelGGL(k_rf_overflow, dim3(1), dim3(64), 0, s, st->status);
   return note_hip(hipGetLastError());
+}
+
+// The panel's product (rank up to 4 KQ): 16 x 16 outputs per wave while the matrix
+// is small enough that larger tiles would leave compute units idle (180 columns: 36
+// workgroups against 9), else 32 x 32.
+template <int KQ>
+static void launch_gj_update(int kp, int n_cols, int lds, const double2* S, double2* D, const double2* T, int ldt,
+                             const int32_t* piv, const int32_t* used, int c0, int qn, int col0, hipStream_t s) {
+  const bool small = (int64_t)kp * n_cols <= 512 * 512;
+  const int tile = small ? 32 : 64;
+  hipLaunchKernelGGL((small ? k_gj_update<1, 1, KQ> : k_gj_update<2, 2, KQ>),
+                     dim3((unsigned)((n_cols + tile - 1) / tile), (unsigned)((kp + tile - 1) / tile)), dim3(256), 0, s,
+                     kp, n_cols, lds, S, D, T, ldt, piv + c0, used, c0, qn, col0);
 }
 
 template <typename T>
@@ -662,56 +820,63 @@ static int refresh_typed(const Geo& g, gfo_state* st, const Layout& L, int32_t k
     int32_t* used = piv + kp;
     const int64_t na = (int64_t)kp * kp;
     hipLaunchKernelGGL(k_rf_build_core, dim3((unsigned)((na + 255) / 256)), dim3(256), 0, s, g,
-                       (const uint8_t*)st->eps_idx, (const int32_t*)V, (const double2*)U, k, kp, W[0],
-                       used);
-    const double2* X = nullptr;   // the in-place result
-    if (kp > 2 * kGjPanel && g.R >= 3 * kGjPanel) {
-      // blocked: the panel buffers and the pivot rows' copy in Z's workspace
-      // (R x kp entries, free until Z = U M), X in place in W[0]
-      double2* Pn[2] = {Z, Z + (int64_t)kp * kGjPanel};
-      double2* Prow = Z + 2 * (int64_t)kp * kGjPanel;
-      const unsigned np = (unsigned)(((int64_t)kp * kGjPanel + 255) / 256);
-      for (int c0 = 0; c0 < kp; c0 += kGjPanel) {
-        const int qn = min(kGjPanel, kp - c0);
-        hipLaunchKernelGGL(k_gj_panel_copy, dim3(np), dim3(256), 0, s, (const double2*)W[0], Pn[0], kp, c0,
-                           qn);
-        for (int l = 0; l < qn; ++l)
-          hipLaunchKernelGGL(k_gj_panel_step, dim3((unsigned)nb), dim3(256), 0, s, (const double2*)Pn[l & 1],
-                             Pn[(l + 1) & 1], kp, c0, qn, c0 + l,
-                             l == 0 ? (const GjPart*)nullptr : (const GjPart*)part[(l + 1) & 1], nb,
-                             part[l & 1], piv, used, st->status);
-        hipLaunchKernelGGL(k_gj_pivot_rows, dim3((unsigned)(((int64_t)qn * kp + 255) / 256)), dim3(256), 0, s,
-                           (const double2*)W[0], Prow, (const int32_t*)piv, kp, c0, qn);
-        EpiGJ eg{W[0], Pn[qn & 1], used, kp, c0, qn};
-        hipLaunchKernelGGL((k_zgemm_f64<false, false, EpiGJ>), dim3((kp + 63) / 64, (kp + 63) / 64), dim3(256),
-                           0, s, kp, kp, qn, (const double2*)Pn[qn & 1], (int64_t)kGjPanel,
-                           (const double2*)Prow, (int64_t)kp, (const int32_t*)nullptr, eg, 0);
+                       (const uint8_t*)st->eps_idx, mon, (const int32_t*)V, (const double2*)U, k, kp, W[0],
+                       used, x);
+    // panel buffers in Z's workspace (free until Z = U M; the layout gives it kGjWork
+    // rows at least)
+    double2* Pn[2] = {Z, Z + (int64_t)kp * kGjPanel};
+    double2* Tn = Z + 2 * (int64_t)kp * kGjPanel;
+    int cur = 0;                  // W[cur] holds X
+    if (kp <= 512) {
+      const unsigned nt = (unsigned)((kp + 63) / 64 * 64);
+      for (int c0 = 0; c0 < kp; c0 += 16, cur ^= 1) {
+        const int qn = min(16, kp - c0);
+        hipLaunchKernelGGL((k_gj_panel<1, 16>), dim3(1), dim3(nt), 0, s, (const double2*)W[cur], kp, c0, Tn, kp, c0, qn,
+                           piv, used, st->status);
+        launch_gj_update<4>(kp, kp, kp, W[cur], W[cur ^ 1], Tn, 16, piv, used, c0, qn, c0, s);
       }
-      X = W[0];
-      M = W[1];
     } else {
-      const dim3 gj_grid((unsigned)nb, (unsigned)((kp + 255) / 256));
-      for (int c = 0; c < kp; ++c)
-        hipLaunchKernelGGL(k_gj_step, gj_grid, dim3(256), 0, s, (const double2*)W[c & 1],
-                           W[(c + 1) & 1], kp, c, c == 0 ? (const GjPart*)nullptr : (const GjPart*)part[(c + 1) & 1],
-                           nb, part[c & 1], piv, used, st->status);
-      // after kp steps the in-place result is in W[kp & 1]; M goes to the other
-      X = W[kp & 1];
-      M = W[(kp + 1) & 1];
+      const unsigned np = (unsigned)(((int64_t)kp * kGjPanel + 255) / 256);
+      const unsigned nt4 = (unsigned)((kp + 255) / 256 * 64);   // four rows per thread, kp <= 2048
+      for (int c0 = 0; c0 < kp; c0 += kGjPanel, cur ^= 1) {
+        const int qn = min(kGjPanel, kp - c0);
+        hipLaunchKernelGGL(k_gj_panel_copy, dim3(np), dim3(256), 0, s, (const double2*)W[cur], Pn[0], kp, c0, qn);
+        int b = 0;                // Pn[b] holds the panel
+        if (kp <= 2048) {
+          for (int s0 = 0; s0 < qn; s0 += 8, b ^= 1) {
+            const int sn = min(8, qn - s0);
+            hipLaunchKernelGGL((k_gj_panel<4, 8>), dim3(1), dim3(nt4), 0, s, (const double2*)Pn[b], kGjPanel, s0, Tn,
+                               kp, c0 + s0, sn, piv, used, st->status);
+            launch_gj_update<2>(kp, qn, kGjPanel, Pn[b], Pn[b ^ 1], Tn, 8, piv, used, c0 + s0, sn, s0, s);
+          }
+        } else {
+          for (int l = 0; l < qn; ++l, b ^= 1)
+            hipLaunchKernelGGL(k_gj_panel_step, dim3((unsigned)nb), dim3(256), 0, s, (const double2*)Pn[b], Pn[b ^ 1],
+                               kp, c0, qn, c0 + l, l == 0 ? (const GjPart*)nullptr : (const GjPart*)part[(l + 1) & 1],
+                               nb, part[l & 1], piv, used, st->status);
+        }
+        launch_gj_update<8>(kp, kp, kp, W[cur], W[cur ^ 1], Pn[b], kGjPanel, piv, used, c0, qn, c0, s);
+      }
     }
+    const double2* X = W[cur];    // the in-place result; M goes to the other buffer
+    M = W[cur ^ 1];
     hipLaunchKernelGGL(k_gj_unpermute, dim3((unsigned)((na + 255) / 256)), dim3(256), 0, s, X, M,
                        (const int32_t*)piv, kp);
     // Z = U M
     EpiStoreZ ez{Z, kp};
-    hipLaunchKernelGGL((k_zgemm_f64_t128<false, false, EpiStoreZ>),
-                       dim3((kp + kZgT - 1) / kZgT, (g.R + kZgT - 1) / kZgT), dim3(512), 0, s, g.R, kp, kp,
-                       (const double2*)U, (int64_t)kp, (const double2*)M, (int64_t)kp,
-                       (const int32_t*)nullptr, ez, 0);
-    hipLaunchKernelGGL(k_rf_xE, dim3((kp + 255) / 256), dim3(256), 0, s, g, mon, (const int32_t*)V,
-                       (const double2*)M, k, kp, x);
+    // the 128 x 128 tiles hold one workgroup per compute unit: below four rounds of
+    // them the 64 x 64 kernel fills the chip better
+    const int zx = (kp + kZgT - 1) / kZgT, zy = (g.R + kZgT - 1) / kZgT;
+    if ((int64_t)zx * zy >= 1024)
+      hipLaunchKernelGGL((k_zgemm_f64_t128<false, false, EpiStoreZ>), dim3(zx, zy), dim3(512), 0, s, g.R, kp, kp,
+                         (const double2*)U, (int64_t)kp, (const double2*)M, (int64_t)kp, (const int32_t*)nullptr, ez, 0);
+    else
+      hipLaunchKernelGGL((k_zgemm_f64<false, false, EpiStoreZ>), dim3((kp + 63) / 64, (g.R + 63) / 64), dim3(256), 0, s,
+                         g.R, kp, kp, (const double2*)U, (int64_t)kp, (const double2*)M, (int64_t)kp,
+                         (const int32_t*)nullptr, ez, 0);
   }
-  hipLaunchKernelGGL(k_rf_field<T>, dim3((g.R + 255) / 256), dim3(256), 0, s, g, mon,
-                     (const double2*)U, (const double2*)x, k, kp, (T*)st->E);
+  hipLaunchKernelGGL(k_rf_field<T>, dim3((unsigned)((g.R + 3) / 4)), dim3(256), 0, s, g, mon,
+                     (const double2*)Z, (const double2*)x, k, kp, (T*)st->E);
   // G = G0 + Z U_D^T over the N design columns (padding columns stay zero):
   // the monitor rows whole and the design block on and above its diagonal (the
   // block is symmetric); when the caller keeps the whole block, its lower
