@@ -13,6 +13,8 @@
 // mirror gives the lower triangle when the state keeps it.
 #include "gfo_internal.hpp"
 
+#include <type_traits>
+
 namespace gfo {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
@@ -528,7 +530,7 @@ struct EpiG0 {
     }
     const double2 val = make_double2(g0.x + v.x, g0.y + v.y);
     G[r.base + c.p] = St<T>::from_d(val);
-    if (r.at.p == c.p) diag64[c.p] = val;
+    if (diag64 != nullptr && r.at.p == c.p) diag64[c.p] = val;
   }
 };
 
@@ -623,81 +625,102 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     }
 }
 
-// The same product with a 128 x 128 output tile per workgroup of 512 threads
-// (8 waves in 2 x 4, each 64 x 32 = 4 x 2 tiles of the 16x16x4 instruction),
-// for the refresh, whose k is the flipped set (hundreds to thousands).  The
-// operands pass through LDS in chunks of 8 k with two buffers: the next chunk
-// is loaded into registers while the current one is multiplied, and a wave
-// waits on global memory only when it stores that chunk to LDS, 64 matrix
-// instructions later.  Each operand element is fetched once per workgroup
-// (1/32 byte per flop, against 1/8 for the 64 x 64 tile, whose waves each load
-// their own rows and columns).  It holds one workgroup per compute unit (two
-// waves per SIMD), so its epilogue does not overlap other tiles' products: the
-// 64 x 64 kernel stays the faster one for the flush's k <= 128, whose
-// epilogue reads and writes G.
-// Every accumulator takes the same instructions on the same operands in the
-// same order as in k_zgemm_f64, and the epilogue covers the same entries (the
-// 64 x 64 tiles wholly below the diagonal within rows < skip_below are left
-// alone), so the two kernels give bitwise equal results.
-constexpr int kZgT = 128, kZgKC = 8, kZgPitch = kZgT + 1;  // pitch: one pad entry per k row
+// The same product for the refresh, whose k is the flipped set (tens to thousands): a
+// GM x GN output tile per workgroup, 16 TM x 16 TU outputs per wave, the operands
+// through LDS in chunks of 8 k with two buffers.  The next chunk is loaded into
+// registers while the current one is multiplied, and a wave waits on global memory
+// only when it stores that chunk to LDS.  Each operand element is fetched once per
+// workgroup.  Bound by the FP64 matrix cores (72.6 TFLOP/s in a large library
+// product on the same card).
+//
+// M3: three real products per complex one (X = sum Ar Br, Y = sum Ai Bi, S = sum
+// (Ar + Ai)(Br + Bi); re = X - Y, im = S - X - Y), a quarter fewer matrix
+// instructions.  Its product's error is 1.4 times that of four products (against
+// long double, 70 to 900 flipped pixels), so it is taken where the result is
+// rounded to FP32, which hides both: complex64 storage, whose FP64 diagonal
+// k_rf_field computes with four.  The whole refresh at 128 x 128, 180 flipped
+// pixels: M3 on 64 x 64 tiles (2 x 2 per wave, 162 registers, three workgroups per
+// compute unit whose epilogues overlap other products) 3.95 ms, M3 on 128 x 64 4.23,
+// four products on 64 x 64 4.50, on 128 x 64 4.60, on 128 x 128 4.74.  complex128,
+// 96 x 131, 1509 flipped: 128 x 64 tiles (4 x 2 per wave) 29.3, 64 x 64 29.4, 128 x
+// 128 29.5 ms.
+//
+// Without M3 every accumulator takes the same instructions on the same operands in
+// the same order as in k_zgemm_f64, whatever the tile, and the epilogue covers the
+// same entries (the 64 x 64 tiles wholly below the diagonal within rows <
+// skip_below are left alone), so the results are bitwise equal.
+constexpr int kZgT = 128, kZgKC = 8;
 
-template <bool AT, bool BT, typename Epi>
-__global__ __launch_bounds__(512) void k_zgemm_f64_t128(int M, int N, int K, const double2* __restrict__ A,
-                                                        int64_t lda, const double2* __restrict__ B,
-                                                        int64_t ldb, const int32_t* __restrict__ kdev,
-                                                        Epi epi, int skip_below) {
+template <bool AT, bool BT, bool M3, int GM, int GN, int TM, int TU, typename Epi>
+__global__ __launch_bounds__(GM * GN / (4 * TM * TU), 2) void k_zgemm_f64_lds(int M, int N, int K, const double2* __restrict__ A,
+                                                       int64_t lda, const double2* __restrict__ B,
+                                                       int64_t ldb, const int32_t* __restrict__ kdev,
+                                                       Epi epi, int skip_below) {
   int by = (int)blockIdx.y, bx = (int)blockIdx.x;
   // (the last tiles first: the monitor rows' are the longest, their G0 entries being evaluated)
   if (skip_below > 0)
-    ut_group(gridDim.x - 1 - blockIdx.x, (N + kZgT - 1) / kZgT, skip_below / kZgT, kZgT, kZgT, by, bx);
-  __shared__ double2 As[2][kZgKC][kZgPitch], Bs[2][kZgKC][kZgPitch];
+    ut_group(gridDim.x - 1 - blockIdx.x, (N + GN - 1) / GN, skip_below / GM, GM, GN, by, bx);
+  constexpr int NT = GM * GN / (4 * TM * TU), EA = GM * kZgKC / NT, EB = GN * kZgKC / NT;   // threads, elements each stages
+  __shared__ double2 As[2][kZgKC][GM + 1], Bs[2][kZgKC][GN + 1];   // one pad entry per k row
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int tm0 = by * kZgT, tn0 = bx * kZgT;
-  const int wm = (w >> 2) * 64, wn = (w & 3) * 32;
+  const int tm0 = by * GM, tn0 = bx * GN;
+  constexpr int WN = GN / (16 * TU);                // waves across
+  const int wm = (w / WN) * 16 * TM, wn = (w % WN) * 16 * TU;
   const int li = lane & 15, lk = lane >> 4;
   // the wave's rows and columns lie in one 64 x 64 tile; a skipped one idles
+  static_assert(TM <= 4 && TU <= 4, "a wave's outputs lie in one 64 x 64 tile");
   const int ty = (tm0 + wm) >> 6, tx = (tn0 + wn) >> 6;
   const bool idle = skip_below > 0 && ty > tx && ((int64_t)ty + 1) * 64 <= skip_below;
   if (kdev != nullptr) K = min(K, *kdev);
-  f64x4 re[4][2], im[4][2];
+  // X, Y: re and im, or with M3 sum Ar Br and sum Ai Bi; S: sum (Ar + Ai)(Br + Bi)
+  f64x4 X[TM][TU], Y[TM][TU], S[M3 ? TM : 1][M3 ? TU : 1];
 #pragma unroll
-  for (int t = 0; t < 4; ++t)
+  for (int t = 0; t < TM; ++t)
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      re[t][u] = (f64x4){0.0, 0.0, 0.0, 0.0};
-      im[t][u] = (f64x4){0.0, 0.0, 0.0, 0.0};
+    for (int u = 0; u < TU; ++u) {
+      X[t][u] = Y[t][u] = (f64x4){0.0, 0.0, 0.0, 0.0};
+      if constexpr (M3) S[t][u] = (f64x4){0.0, 0.0, 0.0, 0.0};
     }
-  // staging: thread tid moves elements tid and tid + 512 of each 128 x 8 chunk,
+  // staging: thread tid moves elements tid, tid + NT, ... of each operand's chunk,
   // consecutive threads along the operand's contiguous index
   auto a_pos = [](int e, int& r, int& kk) {
-    if (AT) { r = e & 127; kk = e >> 7; } else { r = e >> 3; kk = e & 7; }
+    if (AT) { r = e & (GM - 1); kk = e / GM; } else { r = e >> 3; kk = e & 7; }
   };
   auto b_pos = [](int e, int& c, int& kk) {
-    if (BT) { c = e >> 3; kk = e & 7; } else { c = e & 127; kk = e >> 7; }
+    if (BT) { c = e >> 3; kk = e & 7; } else { c = e & (GN - 1); kk = e / GN; }
   };
-  double2 pa[2], pb[2];
+  double2 pa[EA], pb[EB];
   auto load = [&](int k0) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      int r, c, ka, kb;
-      a_pos(tid + 512 * i, r, ka);
-      b_pos(tid + 512 * i, c, kb);
-      const int row = tm0 + r, col = tn0 + c;
+    for (int i = 0; i < EA; ++i) {
+      int r, ka;
+      a_pos(tid + NT * i, r, ka);
+      const int row = tm0 + r;
       ka += k0;
-      kb += k0;
       pa[i] = row < M && ka < K ? (AT ? A[(int64_t)ka * lda + row] : A[(int64_t)row * lda + ka])
                                 : make_double2(0.0, 0.0);
+    }
+#pragma unroll
+    for (int i = 0; i < EB; ++i) {
+      int c, kb;
+      b_pos(tid + NT * i, c, kb);
+      const int col = tn0 + c;
+      kb += k0;
       pb[i] = col < N && kb < K ? (BT ? B[(int64_t)col * ldb + kb] : B[(int64_t)kb * ldb + col])
                                 : make_double2(0.0, 0.0);
     }
   };
   auto store = [&](int buf) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      int r, c, ka, kb;
-      a_pos(tid + 512 * i, r, ka);
-      b_pos(tid + 512 * i, c, kb);
+    for (int i = 0; i < EA; ++i) {
+      int r, ka;
+      a_pos(tid + NT * i, r, ka);
       As[buf][ka][r] = pa[i];
+    }
+#pragma unroll
+    for (int i = 0; i < EB; ++i) {
+      int c, kb;
+      b_pos(tid + NT * i, c, kb);
       Bs[buf][kb][c] = pb[i];
     }
   };
@@ -714,19 +737,24 @@ __global__ __launch_bounds__(512) void k_zgemm_f64_t128(int M, int N, int K, con
 #pragma unroll
       for (int st = 0; st < kZgKC / 4; ++st) {
         if (ch * kZgKC + 4 * st >= K) break;
-        double2 a[4], b[2];
+        double2 a[TM], b[TU];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) a[t] = As[buf][4 * st + lk][wm + 16 * t + li];
+        for (int t = 0; t < TM; ++t) a[t] = As[buf][4 * st + lk][wm + 16 * t + li];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) b[u] = Bs[buf][4 * st + lk][wn + 16 * u + li];
+        for (int u = 0; u < TU; ++u) b[u] = Bs[buf][4 * st + lk][wn + 16 * u + li];
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+        for (int t = 0; t < TM; ++t)
 #pragma unroll
-          for (int u = 0; u < 2; ++u) {
-            re[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].x, b[u].x, re[t][u], 0, 0, 0);
-            re[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[t].y, b[u].y, re[t][u], 0, 0, 0);
-            im[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].x, b[u].y, im[t][u], 0, 0, 0);
-            im[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].y, b[u].x, im[t][u], 0, 0, 0);
+          for (int u = 0; u < TU; ++u) {
+            X[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].x, b[u].x, X[t][u], 0, 0, 0);
+            if constexpr (M3) {
+              Y[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].y, b[u].y, Y[t][u], 0, 0, 0);
+              S[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].x + a[t].y, b[u].x + b[u].y, S[t][u], 0, 0, 0);
+            } else {
+              X[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[t].y, b[u].y, X[t][u], 0, 0, 0);
+              Y[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].x, b[u].y, Y[t][u], 0, 0, 0);
+              Y[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].y, b[u].x, Y[t][u], 0, 0, 0);
+            }
           }
       }
     }
@@ -734,35 +762,51 @@ __global__ __launch_bounds__(512) void k_zgemm_f64_t128(int M, int N, int K, con
     __syncthreads();
   }
   if (idle) return;
-  const int cn0 = tn0 + wn + li, cn1 = cn0 + 16;
-  const auto ca0 = epi.col(cn0 < N ? cn0 : 0), ca1 = epi.col(cn1 < N ? cn1 : 0);
 #pragma unroll
-  for (int t = 0; t < 4; ++t)
+  for (int u = 0; u < TU; ++u) {
+    const int col = tn0 + wn + 16 * u + li;
+    if (col >= N) continue;
+    const auto ca = epi.col(col);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int row = tm0 + wm + 16 * t + lk + 4 * e;
-      if (row >= M) continue;
-      const auto ra = epi.row(row);
-      if (cn0 < N) epi(ra, ca0, make_double2(re[t][0][e], im[t][0][e]));
-      if (cn1 < N) epi(ra, ca1, make_double2(re[t][1][e], im[t][1][e]));
-    }
+    for (int t = 0; t < TM; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int row = tm0 + wm + 16 * t + lk + 4 * e;
+        if (row >= M) continue;
+        double2 v = make_double2(X[t][u][e], Y[t][u][e]);
+        if constexpr (M3) v = make_double2(X[t][u][e] - Y[t][u][e], S[t][u][e] - X[t][u][e] - Y[t][u][e]);
+        epi(epi.row(row), ca, v);
+      }
+  }
 }
 
 // E = Einc + Z x with x = Einc[V] (Z = U M), one wave per row.  (As x = M Einc[V]
 // and then U x, one thread per row each, the two took 0.8 ms at 1500 flipped
-// pixels.)
-template <typename T>
+// pixels.)  DIAG: also diag64[r] = G0[r, r] + Z[r, :] U[r, :] of the design rows.
+template <typename T, bool DIAG>
 __global__ __launch_bounds__(256) void k_rf_field(Geo g, const double* __restrict__ mon_xy,
-                                                  const double2* __restrict__ Z, const double2* __restrict__ x,
-                                                  int k, int kp, T* __restrict__ E) {
+                                                  const double2* __restrict__ table,
+                                                  const double2* __restrict__ Z, const double2* __restrict__ U,
+                                                  const double2* __restrict__ x, int k, int kp, T* __restrict__ E,
+                                                  double2* __restrict__ diag64) {
   const int r = blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (r >= g.R) return;
-  double2 s = make_double2(0.0, 0.0);
+  double2 s = make_double2(0.0, 0.0), d = s;
 #pragma unroll 4
-  for (int i = lane; i < k; i += 64) s = cadd(s, cmul(Z[(int64_t)r * kp + i], x[i]));
+  for (int i = lane; i < k; i += 64) {
+    const double2 z = Z[(int64_t)r * kp + i];
+    s = cadd(s, cmul(z, x[i]));
+    if (DIAG && r < g.N) d = cadd(d, cmul(z, U[(int64_t)r * kp + i]));
+  }
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) s = cadd(s, make_double2(__shfl_xor(s.x, o, 64), __shfl_xor(s.y, o, 64)));
-  if (lane == 0) E[r] = St<T>::from_d(cadd(incident(g, mon_xy, r), s));
+  for (int o = 32; o > 0; o >>= 1) {
+    s = cadd(s, make_double2(__shfl_xor(s.x, o, 64), __shfl_xor(s.y, o, 64)));
+    if (DIAG) d = cadd(d, make_double2(__shfl_xor(d.x, o, 64), __shfl_xor(d.y, o, 64)));
+  }
+  if (lane == 0) {
+    E[r] = St<T>::from_d(cadd(incident(g, mon_xy, r), s));
+    if (DIAG && r < g.N) diag64[r] = cadd(table[0], d);
+  }
 }
 
 // Flipped list V (in the workspace) and its length k, read back to the host
@@ -868,25 +912,30 @@ static int refresh_typed(const Geo& g, gfo_state* st, const Layout& L, int32_t k
     // them the 64 x 64 kernel fills the chip better
     const int zx = (kp + kZgT - 1) / kZgT, zy = (g.R + kZgT - 1) / kZgT;
     if ((int64_t)zx * zy >= 1024)
-      hipLaunchKernelGGL((k_zgemm_f64_t128<false, false, EpiStoreZ>), dim3(zx, zy), dim3(512), 0, s, g.R, kp, kp,
+      hipLaunchKernelGGL((k_zgemm_f64_lds<false, false, false, kZgT, kZgT, 4, 2, EpiStoreZ>), dim3(zx, zy), dim3(512), 0, s, g.R, kp, kp,
                          (const double2*)U, (int64_t)kp, (const double2*)M, (int64_t)kp, (const int32_t*)nullptr, ez, 0);
     else
       hipLaunchKernelGGL((k_zgemm_f64<false, false, EpiStoreZ>), dim3((kp + 63) / 64, (g.R + 63) / 64), dim3(256), 0, s,
                          g.R, kp, kp, (const double2*)U, (int64_t)kp, (const double2*)M, (int64_t)kp,
                          (const int32_t*)nullptr, ez, 0);
   }
-  hipLaunchKernelGGL(k_rf_field<T>, dim3((unsigned)((g.R + 3) / 4)), dim3(256), 0, s, g, mon,
-                     (const double2*)Z, (const double2*)x, k, kp, (T*)st->E);
+  hipLaunchKernelGGL((k_rf_field<T, std::is_same<T, float2>::value>), dim3((unsigned)((g.R + 3) / 4)), dim3(256), 0, s,
+                     g, mon, table, (const double2*)Z, (const double2*)U, (const double2*)x, k, kp, (T*)st->E,
+                     (double2*)st->diag64);
   // G = G0 + Z U_D^T over the N design columns (padding columns stay zero):
   // the monitor rows whole and the design block on and above its diagonal (the
   // block is symmetric); when the caller keeps the whole block, its lower
   // triangle is then the mirror of the upper one (half the product's work)
-  EpiG0<T> eg{g, table, mon, (T*)st->G, (double2*)st->diag64};
-  const int ty = (g.R + kZgT - 1) / kZgT, tx = (g.N + kZgT - 1) / kZgT;
-  hipLaunchKernelGGL((k_zgemm_f64_t128<false, true, EpiG0<T>>),
-                     dim3((unsigned)ut_group_count(ty, tx, g.N / kZgT, kZgT, kZgT)), dim3(512), 0, s, g.R, g.N, kp,
-                     (const double2*)Z, (int64_t)kp,
-                     (const double2*)U, (int64_t)kp, (const int32_t*)nullptr, eg, g.N);
+  EpiG0<T> eg{g, table, mon, (T*)st->G, g.dtype == GFO_C64 ? nullptr : (double2*)st->diag64};
+  // complex64: three real products per complex one (the result is rounded to FP32
+  // once, and diag64 comes from k_rf_field); complex128: four
+  constexpr bool c64 = std::is_same<T, float2>::value;
+  constexpr int GM = c64 ? 64 : 128, GN = 64, TM = c64 ? 2 : 4, TU = 2;
+  const int ty = (g.R + GM - 1) / GM, tx = (g.N + GN - 1) / GN;
+  hipLaunchKernelGGL((k_zgemm_f64_lds<false, true, c64, GM, GN, TM, TU, EpiG0<T>>),
+                     dim3((unsigned)ut_group_count(ty, tx, g.N / GM, GM, GN)), dim3(GM * GN / (4 * TM * TU)), 0, s,
+                     g.R, g.N, kp, (const double2*)Z, (int64_t)kp, (const double2*)U, (int64_t)kp,
+                     (const int32_t*)nullptr, eg, g.N);
   if (note_hip(hipGetLastError()) != hipSuccess) return GFO_EHIP;
   if (!g.upper && launch_sync_lower(g, st, s) != hipSuccess) return GFO_EHIP;   // dense storage
   return GFO_OK;
