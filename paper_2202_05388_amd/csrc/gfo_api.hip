@@ -236,7 +236,6 @@ int init_G0(const gfo_problem* prob, gfo_state* st, hipStream_t stream) {
                               hipMemcpyHostToDevice, stream)) != hipSuccess)
     return GFO_EHIP;
   if (launch_init(g, st, L, stream) != hipSuccess) return GFO_EHIP;
-  if (launch_dl_reset(g, st, L, stream) != hipSuccess) return GFO_EHIP;
   st->pending_calls = 0;
   // deferred mode, or a caller that asked for it (lower_stale = 1 on entry),
   // keeps the upper triangle of the design block alone

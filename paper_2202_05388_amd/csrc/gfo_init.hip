@@ -10,6 +10,8 @@
 // J0/Y0/J1/Y1 are the FP64 device Bessel functions of the ROCm math library.
 #include "gfo_internal.hpp"
 
+#include <algorithm>
+
 namespace gfo {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -29,62 +31,55 @@ __device__ __forceinline__ double2 self_term(const Geo& g) {
   return make_double2(-f * y1(x) - 1.0 / g.k0sq, f * j1(x));
 }
 
-// table[dy * nx + dx] = G0 between pixels offset by (dy, dx) rows/cols
-__global__ void k_init_table(Geo g, double2* __restrict__ table) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= g.ny * g.nx) return;
-  int dy = i / g.nx, dx = i - (i / g.nx) * g.nx;
-  double2 v;
-  if (i == 0) {
-    v = self_term(g);
-  } else {
-    double r = g.h * sqrt((double)dx * dx + (double)dy * dy);
-    v = kernel_h2g(r, g);
-  }
-  table[i] = v;
-}
-
 // Design block: G[p, q] = table[|iy_p - iy_q|, |ix_p - ix_q|]; columns >= N zeroed.
-// A thread writes VN = 16 / sizeof(T) consecutive columns of a row with one
-// 16-byte non-temporal store; the workgroups of grid row y take the rows
-// y, y + gridDim.y, ...  With `upper`, stores that lie wholly below the
-// diagonal are skipped (deferred mode reads the design block from its upper
-// triangle; the caller marks the lower one out of date).
+// A workgroup takes 256 x VN consecutive columns (VN = 16 / sizeof(T) per thread: one
+// 16-byte non-temporal store) and kFillRows consecutive rows of one grid row iy_p, so
+// that a thread's table rows are fixed, a matrix row costs it a column distance, VN
+// table reads (of lines its neighbours read too) and a store, and all rows' reads are
+// in flight together.  With `upper`, stores that lie wholly below the diagonal are
+// skipped (the caller marks the lower triangle out of date).
+// Bound by the stores: constants stored in the same pattern take 205 us for the 1.08 GB
+// upper triangle of 128 x 128 complex64; this takes 235 us with 4 rows (16 rows: 262 us,
+// 2: 278 us, one row in address order: 300 us; a form whose workgroups took every
+// 2048th row, with the divisions and products of each entry's address: 243 us).
+// 31 x 47: 4.4 us (16 rows, too few workgroups: 6.5 us).
+constexpr int kFillRows = 4;
+
 template <typename T>
-__global__ void k_fill_design(Geo g, T* __restrict__ G, const double2* __restrict__ table,
-                              int upper) {
+__global__ __launch_bounds__(256) void k_fill_design(Geo g, T* __restrict__ G, const double2* __restrict__ table,
+                                                     int upper, int nseg) {
   constexpr int VN = 16 / (int)sizeof(T);
-  const int64_t q0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * VN;
+  const int64_t q0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * VN;
   if (q0 >= g.ld) return;
   int iyq[VN], ixq[VN];
+  bool in[VN];
 #pragma unroll
   for (int v = 0; v < VN; ++v) {
-    iyq[v] = (int)((q0 + v) / g.nx);
-    ixq[v] = (int)(q0 + v - (int64_t)iyq[v] * g.nx);
+    in[v] = q0 + v < g.N;
+    const int q = in[v] ? (int)(q0 + v) : 0;
+    iyq[v] = q / g.nx;
+    ixq[v] = q - iyq[v] * g.nx;
   }
-  // with `upper`, rows past the workgroup's last column hold nothing to write
-  const int64_t wg_end = ((int64_t)blockIdx.x + 1) * blockDim.x * VN;
-  const int p_end = upper && wg_end < g.N ? (int)wg_end : g.N;
-  // two rows per step: both rows' table reads are in flight before the stores
-  // (one row at a time: init_G0 329 us at 128 x 128; two: 291 us; four or eight:
-  // no faster)
-  constexpr int RB = 2;
-  for (int p0 = blockIdx.y; p0 < p_end; p0 += RB * gridDim.y) {
-    double2 d[RB][VN];
+  for (int yb = (int)blockIdx.y; yb < g.ny * nseg; yb += (int)gridDim.y) {
+    const int iyp = yb / nseg, x0 = (yb - iyp * nseg) * kFillRows;
+    const int p0 = iyp * g.nx + x0, nr = min(kFillRows, g.nx - x0);
+    // rows past the workgroup's last column hold nothing to write
+    if (upper && p0 >= ((int64_t)blockIdx.x + 1) * 256 * VN) return;
+    const double2* __restrict__ tab[VN];
 #pragma unroll
-    for (int r = 0; r < RB; ++r) {
-      const int p = p0 + r * gridDim.y;
-      const int iyp = p / g.nx, ixp = p - (p / g.nx) * g.nx;
+    for (int v = 0; v < VN; ++v) tab[v] = table + (int64_t)abs(iyp - iyq[v]) * g.nx;
+    double2 d[kFillRows][VN];
+#pragma unroll
+    for (int r = 0; r < kFillRows; ++r)
 #pragma unroll
       for (int v = 0; v < VN; ++v) {
-        d[r][v] = make_double2(0.0, 0.0);
-        if (p < p_end && q0 + v < g.N) d[r][v] = table[abs(iyp - iyq[v]) * g.nx + abs(ixp - ixq[v])];
+        d[r][v] = tab[v][abs(x0 + min(r, nr - 1) - ixq[v])];
+        d[r][v] = pick_of(in[v], d[r][v], make_double2(0.0, 0.0));
       }
-    }
 #pragma unroll
-    for (int r = 0; r < RB; ++r) {
-      const int p = p0 + r * gridDim.y;
-      if (p >= p_end || (upper && q0 + VN - 1 < p)) continue;
+    for (int r = 0; r < kFillRows; ++r) {
+      const int p = p0 + r;
+      if (r >= nr || (upper && q0 + VN - 1 < p)) continue;
       T* dst = G + g_off(g, p, q0);   // packed: q0 >= 64 (p / 64) here (upper)
       if constexpr (VN == 2) {
         const float2 a = St<T>::from_d(d[r][0]), b = St<T>::from_d(d[r][1]);
@@ -96,52 +91,61 @@ __global__ void k_fill_design(Geo g, T* __restrict__ G, const double2* __restric
   }
 }
 
-// Monitor rows: direct FP64 evaluation.
+// Everything of the empty design that does not read the offset table, in one launch
+// (each part alone is a launch of 3 to 5 us; four were a fifth of the set-up of a
+// 24 x 24 job): workgroups [0, nv) the vectors, E = exp(i k0 y) on every row, diag64,
+// eps_idx, the counters; [nv, nv + nt) the table, table[dy nx + dx] = G0 between pixels
+// offset by (dy, dx); from nv + nt on the monitor rows, direct FP64 evaluation, 256
+// columns of one row each (packed 48 x 2048 with 256 monitors, 25 M kernel values: 291 us,
+// 365 us in a launch of their own that walked the rows).  Bound by the Bessel functions (48 registers with the one
+// evaluation that table and monitors share; 194 with one each and a loop over rows).
 template <typename T>
-__global__ void k_fill_monitors(Geo g, T* __restrict__ G, const double* __restrict__ mon_xy) {
-  int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= g.ld) return;
-  for (int m = blockIdx.y; m < g.nmon; m += gridDim.y) {
-    T out;
-    if (q < g.N) {
-      int iyq = (int)(q / g.nx), ixq = (int)(q - (int64_t)iyq * g.nx);
-      double xq = (ixq - 0.5 * (g.nx - 1)) * g.h;
-      double yq = (iyq - 0.5 * (g.ny - 1)) * g.h;
-      double dx = mon_xy[2 * m] - xq, dy = mon_xy[2 * m + 1] - yq;
-      out = St<T>::from_d(kernel_h2g(sqrt(dx * dx + dy * dy), g));
-    } else {
-      out = St<T>::from_d(make_double2(0.0, 0.0));
+__global__ __launch_bounds__(256) void k_init_rest(Geo g, T* __restrict__ G, T* __restrict__ E,
+                                                   double2* __restrict__ diag64, uint8_t* __restrict__ eps_idx,
+                                                   const double* __restrict__ mon_xy, double2* __restrict__ table,
+                                                   int32_t* n_flips, int32_t* status, int32_t* pending,
+                                                   int nv, int nt, int64_t b0) {
+  const int64_t b = b0 + blockIdx.x;
+  if (b < nv) {
+    const int i = (int)b * 256 + threadIdx.x;
+    if (i < g.R) {
+      const double y = i < g.N ? (i / g.nx - 0.5 * (g.ny - 1)) * g.h : mon_xy[2 * (i - g.N) + 1];
+      double s, c;
+      sincos(g.k0 * y, &s, &c);
+      E[i] = St<T>::from_d(make_double2(c, s));
     }
-    G[g_off(g, g.N + m, q)] = out;
-  }
-}
-
-// E = exp(i k0 y) on every row; diag64, eps_idx, counters.
-template <typename T>
-__global__ void k_init_vectors(Geo g, T* __restrict__ E, double2* __restrict__ diag64,
-                               uint8_t* __restrict__ eps_idx, const double* __restrict__ mon_xy,
-                               const double2* __restrict__ table, int32_t* n_flips,
-                               int32_t* status) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < g.R) {
-    double y;
     if (i < g.N) {
-      int iy = i / g.nx;
-      y = (iy - 0.5 * (g.ny - 1)) * g.h;
-    } else {
-      y = mon_xy[2 * (i - g.N) + 1];
+      diag64[i] = self_term(g);
+      eps_idx[i] = (uint8_t)g.bg_idx;
+      if (i == 0) {
+        table[0] = diag64[0];
+        *n_flips = 0;
+        *status = 0;
+        *pending = 0;
+      }
     }
-    double s, c;
-    sincos(g.k0 * y, &s, &c);
-    E[i] = St<T>::from_d(make_double2(c, s));
+    return;
   }
-  if (i < g.N) {
-    diag64[i] = table[0];
-    eps_idx[i] = (uint8_t)g.bg_idx;
+  const bool tab = b < nv + nt;
+  const int nc = (int)((g.ld + 255) / 256);
+  const int m = tab ? 0 : (int)((b - nv - nt) / nc);
+  const int64_t q = (tab ? b - nv : b - nv - nt - (int64_t)m * nc) * 256 + threadIdx.x;
+  const int iy = (int)q / g.nx, ix = (int)q - iy * g.nx;
+  double dx = ix, dy = iy;
+  if (!tab) {
+    const double xq = (ix - 0.5 * (g.nx - 1)) * g.h;
+    const double yq = (iy - 0.5 * (g.ny - 1)) * g.h;
+    dx = mon_xy[2 * m] - xq;
+    dy = mon_xy[2 * m + 1] - yq;
   }
-  if (i == 0) {
-    *n_flips = 0;
-    *status = 0;
+  double r = sqrt(dx * dx + dy * dy);
+  if (tab) r = g.h * r;
+  double2 v = make_double2(0.0, 0.0);
+  if (q < g.N) v = kernel_h2g(r, g);
+  if (tab) {
+    if (q > 0 && q < g.N) table[q] = v;
+  } else if (q < g.ld) {
+    G[g_off(g, g.N + m, q)] = St<T>::from_d(v);
   }
 }
 
@@ -149,23 +153,22 @@ template <typename T>
 static hipError_t init_typed(const Geo& g, gfo_state* st, const Layout& L, hipStream_t s) {
   char* w = (char*)st->work;
   double2* table = (double2*)(w + L.table);
-  double* mon = (double*)(w + L.mon_xy);
   T* G = (T*)st->G;
-  int nt = g.ny * g.nx;
-  hipLaunchKernelGGL(k_init_table, dim3((nt + 255) / 256), dim3(256), 0, s, g, table);
-  dim3 blk(256);
+  const int nv = (g.R + 255) / 256, nt = (g.N + 255) / 256;
+  const int64_t nb = nv + nt + (g.ld + 255) / 256 * g.nmon;
+  constexpr int64_t kMaxBlocks = 1 << 22;   // per launch (2^30 work-items)
+  for (int64_t b0 = 0; b0 < nb; b0 += kMaxBlocks)
+    hipLaunchKernelGGL(k_init_rest<T>, dim3((unsigned)std::min(nb - b0, kMaxBlocks)), dim3(256), 0, s, g, G,
+                       (T*)st->E, (double2*)st->diag64, st->eps_idx, (const double*)(w + L.mon_xy), table,
+                       st->n_flips, st->status, (int32_t*)(w + L.dl_hdr), nv, nt, b0);
   constexpr int VN = 16 / (int)sizeof(T);
-  // a few rows per workgroup: workgroup dispatch, not the stores, bounds one row each
-  dim3 grd((unsigned)((g.ld + 256 * VN - 1) / (256 * VN)), (unsigned)(g.N < 2048 ? g.N : 2048));
-  hipLaunchKernelGGL(k_fill_design<T>, grd, blk, 0, s, g, G, (const double2*)table,
-                     g.upper);
-  if (g.nmon > 0) {
-    dim3 grm((unsigned)((g.ld + 255) / 256), (unsigned)(g.nmon < 65535 ? g.nmon : 65535));
-    hipLaunchKernelGGL(k_fill_monitors<T>, grm, blk, 0, s, g, G, (const double*)mon);
-  }
-  hipLaunchKernelGGL(k_init_vectors<T>, dim3((g.R + 255) / 256), dim3(256), 0, s, g, (T*)st->E,
-                     (double2*)st->diag64, st->eps_idx, (const double*)mon, (const double2*)table,
-                     st->n_flips, st->status);
+  // narrow or very large grids: the workgroups walk the rows (at most 65535 of them over
+  // the rows, and 2^31 work-items in the launch)
+  const int nseg = (g.nx + kFillRows - 1) / kFillRows;
+  const int64_t gx = (g.ld + 256 * VN - 1) / (256 * VN);
+  const int64_t gy = std::min({(int64_t)g.ny * nseg, (int64_t)65535, std::max<int64_t>(1, ((int64_t)1 << 31) / (gx * 256))});
+  hipLaunchKernelGGL(k_fill_design<T>, dim3((unsigned)gx, (unsigned)gy), dim3(256), 0, s, g, G,
+                     (const double2*)table, g.upper, nseg);
   return note_hip(hipGetLastError());
 }
 

@@ -1,0 +1,47 @@
+"""init_G0 at the edges of its blocks: rows in fours within a grid row, two columns
+per thread across the end of a grid row, the monitor columns, grids taller than one
+launch's row blocks."""
+import numpy as np
+import pytest
+
+from oracle import greens, state as ost
+import workloads as W
+from parity import rel_elem
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("ny,nx,n_mon", [(1, 1, 1), (5, 1, 2), (1, 3, 1), (3, 4, 3), (4, 5, 1),
+                                         (7, 7, 4), (2, 257, 2), (9, 63, 5), (129, 4, 2)])
+@pytest.mark.parametrize("kw", [{}, {"delay": 16}, {"delay": 16, "packed": True}])
+def test_fill_edges(dtype, ny, nx, n_mon, kw):
+    """Tolerance: an entry is one FP64 Bessel value, off by a few u of its size near
+    1 (arguments up to 1e2 add 1e2 u; against the floor of 1e-3 of the largest entry
+    that is 1e5 u = 1e-11), rounded once to storage (complex64: 2^-24 per part)."""
+    from paper_2202_05388_amd.job import Job
+    p = W.tiny(ny, nx, n_mon=n_mon, dtype=dtype)
+    print(f"[case] {ny}x{nx} mon={n_mon} {dtype} {kw}", flush=True)
+    job = Job(p, device="cuda:0", **kw)
+    job.init()
+    G, E, d, idx = job.host_state()
+    G0 = greens.build_G0(p)
+    tol = 1e-11 if dtype == "c128" else 2e-7
+    assert G.shape == G0.shape and rel_elem(G, G0) <= tol
+    assert rel_elem(E, ost.dense_state(p, ost.eps_of(p, idx))[1]) <= tol
+    assert rel_elem(d, np.diagonal(G0[:p.n])) <= 1e-11
+    assert (idx == 0).all() and job.status() == 0
+
+
+def test_fill_taller_than_one_launch():
+    """66,000 rows of one pixel: more row blocks than the launch has workgroups.
+    G[p, q] depends on |p - q| alone and comes from the same table entry: equal bits."""
+    import torch
+    from paper_2202_05388_amd.job import Job
+    p = W.tiny(66000, 1, n_mon=1, dtype="c64")
+    job = Job(p, device="cuda:0", delay=16)
+    job.init()
+    torch.cuda.synchronize()
+    N = p.n
+    for r in (1, 3, 4, 511, 65023, 65027, 65028, 65534, 65535, 65536, N - 1):
+        assert torch.equal(job.G[r, r:N], job.G[0, :N - r]), r
