@@ -301,12 +301,20 @@ struct SegWalk {
     return nmb * ((s0 + sw < nbx ? s0 + sw : nbx) - s0);
   }
   __device__ SegTile at(int t) const {
-    SegTile c{0, 0, M, 0, 0};
-    int u = t;
+    int seg = 0, base = 0;
+    return seek(t, seg, base);
+  }
+  // tile t, searched from segment seg on, whose first tile is base; both are left at
+  // t's segment
+  __device__ SegTile seek(int t, int& seg, int& base) const {
+    SegTile c{0, 0, M, 0, seg};
+    int u = t - base;
     while (u >= seg_tri(c.seg) + seg_mon(c.seg)) {
       u -= seg_tri(c.seg) + seg_mon(c.seg);
       ++c.seg;
     }
+    seg = c.seg;
+    base = t - u;
     const int s0 = sw * c.seg, nt = seg_tri(c.seg);
     if (u < nt) {
       const int e = s0 + sw < nby ? s0 + sw : nby, wd = e - s0;
@@ -655,10 +663,44 @@ __global__ __launch_bounds__(256) void k_flush_pack_s3(int R, int64_t ld,
   emit(V, ld, V3);
 }
 
+// The tiles of one workgroup of a persistent flush, in order.  Each XCD takes an
+// eighth of the list; its n workgroups (P / 8, consecutive workgroups go to different
+// XCDs) walk it together, bl tiles each at a time, so that they work in the same
+// column segment and its V parts are read from HBM once per XCD and then from its L2.
+// The last bl to 2 bl tiles per workgroup are cut evenly.  A list of fewer than 8 bl
+// tiles per workgroup is one even cut: it spans two segments at most, and a cut by
+// rounds costs more loads of the A parts (128 x 128 at 64 terms, 65 tiles per
+// workgroup: 463 us in one cut, 485 in rounds; 256 x 256: 8.33 and 8.20 ms).
+struct RunList {
+  int i, n, bl, first, total, rounds, tail;
+  __device__ RunList(int P, int b, int T, int block) {
+    const bool x8 = (P & 7) == 0;
+    const int x = x8 ? b & 7 : 0, per = x8 ? (T + 7) >> 3 : T;
+    i = x8 ? b >> 3 : b;
+    n = x8 ? P >> 3 : P;
+    bl = block;
+    first = x * per;
+    total = (T - first < per ? T - first : per);
+    const int r = total / (n * bl) - 1;
+    rounds = r >= 7 ? r : 0;
+    tail = (total - rounds * n * bl + n - 1) / n;
+  }
+  __device__ int count() const {
+    const int left = total - rounds * n * bl - i * tail;
+    return rounds * bl + (left < 0 ? 0 : left < tail ? left : tail);
+  }
+  // tile k of the workgroup; whether it directly follows tile k - 1
+  __device__ int tile(int k) const {
+    const int r = k / bl;
+    if (r < rounds) return first + (r * n + i) * bl + (k - r * bl);
+    return first + rounds * n * bl + i * tail + (k - rounds * bl);
+  }
+  __device__ bool contiguous(int k) const { return k > rounds * bl || k % bl != 0; }
+};
+
 // Persistent band flush with split products (KC chunks of 16 terms: 2 for up to
-// 32 terms, 4 for up to 64 at two workgroups per compute unit; 8 for up to 128
-// at one, its A parts taking 192 registers of a wave, its B halves 96 KB of
-// LDS).  Same tile list, run assignment, G buffers and
+// 32 terms, 4 for up to 64, at two workgroups per compute unit; more terms:
+// k_flush_c64_s3_ring).  Same tile list, G buffers and
 // epilogue layout as k_flush_c64_band in column-segment order; per wave the
 // output is the 32 x 32 block (rows 32 (w >> 1), columns 32 (w & 1)) of the
 // tile, accumulated as XR = sum Ar Br, XI = sum Ai Bi, Z = sum (Ar Bi + Ai Br).
@@ -670,20 +712,18 @@ __global__ __launch_bounds__(256) void k_flush_pack_s3(int R, int64_t ld,
 //     read into registers while the current tile's matrix steps run on the
 //     other half, and written into its half after a barrier;
 //   - G(t+1) is read into registers after tile t's epilogue, in flight during
-//     tile t+1's matrix steps (at one workgroup per compute unit a second G
-//     register set, G(t+2) in flight, measured slower: 903 against 854 us at
-//     128 terms on the 128 x 128 grid).
+//     tile t+1's matrix steps.
 // Global loads of one wave retire in order; the order per tile, B(t+2) first
 // half, then G(t+1), lets the first-half write of the next tile wait for its
 // B loads while G(t+1) is still in flight.  Rows past the matrix read zero and
 // their stores are dropped (buffer ranges), so every load and store is
 // unconditional.
 template <int KC>
-__global__ __launch_bounds__(256, KC == 8 ? 1 : 2) void k_flush_c64_s3(int M, int R, int64_t ld,
+__global__ __launch_bounds__(256, 2) void k_flush_c64_s3(int M, int R, int64_t ld,
                                                       const int32_t* __restrict__ count,
                                                       const bf16x8* __restrict__ A3,
                                                       const bf16x8* __restrict__ V3,
-                                                      float2* __restrict__ G, int nby, int chunk,
+                                                      float2* __restrict__ G, int nby,
                                                       int packed, int64_t mon_base, int sw) {
   constexpr int NU = 12 * KC;         // split units per index
   constexpr int HU = NU / 2;          // units per LDS half
@@ -692,11 +732,9 @@ __global__ __launch_bounds__(256, KC == 8 ? 1 : 2) void k_flush_c64_s3(int M, in
   if (K == 0) return;
   const SegWalk walk{M, R, nby, (int)(ld / 64), (R - M + 63) / 64, sw};
   const int T = nby * (nby + 1) / 2 + walk.nmb * walk.nbx;
-  const int P = (int)gridDim.x, b = (int)blockIdx.x;
-  const int run = (P & 7) == 0 ? (b & 7) * (P >> 3) + (b >> 3) : b;
-  const int t0 = run * chunk;
-  const int t1 = t0 + chunk < T ? t0 + chunk : T;
-  if (t0 >= t1) return;
+  const RunList list((int)gridDim.x, (int)blockIdx.x, T, sw);
+  const int cnt = list.count();
+  if (cnt <= 0) return;
   __shared__ bf16x8 Bsh[NU][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int h = lane >> 5;
@@ -775,8 +813,13 @@ __global__ __launch_bounds__(256, KC == 8 ? 1 : 2) void k_flush_c64_s3(int M, in
     }
   };
   // prologue: tile t0's operands and B, then the next tile's first half and G(t0)
-  SegTile cur = walk.at(t0);
-  SegTile nxt = t0 + 1 < t1 ? walk.next(cur) : cur;
+  int seg = 0, base = 0;
+  auto advance = [&](const SegTile& c, int i) __attribute__((always_inline)) {   // c: tile i - 1
+    if (i >= cnt) return c;
+    return list.contiguous(i) ? walk.next(c) : walk.seek(list.tile(i), seg, base);
+  };
+  SegTile cur = walk.seek(list.tile(0), seg, base);
+  SegTile nxt = advance(cur, 1);
   load_A(cur);
   load_S(cur.bx, 0);
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
@@ -787,8 +830,8 @@ __global__ __launch_bounds__(256, KC == 8 ? 1 : 2) void k_flush_c64_s3(int M, in
   load_S(nxt.bx, 0);
   load_G(cur, gG);
   __syncthreads();
-  if (KC < 8 && (run & 1) && (P & 7) == 0) __builtin_amdgcn_s_sleep(48);
-  for (int t = t0; t < t1; ++t) {
+  if ((list.i & 1) && (gridDim.x & 7) == 0) __builtin_amdgcn_s_sleep(48);
+  for (int t = 0; t < cnt; ++t) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) XR[e] = XI[e] = Z[e] = 0.f;
     steps(0, KC / 2);
@@ -813,12 +856,185 @@ __global__ __launch_bounds__(256, KC == 8 ? 1 : 2) void k_flush_c64_s3(int M, in
     }
     __builtin_amdgcn_sched_barrier(0);
     // B(t+2) first half, then G(t+1)
-    const SegTile nn = t + 2 < t1 ? walk.next(nxt) : nxt;
+    const SegTile nn = advance(nxt, t + 2);
     load_S(nn.bx, 0);
     load_G(nxt, gG);
     cur = nxt;
     nxt = nn;
   }
+}
+
+// The same flush for 65 to 128 terms (KC = 8), one workgroup per compute unit: the A
+// parts of 128 terms take 192 registers of a wave, so one wave per SIMD has to keep
+// its matrix core busy by itself.  Per tile 192 matrix steps in four phases of two
+// chunks, and everything else placed between them, at most two memory operations to
+// every four steps:
+//   - B in a ring of four LDS slots, one phase each.  In phase q the part planes of
+//     the phase after next go from registers into slot q + 2 and the registers are
+//     loaded again, a whole tile ahead; operands are read two groups ahead, across
+//     the phase's barrier, which is the only one.
+//   - G(t+1) is read after tile t's entries are stored, a whole tile ahead as well.
+// The order of the matrix steps of an entry is that of k_flush_c64_s3, and so are its
+// bits.  Bound by the matrix cores' rate under this load (the clock falls to 1.7 GHz):
+// packed 48 x 2048 with 256 monitors at 128 terms, 29.9 TFLOP of part products and
+// 77 GB of G, 28.9 ms (1.03 PFLOP/s); 32.3 ms with B in two halves between barriers
+// and each workgroup on a stretch of the list of its own (31.1 ms in rounds, which
+// take the reads from HBM from 114 to 51 GB; 29.7 ms without the placing).
+// 128 x 128: 751 us, 862 before; 32 x 32: 11.3 us, 12.8 before.
+__global__ __launch_bounds__(256, 1) void k_flush_c64_s3_ring(int M, int R, int64_t ld,
+                                                              const int32_t* __restrict__ count,
+                                                              const bf16x8* __restrict__ A3,
+                                                              const bf16x8* __restrict__ V3,
+                                                              float2* __restrict__ G, int nby,
+                                                              int packed, int64_t mon_base, int sw) {
+  constexpr int KC = 8, NU = 12 * KC, PU = 24;   // units per index; per phase
+  const int K = *count;
+  if (K == 0) return;
+  const SegWalk walk{M, R, nby, (int)(ld / 64), (R - M + 63) / 64, sw};
+  const int T = nby * (nby + 1) / 2 + walk.nmb * walk.nbx;
+  const RunList list((int)gridDim.x, (int)blockIdx.x, T, sw);
+  const int cnt = list.count();
+  if (cnt <= 0) return;
+  __shared__ bf16x8 Bsh[4][PU][64];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int h = lane >> 5;
+  const __amdgpu_buffer_rsrc_t ra =
+      __builtin_amdgcn_make_buffer_rsrc((void*)A3, (short)0, NU * R * 16, kBufferDword3);
+  const __amdgpu_buffer_rsrc_t rb =
+      __builtin_amdgcn_make_buffer_rsrc((void*)V3, (short)0, (int)(NU * ld * 16), kBufferDword3);
+  const int q32 = (w >> 1) * 32 + (lane & 31);  // row of the band (A operand)
+  const int cc = (w & 1) * 32 + (lane & 31);    // column of the tile (B operand)
+  const int lrow = (w >> 1) * 32 + 4 * h;       // the lane's first output row within a tile
+  bf16x8 aR[6 * KC];
+  auto load_A = [&](const SegTile& c) __attribute__((always_inline)) {
+    const int am = c.rbase + q32;
+    const unsigned off = am < c.lim ? (unsigned)am * 16u : 0xFFFFFFF0u;
+#pragma unroll
+    for (int k = 0; k < KC; ++k)
+#pragma unroll
+      for (int p = 0; p < 6; ++p) {
+        const unsigned u = (unsigned)(6 * (2 * k + h) + p);
+        aR[6 * k + p] = __builtin_bit_cast(
+            bf16x8, __builtin_amdgcn_raw_buffer_load_b128(ra, am < c.lim ? off + u * (unsigned)R * 16u : off, 0, 0));
+      }
+  };
+  // staged part planes: set p holds 6 of the wave's units (4 j + w) of a phase p
+  bf16x8 S[4][6];
+  auto load_S = [&](int bx, int p, int j) __attribute__((always_inline)) {
+    const int so = (int)(((int64_t)(p * PU + 4 * j + w) * ld + bx * 64) * 16);
+    S[p][j] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rb, lane * 16, so, 0));
+  };
+  auto write_S = [&](int p, int j) __attribute__((always_inline)) { Bsh[p][4 * j + w][lane] = S[p][j]; };
+  auto barrier = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+  };
+  struct Out {                  // a tile's output block
+    __amdgpu_buffer_rsrc_t r;
+    int64_t stride;
+    unsigned vo;
+  };
+  auto out_of = [&](const SegTile& c, bool none) __attribute__((always_inline)) {
+    const int rows = c.lim - c.rbase < 64 ? c.lim - c.rbase : 64;
+    const TileAt ta = tile_at(packed, M, ld, mon_base, c.rbase, c.bx);
+    return Out{__builtin_amdgcn_make_buffer_rsrc((void*)(G + ta.base), (short)0,
+                                                 none ? 0 : (int)((int64_t)rows * ta.stride * 8), kBufferDword3),
+               ta.stride, (unsigned)((int64_t)lrow * ta.stride + cc) * 8u};
+  };
+  auto row_off = [&](int64_t stride, int e) { return (int)((int64_t)(8 * (e >> 2) + (e & 3)) * stride * 8); };
+  float2 gG[16];
+  struct Acc {
+    f32x16 XR, XI, Z;
+  };
+  auto finish = [&](const Out& o, const Acc& a, int e) __attribute__((always_inline)) {
+    const f32x2 v = {gG[e].x + (a.XR[e] - a.XI[e]), gG[e].y + a.Z[e]};
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), o.r, o.vo, row_off(o.stride, e), 2);
+  };
+  auto load_G = [&](const Out& o, int e) __attribute__((always_inline)) {
+    gG[e] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(o.r, o.vo, row_off(o.stride, e), 2));
+  };
+  bf16x8 br[3], bi[3];
+  auto frag = [&](int p, int gr, int f) __attribute__((always_inline)) {   // operands of group gr = 3 k + j of phase p
+    const int u = 6 * (2 * (gr / 3) + h) + gr % 3;
+    br[f] = Bsh[p][u][cc];
+    bi[f] = Bsh[p][u + 3][cc];
+  };
+  int seg = 0, base = 0;
+  auto advance = [&](const SegTile& c, int i) __attribute__((always_inline)) {   // c: tile i - 1
+    if (i >= cnt) return c;
+    return list.contiguous(i) ? walk.next(c) : walk.seek(list.tile(i), seg, base);
+  };
+  SegTile cur = walk.seek(list.tile(0), seg, base);
+  SegTile nxt = advance(cur, 1);
+  load_A(cur);
+#pragma unroll
+  for (int p = 0; p < 4; ++p)
+#pragma unroll
+    for (int j = 0; j < 6; ++j) load_S(cur.bx, p, j);
+#pragma unroll
+  for (int p = 0; p < 2; ++p)
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+      write_S(p, j);
+      load_S(nxt.bx, p, j);
+    }
+  {
+    const Out o = out_of(cur, false);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) load_G(o, e);
+  }
+  barrier();
+  frag(0, 0, 0);
+  frag(0, 1, 1);
+  auto tile = [&](int t, Acc& a) __attribute__((always_inline)) {
+    const SegTile nn = advance(nxt, t + 2);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) a.XR[e] = a.XI[e] = a.Z[e] = 0.f;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      const int ps = (p + 2) & 3, bxs = p < 2 ? nxt.bx : nn.bx;
+#pragma unroll
+      for (int gr = 0; gr < 6; ++gr) {
+        const int k = 2 * p + gr / 3, j = gr % 3, f = gr % 3;
+#pragma unroll
+        for (int i = 0; i + j < 3; ++i) {
+          // operands two groups ahead with a group's first step, a staged unit with each other
+          if (i == 0) {
+            if (gr < 4) frag(p, gr + 2, (gr + 2) % 3);
+            else frag((p + 1) & 3, gr - 4, (gr + 2) % 3);
+          } else {
+            const int u = 3 * (gr / 3) + 2 * j + i - 1;   // 0..5 over the phase
+            write_S(ps, u);
+            load_S(bxs, ps, u);
+          }
+          const bf16x8 ar = aR[6 * k + i], ai = aR[6 * k + 3 + i];
+          a.XR = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ar, br[f], a.XR, 0, 0, 0);
+          a.Z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ar, bi[f], a.Z, 0, 0, 0);
+          a.XI = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ai, bi[f], a.XI, 0, 0, 0);
+          a.Z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ai, br[f], a.Z, 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      if (p == 3) {
+        const Out out = out_of(cur, false), on = out_of(nxt, false);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) finish(out, a, e);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) load_G(on, e);
+      }
+      barrier();
+    }
+    if (nxt.band != cur.band) {
+      load_A(nxt);
+      __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    }
+    cur = nxt;
+    nxt = nn;
+  };
+  Acc acc;
+  for (int t = 0; t < cnt; ++t) tile(t, acc);
 }
 
 // flush variants for complex64 storage (selected by the autotuner; all give the
@@ -885,8 +1101,6 @@ hipError_t launch_flush(const Geo& g, gfo_state* st, const Layout& L, hipStream_
         break;
       default: {
         const int bound = st->pending_calls;
-        // split products: 17 to 64 terms (the matrix work of up to 16 terms hides
-        // behind the G stream in the pair form); 32-bit offsets into G tiles
         // split products: 17 to 128 terms (the matrix work of up to 16 terms hides
         // behind the G stream in the pair form); 32-bit offsets into G tiles and
         // into the part planes
@@ -897,10 +1111,8 @@ hipError_t launch_flush(const Geo& g, gfo_state* st, const Layout& L, hipStream_
           // 64: 3.5 % more traffic), of 16 beyond (twice the V parts per column)
           const int sw = bound <= 64 ? 32 : 16;
           const int nb = (g.N + 63) / 64;
-          const int nmb = (g.nmon + 63) / 64, nbx = (int)(g.ld / 64);
           bf16x8* a3 = (bf16x8*)(w + L.dl_split);
           bf16x8* v3 = a3 + (size_t)kSplitUnits * g.R;
-          const int T = nb * (nb + 1) / 2 + nmb * nbx;
           const unsigned gx = (unsigned)((nx + 255) / 256);
           auto run = [&](auto kc) {
             constexpr int KC = decltype(kc)::value;
@@ -909,9 +1121,10 @@ hipError_t launch_flush(const Geo& g, gfo_state* st, const Layout& L, hipStream_
             const int P = band_workgroups(KC == 8 ? 1 : 2);
             hipLaunchKernelGGL(k_flush_pack_s3<KC>, dim3(gx, 2 * KC), blk, 0, s, g.R, g.ld, count, cu, vv,
                                a3, v3);
-            hipLaunchKernelGGL(k_flush_c64_s3<KC>, dim3((unsigned)P), blk, 0, s, g.N, g.R, g.ld, count,
-                               (const bf16x8*)a3, (const bf16x8*)v3, G, nb, (T + P - 1) / P, g.packed,
-                               g.mon_base, sw);
+            auto* kernel = k_flush_c64_s3_ring;
+            if constexpr (KC < 8) kernel = k_flush_c64_s3<KC>;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)P), blk, 0, s, g.N, g.R, g.ld, count,
+                               (const bf16x8*)a3, (const bf16x8*)v3, G, nb, g.packed, g.mon_base, sw);
           };
           if (bound <= 32) run(std::integral_constant<int, 2>{});
           else if (bound <= 64) run(std::integral_constant<int, 4>{});
