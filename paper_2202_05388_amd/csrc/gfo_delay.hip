@@ -115,17 +115,6 @@ __device__ __forceinline__ GatherElem gather_elem(const Geo& g) {
   return el;
 }
 
-template <typename T>
-__device__ __forceinline__ T buf_load(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff);
-template <>
-__device__ __forceinline__ float2 buf_load<float2>(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff) {
-  return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, 0));
-}
-template <>
-__device__ __forceinline__ double2 buf_load<double2>(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff) {
-  return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, 0));
-}
-
 template <typename T, int B>
 __device__ __forceinline__ void gather_prefetch_n(const Geo& g, int cnt, const T* __restrict__ CUs,
                                                   const T* __restrict__ Vs, GatherPre<T, B>& pre) {

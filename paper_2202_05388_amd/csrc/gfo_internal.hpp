@@ -186,6 +186,18 @@ __device__ inline int block_min(int v, int* sh) {
   return r;
 }
 
+// One entry through a buffer resource (zero past its range) at byte off + soff.
+template <typename T>
+__device__ __forceinline__ T buf_load(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff);
+template <>
+__device__ __forceinline__ float2 buf_load<float2>(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff) {
+  return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, 0));
+}
+template <>
+__device__ __forceinline__ double2 buf_load<double2>(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff) {
+  return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, 0));
+}
+
 // Snapshot of the accepted move, written before G is modified.
 struct Snap {
   int32_t j;          // pixel, -1 = no move
@@ -323,8 +335,8 @@ __device__ inline void score_block_end(const Geo& g, double best, int p, bool ha
   }
 }
 
-// The greedy pick over scores written one pixel per thread by workgroups of
-// kScoreThreads (workgroup b covered pixels [b * kScoreThreads, ...) and left
+// The greedy pick over scores written by workgroups that covered span_px pixels
+// each (kScoreThreads, one per thread; workgroup b pixels [b * span_px, ...) and left
 // partial[b] and pfirst[b], score_block_end): accept the best score F* only if
 // F* > fom (1 + tau); the winner is the lowest (pixel, material) index whose
 // score is within the relative band tau of F*.  It lies in the lowest workgroup
@@ -336,7 +348,7 @@ __device__ inline gfo_pick greedy_pick_block(const Geo& g, double fom,
                                              const double* __restrict__ scores,
                                              const double* __restrict__ partial,
                                              const int* __restrict__ pfirst, int nblk, double tau,
-                                             double* shd, int* shi) {
+                                             double* shd, int* shi, int span_px = kScoreThreads) {
   gfo_pick pk;
   pk.pixel = -1;
   pk.eps_idx = -1;
@@ -360,7 +372,7 @@ __device__ inline gfo_pick greedy_pick_block(const Geo& g, double fom,
   if (partial[bq] == m && pf != 0x7fffffff) {
     first = pf;
   } else {
-    const int total = g.N * g.n_eps, span = kScoreThreads * g.n_eps;
+    const int total = g.N * g.n_eps, span = span_px * g.n_eps;
     const int lo = bq * span, hi = min(lo + span, total);
     int f = 0x7fffffff;
     for (int i = lo + threadIdx.x; i < hi; i += blockDim.x) {

@@ -28,84 +28,105 @@ __device__ __forceinline__ double2 cdiv(double2 a, double2 b) {
   return make_double2((a.x * b.x + a.y * b.y) / n, (a.y * b.x - a.x * b.y) / n);
 }
 
-// One thread per region (workgroups of kScoreThreads; workgroup w covers regions
-// [256 w, 256 w + 256) and leaves its best score and the lowest index within
-// the tie band of that best).  The in-block entries of G are read from G, plus,
-// in deferred mode, the `count` pending terms cu_s[p] v_s[q]; the diagonal comes
-// from diag64 (FP64).  The 4 x 4 systems are solved in FP64 by Gaussian
-// elimination with partial pivoting.
+// Scores of 16 regions at a time, on 12 x 16 threads.  Thread (w, r) sums one
+// off-diagonal entry (i, j) of the 4 x 4 block of G of region r: the entry read from G,
+// plus, in deferred mode, the `count` pending terms cu_s[p] v_s[q] in term order (the
+// diagonal comes from diag64, FP64); the entries meet in LDS, and thread (e, r) solves
+// the system of material e in FP64 by Gaussian elimination with partial pivoting.
+// Workgroup b covers the regions [16 per b, 16 per (b + 1)) and leaves its best score
+// and the lowest index within the tie band of that best.
+// Bound by the reads of the terms, written by other compute units shortly before, and
+// a compute unit keeps few lines of them in flight, so the regions are spread over all:
+// 4096 regions, 0 to 60 pending terms, 11.1 us (64 regions a workgroup with 12 entry
+// waves 15.9, with a wave per row 15.1; a thread per region, 16 workgroups, 20.8 us).
+constexpr int kRegionLanes = 16;
+constexpr int kRegionWaves = kRegionPix * (kRegionPix - 1);
+constexpr int kRegionThreads = kRegionLanes * kRegionWaves;
+static_assert(kRegionWaves >= GFO_MAX_EPS, "a thread per region and material");
+
 template <typename T>
-__global__ __launch_bounds__(kScoreThreads) void k_score_regions(
+__global__ __launch_bounds__(kRegionThreads) void k_score_regions(
     Geo g, int n_regions, const T* __restrict__ G, const T* __restrict__ E,
     const double2* __restrict__ diag64, const uint8_t* __restrict__ eps_idx,
     const int32_t* __restrict__ count, const T* __restrict__ CUs, const T* __restrict__ Vs,
     uint32_t mask, double tau, double* __restrict__ scores, double* __restrict__ partial,
-    int* __restrict__ pfirst, int32_t* __restrict__ status) {
-  __shared__ double sh[kScoreThreads / 64];
-  __shared__ int shi[kScoreThreads / 64];
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  Geo gr = g;                      // the region index space, for the summaries
-  gr.N = n_regions;
-  double F[GFO_MAX_EPS];
+    int* __restrict__ pfirst, int32_t* __restrict__ status, int per) {
+  __shared__ double sh[kRegionThreads / 64];
+  __shared__ int shi[kRegionThreads / 64];
+  __shared__ double2 Gs[kRegionPix][kRegionPix][kRegionLanes];
+  const int lane = threadIdx.x % kRegionLanes, w = threadIdx.x / kRegionLanes;
+  const int K = count ? __builtin_amdgcn_readfirstlane(*count) : 0;
+  const T* __restrict__ grow = G + g_off(g, g.N + g.m0, 0);
+  const double2 Em0 = St<T>::to_d(E[g.N + g.m0]);
   double best = -INFINITY;
   bool bad = false;
-  if (k < n_regions) {
+  for (int c = 0; c < per; ++c) {
+    const int k = ((int)blockIdx.x * per + c) * kRegionLanes + lane;
+    const bool live = k < n_regions;
     int V[kRegionPix];
-    region_pixels(g, k, V);
-    double2 Gvv[kRegionPix][kRegionPix], EV[kRegionPix], gm[kRegionPix];
+    region_pixels(g, live ? k : 0, V);
+    if (c > 0) __syncthreads();   // the previous regions' blocks have been read
+    {
+      // the thread's entry (i, j), and the pixels V[i], V[j] without a register index
+      const int i = w / (kRegionPix - 1), r = w - i * (kRegionPix - 1), j = r + (r >= i ? 1 : 0);
+      const int Vi = V[0] + i / kRegion * g.nx + i % kRegion, Vj = V[0] + j / kRegion * g.nx + j % kRegion;
+      const T g0 = G[g_at(g, Vi, Vj)];
+      const double2 di = diag64[Vi];
+      // terms in batches whose loads are in flight together, through buffers whose
+      // ranges end at the count: slots past it read as zero and add zero
+      constexpr int kBatch = 256 / (int)sizeof(T);
+      const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
+          (void*)CUs, (short)0, (int)(K * (int64_t)g.R * (int64_t)sizeof(T)), 0x00020000);
+      const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(
+          (void*)Vs, (short)0, (int)(K * g.ld * (int64_t)sizeof(T)), 0x00020000);
+      const unsigned ci = (unsigned)Vi * (unsigned)sizeof(T), vj = (unsigned)Vj * (unsigned)sizeof(T);
+      double2 sum = make_double2(0.0, 0.0);
+      for (int s0 = 0; s0 < K; s0 += kBatch) {
+        T cu[kBatch], v[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+          cu[u] = buf_load<T>(rc, ci, (unsigned)(s0 + u) * (unsigned)g.R * (unsigned)sizeof(T));
+          v[u] = buf_load<T>(rv, vj, (unsigned)(s0 + u) * (unsigned)g.ld * (unsigned)sizeof(T));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (s0 == 0) sum = St<T>::to_d(g0);
+#pragma unroll
+        for (int u0 = 0; u0 < kBatch; u0 += 4) {
+          if (s0 + u0 < K) {
+#pragma unroll
+            for (int u = u0; u < u0 + 4; ++u) sum = cadd(sum, cmul(St<T>::to_d(cu[u]), St<T>::to_d(v[u])));
+          }
+        }
+      }
+      if (K <= 0) sum = St<T>::to_d(g0);
+      Gs[i][j][lane] = sum;
+      if (r == 0) Gs[i][i][lane] = di;
+    }
     int cur[kRegionPix];
-    const T* __restrict__ grow = G + g_off(g, g.N + g.m0, 0);
+    double2 EV[kRegionPix], gm[kRegionPix];
 #pragma unroll
     for (int i = 0; i < kRegionPix; ++i) {
       cur[i] = eps_idx[V[i]];
       EV[i] = St<T>::to_d(E[V[i]]);
       gm[i] = St<T>::to_d(grow[V[i]]);
-#pragma unroll
-      for (int j = 0; j < kRegionPix; ++j)
-        Gvv[i][j] = i == j ? diag64[V[i]] : St<T>::to_d(G[g_at(g, V[i], V[j])]);
     }
-    const int K = count ? *count : 0;
-    // terms in groups of kTermBatch: every load of a group is issued before its
-    // first use (each term is an L2 round trip), the sums in term order
-    constexpr int kTermBatch = 4;
-    for (int s0 = 0; s0 < K; s0 += kTermBatch) {
-      T cuw[kTermBatch][kRegionPix], vw[kTermBatch][kRegionPix];
-#pragma unroll
-      for (int u = 0; u < kTermBatch; ++u)
-#pragma unroll
-        for (int i = 0; i < kRegionPix; ++i)
-          if (s0 + u < K) {
-            cuw[u][i] = CUs[(int64_t)(s0 + u) * g.R + V[i]];
-            vw[u][i] = Vs[(int64_t)(s0 + u) * g.ld + V[i]];
-          }
-#pragma unroll
-      for (int u = 0; u < kTermBatch; ++u) {
-        if (s0 + u >= K) break;
-        double2 cu[kRegionPix], v[kRegionPix];
-#pragma unroll
-        for (int i = 0; i < kRegionPix; ++i) {
-          cu[i] = St<T>::to_d(cuw[u][i]);
-          v[i] = St<T>::to_d(vw[u][i]);
-        }
-#pragma unroll
-        for (int i = 0; i < kRegionPix; ++i)
-#pragma unroll
-          for (int j = 0; j < kRegionPix; ++j)
-            if (i != j) Gvv[i][j] = cadd(Gvv[i][j], cmul(cu[i], v[j]));
-      }
-    }
-    const double2 Em0 = St<T>::to_d(E[g.N + g.m0]);
-#pragma unroll
-    for (int e = 0; e < GFO_MAX_EPS; ++e) {
-      if (e >= g.n_eps) continue;
+    __syncthreads();
+    if (w < g.n_eps) {
+      const int e = w;
       double Fe = -INFINITY;
       bool changes = false;
 #pragma unroll
       for (int i = 0; i < kRegionPix; ++i) changes |= cur[i] != e;
-      if (((mask >> e) & 1u) && changes) {
+      if (live && ((mask >> e) & 1u) && changes) {
+        const double eps_new = eps_of(g, e);
         double b[kRegionPix];
 #pragma unroll
-        for (int i = 0; i < kRegionPix; ++i) b[i] = g.k0sq * (g.eps[e] - g.eps[cur[i]]);
+        for (int i = 0; i < kRegionPix; ++i) b[i] = g.k0sq * (eps_new - eps_of(g, cur[i]));
+        double2 Gvv[kRegionPix][kRegionPix];
+#pragma unroll
+        for (int i = 0; i < kRegionPix; ++i)
+#pragma unroll
+          for (int j = 0; j < kRegionPix; ++j) Gvv[i][j] = Gs[i][j][lane];
         // A = I - G_VV B, augmented with E_V
         double2 A[kRegionPix][kRegionPix + 1];
 #pragma unroll
@@ -166,29 +187,48 @@ __global__ __launch_bounds__(kScoreThreads) void k_score_regions(
         }
         best = fmax(best, Fe);
       }
-      F[e] = Fe;
-      scores[(int64_t)k * g.n_eps + e] = Fe;
+      if (live) scores[(int64_t)k * g.n_eps + e] = Fe;
     }
   }
-  score_block_end(gr, best, k, true, F, tau, partial, pfirst, (n_regions + kScoreThreads - 1) / kScoreThreads,
-                  sh, shi);
+  const double bb = block_max(best, sh);
+  int f = 0x7fffffff;
+  if (bb > -INFINITY) {
+    // the thread's own scores again (its own stores)
+    const double thr = tie_threshold(bb, tau);
+    for (int c = 0; c < per; ++c) {
+      const int k = ((int)blockIdx.x * per + c) * kRegionLanes + lane;
+      if (w < g.n_eps && k < n_regions && scores[(int64_t)k * g.n_eps + w] >= thr) f = min(f, k * g.n_eps + w);
+    }
+  }
+  f = block_min(f, shi);
+  if (threadIdx.x == 0) {
+    partial[blockIdx.x] = bb;
+    pfirst[blockIdx.x] = f;
+  }
   if (bad) atomicOr(status, GFO_STATUS_NONFINITE);
 }
 
-// The greedy pick over the region scores (one wave); FOM from E at the monitor.
+// Regions per workgroup of the scores, in 16s: one, or what keeps the workgroups
+// within the summaries (more than 16384 regions).
+static int region_span(int n_regions) {
+  const int n = (n_regions + kRegionLanes - 1) / kRegionLanes;
+  return (n + kScoreMaxBlocks - 1) / kScoreMaxBlocks;
+}
+
+// The greedy pick over the region scores (one workgroup); FOM from E at the monitor.
 template <typename T>
-__global__ __launch_bounds__(64) void k_region_pick(Geo g, int n_regions, const T* __restrict__ E,
+__global__ __launch_bounds__(256) void k_region_pick(Geo g, int n_regions, const T* __restrict__ E,
                                                     const double* __restrict__ scores,
                                                     const double* __restrict__ partial,
                                                     const int* __restrict__ pfirst, double tau,
-                                                    gfo_pick* __restrict__ out) {
-  __shared__ double shd[1];
-  __shared__ int shi[1];
+                                                    gfo_pick* __restrict__ out, int per) {
+  __shared__ double shd[4];
+  __shared__ int shi[4];
   Geo gr = g;
   gr.N = n_regions;
   const double fom = cabs2(St<T>::to_d(E[g.N + g.m0]));
-  const int nblk = (n_regions + kScoreThreads - 1) / kScoreThreads;
-  const gfo_pick pk = greedy_pick_block(gr, fom, scores, partial, pfirst, nblk, tau, shd, shi);
+  const int span = kRegionLanes * per, nblk = (n_regions + span - 1) / span;
+  const gfo_pick pk = greedy_pick_block(gr, fom, scores, partial, pfirst, nblk, tau, shd, shi, span);
   if (threadIdx.x == 0) *out = pk;
 }
 
@@ -223,27 +263,28 @@ hipError_t launch_score_regions(const Geo& g, const gfo_state* st, const Layout&
                                 double tau, gfo_pick* out, hipStream_t s) {
   char* w = (char*)st->work;
   const int n_regions = (g.ny / kRegion) * (g.nx / kRegion);
-  const int nblk = (n_regions + kScoreThreads - 1) / kScoreThreads;
+  const int per = region_span(n_regions);
+  const int nblk = (n_regions + kRegionLanes * per - 1) / (kRegionLanes * per);
   const int32_t* count = st->delay > 0 ? (const int32_t*)(w + L.dl_hdr) : nullptr;
   double* scores = (double*)(w + L.scores);
   double* partial = (double*)(w + L.partial);
   int* pfirst = (int*)(w + L.pfirst);
   if (g.dtype == GFO_C64) {
-    hipLaunchKernelGGL(k_score_regions<float2>, dim3(nblk), dim3(kScoreThreads), 0, s, g, n_regions,
+    hipLaunchKernelGGL(k_score_regions<float2>, dim3(nblk), dim3(kRegionThreads), 0, s, g, n_regions,
                        (const float2*)st->G, (const float2*)st->E, (const double2*)st->diag64,
                        (const uint8_t*)st->eps_idx, count, (const float2*)(w + L.dl_CUs),
-                       (const float2*)(w + L.dl_Vs), mask, tau, scores, partial, pfirst, st->status);
-    hipLaunchKernelGGL(k_region_pick<float2>, dim3(1), dim3(64), 0, s, g, n_regions,
+                       (const float2*)(w + L.dl_Vs), mask, tau, scores, partial, pfirst, st->status, per);
+    hipLaunchKernelGGL(k_region_pick<float2>, dim3(1), dim3(256), 0, s, g, n_regions,
                        (const float2*)st->E, (const double*)scores, (const double*)partial,
-                       (const int*)pfirst, tau, out);
+                       (const int*)pfirst, tau, out, per);
   } else {
-    hipLaunchKernelGGL(k_score_regions<double2>, dim3(nblk), dim3(kScoreThreads), 0, s, g, n_regions,
+    hipLaunchKernelGGL(k_score_regions<double2>, dim3(nblk), dim3(kRegionThreads), 0, s, g, n_regions,
                        (const double2*)st->G, (const double2*)st->E, (const double2*)st->diag64,
                        (const uint8_t*)st->eps_idx, count, (const double2*)(w + L.dl_CUs),
-                       (const double2*)(w + L.dl_Vs), mask, tau, scores, partial, pfirst, st->status);
-    hipLaunchKernelGGL(k_region_pick<double2>, dim3(1), dim3(64), 0, s, g, n_regions,
+                       (const double2*)(w + L.dl_Vs), mask, tau, scores, partial, pfirst, st->status, per);
+    hipLaunchKernelGGL(k_region_pick<double2>, dim3(1), dim3(256), 0, s, g, n_regions,
                        (const double2*)st->E, (const double*)scores, (const double*)partial,
-                       (const int*)pfirst, tau, out);
+                       (const int*)pfirst, tau, out, per);
   }
   return note_hip(hipGetLastError());
 }
