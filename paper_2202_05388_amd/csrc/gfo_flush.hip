@@ -281,6 +281,8 @@ __global__ __launch_bounds__(256) void k_flush_c64_pair(int M, int R, int64_t ld
 
 
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // Position of a persistent flush run in the tile list in column segments of sw
 // tiles (segment j: columns [sw j, sw j + sw)); inside a segment the triangle's
@@ -1037,6 +1039,166 @@ __global__ __launch_bounds__(256, 1) void k_flush_c64_s3_ring(int M, int R, int6
   for (int t = 0; t < cnt; ++t) tile(t, acc);
 }
 
+// The flush of complex128 storage, persistent, FP64 matrix cores: G += CU V^T on the
+// tiles on and above the design block's diagonal and the monitor rows, two workgroups
+// per compute unit.  An XCD's workgroups take consecutive tiles of a column segment at
+// a time, 16 bands' A terms and 16 tiles' B terms being all that its L2 has to hold.  A
+// wave takes 32 x 32 of a
+// 64 x 64 tile as 2 x 2 v_mfma_f64_16x16x4 tiles (operand layout as in k_zgemm_f64, and
+// per entry the same instructions in the same order, so the same bits).
+//   - Both operands go through a ring of four LDS slots, one phase of 8 terms each: in
+//     phase p the terms of phase p + 2 go from registers into their slot and the
+//     registers are loaded again with those of p + 4, past the end of a tile with the
+//     next tile's.  One barrier per two phases.  Slots past the count read as zero
+//     through the buffers' ranges and take no matrix steps.
+//   - G(t+1) is read into registers after tile t's entries are stored, a tile ahead.
+// Bound by the FP64 matrix cores (64 cycles per step; 0.98 ms at the 2.16 GHz this load
+// leaves) at 64 terms, by the stream of G at few: 128 x 128, 2.15 GB of G, 1.29 ms at 64
+// terms and 0.86 at 17; the tiled product of k_zgemm_f64, four waves per SIMD without
+// LDS, 1.45 and 0.86 (32 x 32 at 48 terms 16 and 25 us, 21 x 21 at 16 8.3 and 14.7).
+// Each workgroup on a stretch of 16-tile rows of its own: 36 instead of 20 million
+// reads from HBM, 1.33 ms; a barrier per phase: 1.32 ms.
+__global__ __launch_bounds__(256, 2) void k_flush_c128(int M, int R, int64_t ld, const int32_t* __restrict__ count,
+                                                       const double2* __restrict__ CU,
+                                                       const double2* __restrict__ V, double2* __restrict__ G,
+                                                       int nby, int packed, int64_t mon_base, int sw) {
+  constexpr int kPh = 8;                        // terms of a phase
+  const int K = *count;
+  if (K == 0) return;
+  const SegWalk walk{M, R, nby, (int)(ld / 64), (R - M + 63) / 64, sw};
+  const int T = nby * (nby + 1) / 2 + walk.nmb * walk.nbx;
+  const RunList list((int)gridDim.x, (int)blockIdx.x, T, 1);
+  const int cnt = list.count();
+  if (cnt <= 0) return;
+  __shared__ double2 As[4][kPh][64], Bs[4][kPh][64];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int li = lane & 15, lk = lane >> 4;
+  const int wm = (w >> 1) * 32, wn = (w & 1) * 32;
+  const __amdgpu_buffer_rsrc_t ra =
+      __builtin_amdgcn_make_buffer_rsrc((void*)CU, (short)0, (int)((int64_t)K * R * 16), kBufferDword3);
+  const __amdgpu_buffer_rsrc_t rb =
+      __builtin_amdgcn_make_buffer_rsrc((void*)V, (short)0, (int)((int64_t)K * ld * 16), kBufferDword3);
+  // staged terms of a phase: k = w + 4 i, row or column `lane` of the tile
+  double2 pa[2][2], pb[2][2];
+  auto load = [&](const SegTile& c, int ch, int set) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const unsigned k = (unsigned)(kPh * ch + w + 4 * i);
+      pa[set][i] = buf_load<double2>(ra, lane * 16u, (k * (unsigned)R + (unsigned)c.rbase) * 16u);
+      pb[set][i] = buf_load<double2>(rb, lane * 16u, (k * (unsigned)ld + 64u * (unsigned)c.bx) * 16u);
+    }
+  };
+  auto store = [&](int slot, int set) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      As[slot][w + 4 * i][lane] = pa[set][i];
+      Bs[slot][w + 4 * i][lane] = pb[set][i];
+    }
+  };
+  auto barrier = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+  };
+  struct Out {                  // a tile's output block
+    __amdgpu_buffer_rsrc_t r;
+    int64_t stride;
+    unsigned vo;
+  };
+  auto out_of = [&](const SegTile& c) __attribute__((always_inline)) {
+    const int rows = c.lim - c.rbase < 64 ? c.lim - c.rbase : 64;
+    const TileAt ta = tile_at(packed, M, ld, mon_base, c.rbase, c.bx);
+    return Out{__builtin_amdgcn_make_buffer_rsrc((void*)(G + ta.base), (short)0,
+                                                 (int)((int64_t)rows * ta.stride * 16), kBufferDword3),
+               ta.stride, (unsigned)((int64_t)(wm + lk) * ta.stride + wn + li) * 16u};
+  };
+  auto entry = [&](const Out& o, int t, int u, int e) { return (unsigned)((16 * t + 4 * e) * o.stride + 16 * u) * 16u; };
+  double2 fa[2][2], fb[2][2];   // a step's operands, two sets
+  auto frag = [&](int slot, int st, int f) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) fa[f][t] = As[slot][4 * st + lk][wm + 16 * t + li];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) fb[f][u] = Bs[slot][4 * st + lk][wn + 16 * u + li];
+  };
+  double2 gG[2][2][4];
+  auto load_G = [&](const Out& o) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+          gG[t][u][e] = __builtin_bit_cast(
+              double2, __builtin_amdgcn_raw_buffer_load_b128(o.r, o.vo, entry(o, t, u, e), 2));
+  };
+  int seg = 0, base = 0;
+  auto advance = [&](const SegTile& c, int i) __attribute__((always_inline)) {   // c: tile i - 1
+    if (i >= cnt) return c;
+    return list.contiguous(i) ? walk.next(c) : walk.seek(list.tile(i), seg, base);
+  };
+  SegTile cur = walk.seek(list.tile(0), seg, base);
+  load(cur, 0, 0);
+  load(cur, 1, 1);
+  store(0, 0);
+  load(cur, 2, 0);
+  store(1, 1);
+  load(cur, 3, 1);
+  Out out = out_of(cur);
+  load_G(out);
+  barrier();
+  const int nq = (K + 4 * kPh - 1) / (4 * kPh);   // rounds of four phases
+  for (int tile = 0; tile < cnt; ++tile) {
+    const SegTile nxt = advance(cur, tile + 1);
+    f64x4 X[2][2], Y[2][2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) X[t][u] = Y[t][u] = (f64x4){0.0, 0.0, 0.0, 0.0};
+    for (int q = 0; q < nq; ++q) {
+      const bool last = q + 1 == nq;
+      const SegTile src = last ? nxt : cur;
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        store((p + 2) & 3, p & 1);
+        load(src, last ? p : 4 * (q + 1) + p, p & 1);
+        if ((p & 1) == 0) frag(p, 0, 0);
+#pragma unroll
+        for (int st = 0; st < 2; ++st) {
+          // operands a step ahead, except across a barrier
+          if (st == 0) frag(p, 1, 1);
+          else if ((p & 1) == 0) frag(p + 1, 0, 0);
+          if (kPh * (4 * q + p) + 4 * st < K) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+              for (int u = 0; u < 2; ++u) {
+                const double2 a = fa[st][t], b = fb[st][u];
+                X[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, X[t][u], 0, 0, 0);
+                X[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.y, X[t][u], 0, 0, 0);
+                Y[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, Y[t][u], 0, 0, 0);
+                Y[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.x, Y[t][u], 0, 0, 0);
+              }
+          }
+        }
+        if (p & 1) barrier();
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const double2 o = cadd(gG[t][u][e], make_double2(X[t][u][e], Y[t][u][e]));
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), out.r, out.vo, entry(out, t, u, e), 2);
+        }
+    __builtin_amdgcn_sched_barrier(0);
+    out = out_of(nxt);
+    load_G(out);
+    cur = nxt;
+  }
+}
+
 // flush variants for complex64 storage (selected by the autotuner; all give the
 // eager results to FP32 rounding, tests/test_gpu_deferred.py).  The default,
 // up_bandseg_s3: the split-product band flush for 17 to 64 terms, the pair
@@ -1202,8 +1364,20 @@ hipError_t launch_flush(const Geo& g, gfo_state* st, const Layout& L, hipStream_
     }
   } else {
     if (hipError_t er = record_event(before, s)) return note_hip(er);
-    e = launch_zgemm_update_f64(g, count, (const double2*)(w + L.dl_CUs),
-                                (const double2*)(w + L.dl_Vs), (double2*)st->G, s);
+    // 32-bit offsets into the term buffers and the G tiles; beyond (a million rows) the
+    // tiled product, which addresses each entry in full
+    const int64_t nx = g.R > g.ld ? (int64_t)g.R : g.ld;
+    if ((int64_t)GFO_MAX_DELAY * nx * 16 < ((int64_t)1 << 31)) {
+      constexpr int kSegTiles = 16;
+      const int nb = (g.N + 63) / 64;
+      hipLaunchKernelGGL(k_flush_c128, dim3((unsigned)band_workgroups(2)), dim3(256), 0, s, g.N, g.R, g.ld, count,
+                         (const double2*)(w + L.dl_CUs), (const double2*)(w + L.dl_Vs), (double2*)st->G, nb, g.packed,
+                         g.mon_base, kSegTiles);
+      e = note_hip(hipGetLastError());
+    } else {
+      e = launch_zgemm_update_f64(g, count, (const double2*)(w + L.dl_CUs), (const double2*)(w + L.dl_Vs),
+                                  (double2*)st->G, s);
+    }
     if (e == hipSuccess) e = record_event(after, s);
     if (e != hipSuccess) return note_hip(e);
     st->lower_stale = 1;

@@ -52,3 +52,30 @@ def test_rounds_equal_pair_flush(ny, nx, n_mon, steps, delay, packed):
             x, y = torch.where(keep, x, 0), torch.where(keep, y, 0)
         assert float((x - y).abs().max()) <= tol * float(x.abs().max()), r
     assert (jobs[0].history() == jobs[1].history()).all()
+
+
+@pytest.mark.parametrize("ny,nx,n_mon,steps,delay,packed", [
+    (7, 9, 1, 1, 16, False), (7, 9, 70, 8, 16, False), (8, 8, 64, 9, 64, True), (16, 20, 65, 31, 64, True),
+    (24, 26, 3, 32, 64, False), (30, 34, 130, 33, 64, False), (64, 64, 2, 64, 128, True),
+    (63, 65, 2, 65, 128, False), (96, 97, 70, 100, 128, True)])
+def test_c128_flush_equals_eager(ny, nx, n_mon, steps, delay, packed):
+    """complex128: the counts around the phases of 8 terms and the rounds of 32, one
+    tile to several rounds of tiles per workgroup, ragged bands, one to three monitor
+    bands.  Tolerance: K terms summed in FP64, each off by a few u of the largest entry,
+    on either side: 8 K u, u = 2^-53."""
+    import numpy as np
+    from paper_2202_05388_amd.job import Job
+    from parity import rel_elem
+    p = W.tiny(ny, nx, n_mon=n_mon, dtype="c128", cand_mask=W.MASK_BOTH, tau=1e-9)
+    print(f"[case] c128 {ny}x{nx} n_mon {n_mon}: {steps} moves, packed {packed}", flush=True)
+    a = Job(p, device="cuda:0")
+    a.init()
+    a.run_greedy(steps, poll_every=steps)
+    b = Job(p, device="cuda:0", delay=delay, packed=packed)
+    b.init()
+    b.run_greedy(steps, poll_every=steps)
+    assert b.state.pending_calls == steps or delay == steps
+    Gb, Eb, db, ib = b.host_state()
+    Ga, Ea, da, ia = a.host_state()
+    assert np.array_equal(ia, ib) and np.array_equal(a.history(), b.history())
+    assert rel_elem(Gb, Ga, floor=1.0) <= 8 * steps * 2.0 ** -53
