@@ -487,13 +487,18 @@ __global__ __launch_bounds__(256) void k_gj_update(int kp, int n_cols, int lds, 
 // An epilogue prepares a thread's rows and columns once (row, col) and then takes
 // each entry: a G0 entry needs the grid coordinates of both pixels, and four integer
 // divisions per entry were a sixth of the refresh product's time at 180 flipped
-// pixels.
+// pixels.  The rows from inner_rows on may each take a path of their own; for those
+// before it, `pre` reads what an entry needs and `put` finishes it, without a branch.
 struct EpiStoreZ {
   double2* Z;
   int64_t ldz;
   __device__ int64_t row(int m) const { return m * ldz; }
+  __device__ int64_t inner_row(int m) const { return m * ldz; }
   __device__ int col(int n) const { return n; }
   __device__ void operator()(int64_t r, int n, double2 v) const { Z[r + n] = v; }
+  __device__ int inner_rows(int M) const { return M; }
+  __device__ double2 pre(int64_t, int) const { return make_double2(0.0, 0.0); }
+  __device__ void put(int64_t r, int n, bool, double2, double2 v) const { Z[r + n] = v; }
 };
 
 template <typename T>
@@ -503,6 +508,7 @@ struct EpiG0 {
   const double* mon_xy;
   T* G;
   double2* diag64;
+  float inv_nx;         // 1 / nx
   struct Pixel {
     int p, iy, ix;
   };
@@ -510,9 +516,15 @@ struct EpiG0 {
     Pixel at;
     int64_t base;       // offset of column 0 (packed: of the column before the band's first by 64 b)
   };
+  // p / nx and the rest: the quotient from a product that is off by one at most for
+  // p < 2^24, put right (an integer division is 25 instructions, and nothing of them
+  // overlaps the FP64 matrix steps of the other waves)
   __device__ Pixel pixel(int p) const {
-    const int iy = p / g.nx;
-    return Pixel{p, iy, p - iy * g.nx};
+    int iy = (int)((float)p * inv_nx);
+    int ix = p - iy * g.nx;
+    iy += (ix >= g.nx) - (ix < 0);
+    ix += ix < 0 ? g.nx : ix >= g.nx ? -g.nx : 0;
+    return Pixel{p, iy, ix};
   }
   __device__ RowAt row(int m) const {
     if (m >= g.N) return RowAt{Pixel{m, 0, 0}, g_mon(g, m - g.N, 0)};
@@ -528,9 +540,18 @@ struct EpiG0 {
     } else {
       g0 = g0_entry(g, table, mon_xy, r.at.p, c.p);
     }
+    put(r, c, true, g0, v);
+  }
+  // the design rows, whose G0 is the table's
+  __device__ int inner_rows(int) const { return g.N; }
+  __device__ RowAt inner_row(int m) const { return RowAt{pixel(m), g_off(g, m, m & ~63) - (m & ~63)}; }
+  __device__ double2 pre(const RowAt& r, const Pixel& c) const {
+    return table[abs(r.at.iy - c.iy) * g.nx + abs(r.at.ix - c.ix)];
+  }
+  __device__ void put(const RowAt& r, const Pixel& c, bool diag, double2 g0, double2 v) const {
     const double2 val = make_double2(g0.x + v.x, g0.y + v.y);
     G[r.base + c.p] = St<T>::from_d(val);
-    if (diag64 != nullptr && r.at.p == c.p) diag64[c.p] = val;
+    if (diag && diag64 != nullptr && r.at.p == c.p) diag64[c.p] = val;
   }
 };
 
@@ -639,11 +660,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 // long double, 70 to 900 flipped pixels), so it is taken where the result is
 // rounded to FP32, which hides both: complex64 storage, whose FP64 diagonal
 // k_rf_field computes with four.  The whole refresh at 128 x 128, 180 flipped
-// pixels: M3 on 64 x 64 tiles (2 x 2 per wave, 162 registers, three workgroups per
-// compute unit whose epilogues overlap other products) 3.95 ms, M3 on 128 x 64 4.23,
-// four products on 64 x 64 4.50, on 128 x 64 4.60, on 128 x 128 4.74.  complex128,
-// 96 x 131, 1509 flipped: 128 x 64 tiles (4 x 2 per wave) 29.3, 64 x 64 29.4, 128 x
-// 128 29.5 ms.
+// pixels, with one epilogue for all rows: M3 on 64 x 64 tiles (2 x 2 per wave, 162
+// registers, three workgroups per compute unit whose epilogues overlap other
+// products) 3.95 ms, M3 on 128 x 64 4.23, four products on 64 x 64 4.50, on 128 x 64
+// 4.60, on 128 x 128 4.74.  complex128, 96 x 131, 1509 flipped: 128 x 64 tiles (4 x 2
+// per wave) 29.3, 64 x 64 29.4, 128 x 128 29.5 ms.
+//
+// A FP64 matrix step shares its unit with the vector instructions, so what the loads
+// and the epilogue take is added to the product.  The product alone at those two
+// sizes: 3.10 and 15.85 ms with a test of row and k per load and, in the epilogue, a
+// branch per entry between the table and the monitors' Bessel functions (each entry's
+// read waited for by itself); 2.86 and 15.0 with the loads through buffers, 2.80 and
+// 14.4 with the branch once per tile (2.03 and 13.3 for the matrix steps).
 //
 // Without M3 every accumulator takes the same instructions on the same operands in
 // the same order as in k_zgemm_f64, whatever the tile, and the epilogue covers the
@@ -651,17 +679,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 // skip_below are left alone), so the results are bitwise equal.
 constexpr int kZgT = 128, kZgKC = 8;
 
-template <bool AT, bool BT, bool M3, int GM, int GN, int TM, int TU, typename Epi>
+template <bool BT, bool M3, int GM, int GN, int TM, int TU, typename Epi>
 __global__ __launch_bounds__(GM * GN / (4 * TM * TU), 2) void k_zgemm_f64_lds(int M, int N, int K, const double2* __restrict__ A,
                                                        int64_t lda, const double2* __restrict__ B,
-                                                       int64_t ldb, const int32_t* __restrict__ kdev,
-                                                       Epi epi, int skip_below) {
+                                                       int64_t ldb, Epi epi, int skip_below) {
   int by = (int)blockIdx.y, bx = (int)blockIdx.x;
   // (the last tiles first: the monitor rows' are the longest, their G0 entries being evaluated)
   if (skip_below > 0)
     ut_group(gridDim.x - 1 - blockIdx.x, (N + GN - 1) / GN, skip_below / GM, GM, GN, by, bx);
   constexpr int NT = GM * GN / (4 * TM * TU), EA = GM * kZgKC / NT, EB = GN * kZgKC / NT;   // threads, elements each stages
-  __shared__ double2 As[2][kZgKC][GM + 1], Bs[2][kZgKC][GN + 1];   // one pad entry per k row
+  // two pad entries per k row: a staging store's 8 k and 2 rows fall on different banks
+  __shared__ double2 As[2][kZgKC][GM + 2], Bs[2][kZgKC][GN + 2];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int tm0 = by * GM, tn0 = bx * GN;
   constexpr int WN = GN / (16 * TU);                // waves across
@@ -671,7 +699,6 @@ __global__ __launch_bounds__(GM * GN / (4 * TM * TU), 2) void k_zgemm_f64_lds(in
   static_assert(TM <= 4 && TU <= 4, "a wave's outputs lie in one 64 x 64 tile");
   const int ty = (tm0 + wm) >> 6, tx = (tn0 + wn) >> 6;
   const bool idle = skip_below > 0 && ty > tx && ((int64_t)ty + 1) * 64 <= skip_below;
-  if (kdev != nullptr) K = min(K, *kdev);
   // X, Y: re and im, or with M3 sum Ar Br and sum Ai Bi; S: sum (Ar + Ai)(Br + Bi)
   f64x4 X[TM][TU], Y[TM][TU], S[M3 ? TM : 1][M3 ? TU : 1];
 #pragma unroll
@@ -682,46 +709,39 @@ __global__ __launch_bounds__(GM * GN / (4 * TM * TU), 2) void k_zgemm_f64_lds(in
       if constexpr (M3) S[t][u] = (f64x4){0.0, 0.0, 0.0, 0.0};
     }
   // staging: thread tid moves elements tid, tid + NT, ... of each operand's chunk,
-  // consecutive threads along the operand's contiguous index
-  auto a_pos = [](int e, int& r, int& kk) {
-    if (AT) { r = e & (GM - 1); kk = e / GM; } else { r = e >> 3; kk = e & 7; }
-  };
-  auto b_pos = [](int e, int& c, int& kk) {
-    if (BT) { c = e >> 3; kk = e & 7; } else { c = e & (GN - 1); kk = e / GN; }
-  };
+  // consecutive threads along the operand's contiguous index, through buffers that end
+  // at the operand's last row, so that a load costs one scalar addition.  (A last chunk
+  // of four k reads on into the next row where k is contiguous; its second step is
+  // left out.)
+  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(A + tm0 * lda), (short)0, (int)(min(GM, M - tm0) * lda * 16), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rbt = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(B + tn0 * ldb), (short)0, (int)(min(GN, N - tn0) * ldb * 16), 0x00020000);
+  const int ar = tid >> 3, ak = tid & 7, bc = BT ? tid >> 3 : tid & (GN - 1), bk = BT ? tid & 7 : tid / GN;
+  const unsigned va = (unsigned)((ar * lda + ak) * 16);
+  const unsigned vb = (unsigned)((BT ? bc * ldb + bk : bk * ldb + bc) * 16);
+  static_assert(NT % 8 == 0 && NT % GN == 0, "whole rows per staging round");
   double2 pa[EA], pb[EB];
   auto load = [&](int k0) {
 #pragma unroll
-    for (int i = 0; i < EA; ++i) {
-      int r, ka;
-      a_pos(tid + NT * i, r, ka);
-      const int row = tm0 + r;
-      ka += k0;
-      pa[i] = row < M && ka < K ? (AT ? A[(int64_t)ka * lda + row] : A[(int64_t)row * lda + ka])
-                                : make_double2(0.0, 0.0);
-    }
+    for (int i = 0; i < EA; ++i) pa[i] = buf_load<double2>(ra, va, (unsigned)((i * (NT / 8) * lda + k0) * 16));
+    if constexpr (BT) {
 #pragma unroll
-    for (int i = 0; i < EB; ++i) {
-      int c, kb;
-      b_pos(tid + NT * i, c, kb);
-      const int col = tn0 + c;
-      kb += k0;
-      pb[i] = col < N && kb < K ? (BT ? B[(int64_t)col * ldb + kb] : B[(int64_t)kb * ldb + col])
-                                : make_double2(0.0, 0.0);
+      for (int i = 0; i < EB; ++i) pb[i] = buf_load<double2>(rbt, vb, (unsigned)((i * (NT / 8) * ldb + k0) * 16));
+    } else {
+      const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
+          (void*)(B + k0 * ldb + tn0), (short)0, (int)((min(kZgKC, K - k0) * ldb - tn0) * 16), 0x00020000);
+#pragma unroll
+      for (int i = 0; i < EB; ++i) pb[i] = buf_load<double2>(rb, vb, (unsigned)(i * (NT / GN) * ldb * 16));
     }
   };
   auto store = [&](int buf) {
 #pragma unroll
-    for (int i = 0; i < EA; ++i) {
-      int r, ka;
-      a_pos(tid + NT * i, r, ka);
-      As[buf][ka][r] = pa[i];
-    }
+    for (int i = 0; i < EA; ++i) As[buf][ak][ar + i * (NT / 8)] = pa[i];
 #pragma unroll
     for (int i = 0; i < EB; ++i) {
-      int c, kb;
-      b_pos(tid + NT * i, c, kb);
-      Bs[buf][kb][c] = pb[i];
+      if (BT) Bs[buf][bk][bc + i * (NT / 8)] = pb[i];
+      else Bs[buf][bk + i * (NT / GN)][bc] = pb[i];
     }
   };
   const int nch = (K + kZgKC - 1) / kZgKC;
@@ -762,22 +782,46 @@ __global__ __launch_bounds__(GM * GN / (4 * TM * TU), 2) void k_zgemm_f64_lds(in
     __syncthreads();
   }
   if (idle) return;
+  auto entry = [&](int t, int u, int e) __attribute__((always_inline)) {
+    if constexpr (M3) return make_double2(X[t][u][e] - Y[t][u][e], S[t][u][e] - X[t][u][e] - Y[t][u][e]);
+    else return make_double2(X[t][u][e], Y[t][u][e]);
+  };
+  decltype(epi.col(0)) ca[TU];
 #pragma unroll
-  for (int u = 0; u < TU; ++u) {
-    const int col = tn0 + wn + 16 * u + li;
-    if (col >= N) continue;
-    const auto ca = epi.col(col);
+  for (int u = 0; u < TU; ++u) ca[u] = epi.col(tn0 + wn + 16 * u + li);
+  if (tm0 + GM <= epi.inner_rows(M) && tn0 + GN <= N) {
+    // a tile whose rows and columns all exist and are of one kind: what the epilogue
+    // reads, requested for a row of matrix tiles at a time, without a branch per entry
 #pragma unroll
-    for (int t = 0; t < TM; ++t)
+    for (int t = 0; t < TM; ++t) {
+      decltype(epi.row(0)) rw[4];
+      double2 pre[4][TU];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int row = tm0 + wm + 16 * t + lk + 4 * e;
-        if (row >= M) continue;
-        double2 v = make_double2(X[t][u][e], Y[t][u][e]);
-        if constexpr (M3) v = make_double2(X[t][u][e] - Y[t][u][e], S[t][u][e] - X[t][u][e] - Y[t][u][e]);
-        epi(epi.row(row), ca, v);
+        rw[e] = epi.inner_row(tm0 + wm + 16 * t + lk + 4 * e);
+#pragma unroll
+        for (int u = 0; u < TU; ++u) pre[e][u] = epi.pre(rw[e], ca[u]);
       }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int u = 0; u < TU; ++u) epi.put(rw[e], ca[u], ty == tx, pre[e][u], entry(t, u, e));
+    }
+    return;
   }
+#pragma unroll
+  for (int t = 0; t < TM; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int row = tm0 + wm + 16 * t + lk + 4 * e;
+      if (row >= M) continue;
+      const auto rw = epi.row(row);
+#pragma unroll
+      for (int u = 0; u < TU; ++u) {
+        if (tn0 + wn + 16 * u + li >= N) continue;
+        epi(rw, ca[u], entry(t, u, e));
+      }
+    }
 }
 
 // E = Einc + Z x with x = Einc[V] (Z = U M), one wave per row.  (As x = M Einc[V]
@@ -912,8 +956,8 @@ static int refresh_typed(const Geo& g, gfo_state* st, const Layout& L, int32_t k
     // them the 64 x 64 kernel fills the chip better
     const int zx = (kp + kZgT - 1) / kZgT, zy = (g.R + kZgT - 1) / kZgT;
     if ((int64_t)zx * zy >= 1024)
-      hipLaunchKernelGGL((k_zgemm_f64_lds<false, false, false, kZgT, kZgT, 4, 2, EpiStoreZ>), dim3(zx, zy), dim3(512), 0, s, g.R, kp, kp,
-                         (const double2*)U, (int64_t)kp, (const double2*)M, (int64_t)kp, (const int32_t*)nullptr, ez, 0);
+      hipLaunchKernelGGL((k_zgemm_f64_lds<false, false, kZgT, kZgT, 4, 2, EpiStoreZ>), dim3(zx, zy), dim3(512), 0, s, g.R, kp, kp,
+                         (const double2*)U, (int64_t)kp, (const double2*)M, (int64_t)kp, ez, 0);
     else
       hipLaunchKernelGGL((k_zgemm_f64<false, false, EpiStoreZ>), dim3((kp + 63) / 64, (g.R + 63) / 64), dim3(256), 0, s,
                          g.R, kp, kp, (const double2*)U, (int64_t)kp, (const double2*)M, (int64_t)kp,
@@ -926,16 +970,15 @@ static int refresh_typed(const Geo& g, gfo_state* st, const Layout& L, int32_t k
   // the monitor rows whole and the design block on and above its diagonal (the
   // block is symmetric); when the caller keeps the whole block, its lower
   // triangle is then the mirror of the upper one (half the product's work)
-  EpiG0<T> eg{g, table, mon, (T*)st->G, g.dtype == GFO_C64 ? nullptr : (double2*)st->diag64};
+  EpiG0<T> eg{g, table, mon, (T*)st->G, g.dtype == GFO_C64 ? nullptr : (double2*)st->diag64, 1.0f / (float)g.nx};
   // complex64: three real products per complex one (the result is rounded to FP32
   // once, and diag64 comes from k_rf_field); complex128: four
   constexpr bool c64 = std::is_same<T, float2>::value;
   constexpr int GM = c64 ? 64 : 128, GN = 64, TM = c64 ? 2 : 4, TU = 2;
   const int ty = (g.R + GM - 1) / GM, tx = (g.N + GN - 1) / GN;
-  hipLaunchKernelGGL((k_zgemm_f64_lds<false, true, c64, GM, GN, TM, TU, EpiG0<T>>),
+  hipLaunchKernelGGL((k_zgemm_f64_lds<true, c64, GM, GN, TM, TU, EpiG0<T>>),
                      dim3((unsigned)ut_group_count(ty, tx, g.N / GM, GM, GN)), dim3(GM * GN / (4 * TM * TU)), 0, s,
-                     g.R, g.N, kp, (const double2*)Z, (int64_t)kp, (const double2*)U, (int64_t)kp,
-                     (const int32_t*)nullptr, eg, g.N);
+                     g.R, g.N, kp, (const double2*)Z, (int64_t)kp, (const double2*)U, (int64_t)kp, eg, g.N);
   if (note_hip(hipGetLastError()) != hipSuccess) return GFO_EHIP;
   if (!g.upper && launch_sync_lower(g, st, s) != hipSuccess) return GFO_EHIP;   // dense storage
   return GFO_OK;

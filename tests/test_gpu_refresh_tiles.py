@@ -1,0 +1,43 @@
+"""The refresh product's tiles: whole ones of design rows, ragged ones, ones that hold
+monitor rows; pixel coordinates on grids from one column to one row."""
+import numpy as np
+import pytest
+
+from oracle import greens, state as ost
+import workloads as W
+from parity import rel_elem
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("ny,nx,n_mon,flips,kw", [
+    (1, 130, 1, 5, {}), (130, 1, 2, 4, {}), (64, 3, 64, 13, {"delay": 16}), (16, 16, 65, 60, {}),
+    (33, 8, 3, 31, {"delay": 16, "packed": True}), (20, 19, 130, 100, {"upper": True})])
+def test_refresh_tiles(dtype, ny, nx, n_mon, flips, kw):
+    """Tolerance: 100 u kappa of the core, u = 2^-53, as two FP64 solves of one system
+    differ by a modest multiple of u kappa (complex64: plus one rounding); at least
+    1e-11, what the Bessel functions of two libraries differ by against the floor of
+    1e-3 of the largest entry."""
+    from paper_2202_05388_amd.job import Job
+    p = W.tiny(ny, nx, n_mon=n_mon, dtype=dtype)
+    print(f"[case] {ny}x{nx} n_mon {n_mon} {dtype} {flips} flipped {kw}", flush=True)
+    rng = np.random.default_rng(ny + 7 * nx)
+    idx = np.zeros(p.n, np.uint8)
+    idx[rng.choice(p.n, flips, replace=False)] = 1
+    job = Job(p, device="cuda:0", kmax=flips, **kw)
+    job.init()
+    import torch
+    job.eps_idx.copy_(torch.from_numpy(idx))
+    job.refresh()
+    G, E, d, idx2 = job.host_state()
+    eps = ost.eps_of(p, idx)
+    Gd, Ed = ost.dense_state(p, eps)
+    alpha = greens.alpha_of(p, eps)
+    V = np.nonzero(alpha != 0)[0]
+    kappa = np.linalg.cond(np.diag(1.0 / alpha[V]) - greens.build_G0(p)[np.ix_(V, V)])
+    tol64 = max(1e-11, 100 * 2.0 ** -53 * kappa)
+    tol = tol64 if dtype == "c128" else 3e-7 + tol64
+    assert rel_elem(G, Gd) <= tol and rel_elem(E, Ed) <= tol
+    assert rel_elem(d, np.diagonal(Gd[:p.n])) <= tol64
+    assert np.array_equal(idx, idx2) and job.status() == 0
