@@ -18,8 +18,11 @@ _DTYPES = {"c64": (L.GFO_C64, torch.complex64, 8), "c128": (L.GFO_C128, torch.co
 
 
 def _stream_handle(stream=None) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream
+    # the current stream's handle without a Stream object around it (0.2 against 3.1 us;
+    # a call of two kernels is some 10 us of host time)
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 class Job:
