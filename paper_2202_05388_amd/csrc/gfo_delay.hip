@@ -104,11 +104,11 @@ struct GatherElem {
   int64_t i, q;               // monitor row N + e, or row entry q (clamped)
 };
 
-__device__ __forceinline__ GatherElem gather_elem(const Geo& g) {
+__device__ __forceinline__ GatherElem gather_elem(const Geo& g, int bx) {
   GatherElem el;
   const int mpad = gather_mpad(g);
-  el.e = (int64_t)blockIdx.x * kGatherElems + (threadIdx.x & 63);
-  el.mon = (int64_t)blockIdx.x * kGatherElems < mpad;
+  el.e = (int64_t)bx * kGatherElems + (threadIdx.x & 63);
+  el.mon = (int64_t)bx * kGatherElems < mpad;
   el.live = el.mon ? el.e < g.nmon : el.e - mpad < g.ld;
   el.i = el.mon ? g.N + (el.live ? el.e : 0) : 0;
   el.q = el.mon ? 0 : (el.live ? el.e - mpad : 0);
@@ -117,9 +117,10 @@ __device__ __forceinline__ GatherElem gather_elem(const Geo& g) {
 
 template <typename T, int B>
 __device__ __forceinline__ void gather_prefetch_n(const Geo& g, int cnt, const T* __restrict__ CUs,
-                                                  const T* __restrict__ Vs, GatherPre<T, B>& pre) {
+                                                  const T* __restrict__ Vs, GatherPre<T, B>& pre,
+                                                  int bx) {
   pre.cnt = cnt;
-  const GatherElem el = gather_elem(g);
+  const GatherElem el = gather_elem(g, bx);
   // one resource per workgroup: its range ends at the term count
   const int64_t stride = el.mon ? g.R : g.ld;
   const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
@@ -136,7 +137,7 @@ template <typename T, int B>
 __device__ __forceinline__ void gather_prefetch(const Geo& g, const int32_t* __restrict__ count,
                                                 const T* __restrict__ CUs,
                                                 const T* __restrict__ Vs, GatherPre<T, B>& pre) {
-  gather_prefetch_n<T, B>(g, __builtin_amdgcn_readfirstlane(*count), CUs, Vs, pre);
+  gather_prefetch_n<T, B>(g, __builtin_amdgcn_readfirstlane(*count), CUs, Vs, pre, (int)blockIdx.x);
 }
 
 // Sum of a wave's terms s0 + k < cnt (k < B) from zero in slot order: the lane's
@@ -178,7 +179,7 @@ __device__ __forceinline__ void gather_finish(const Geo& g, const gfo_pick pk,
   const int cnt = pre.cnt;
   const int jc = __builtin_amdgcn_readfirstlane(pk.pixel >= 0 && pk.pixel < g.N ? pk.pixel : 0);
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-  const GatherElem el = gather_elem(g);
+  const GatherElem el = gather_elem(g, (int)blockIdx.x);
   const int64_t e = el.e, i = el.i, q = el.q;
   const bool mon = el.mon, live = el.live;
   // every load that depends on the pick, issued together: the terms' entries at
@@ -452,6 +453,10 @@ hipError_t launch_dl_reset(const Geo&, gfo_state* st, const Layout& L, hipStream
 // flush, read it from memory, which k_move_finish brings up to date);
 // snapshots, scores and summaries alternate between two sets of buffers.  The expressions are those of the per-call path (k_gather_dl,
 // k_mon_dl, k_score), so the state and the picks are bit for bit the same.
+// hint: slots past it are not read, unless there are more terms.  The grouped kernel
+// gives the host's count of pending terms (12 jobs of 96 x 96 at 0 to 31 of 64 terms:
+// 14.6 against 17.4 us); for one job every slot's read costs nothing (6.1 us either
+// way at 128 x 128, 5.4 against 5.6 at 31 x 25).
 // Five waves per workgroup: wave 4 takes the pick and then computes what is alike
 // everywhere (the snapshot with its divisions, the FOM monitor's term entry and
 // field) while waves 0 to 3 sum the terms (kGatherParts); wave 0 then applies the
@@ -475,7 +480,7 @@ struct MoveShared {
 
 template <typename T, int PPL, int B, int NE>
 __device__ __forceinline__ void move_body(
-    const Geo& g, int has_prev, int flushed, const Snap* __restrict__ snap_prev,
+    const Geo& g, int bx, int has_prev, int flushed, int hint, const Snap* __restrict__ snap_prev,
     Snap* __restrict__ snap_out, const double* __restrict__ scores_prev,
     const double* __restrict__ partial_prev, const int* __restrict__ pfirst_prev, int nblk_prev,
     int bpix_prev, double* __restrict__ scores_next, double* __restrict__ partial_next,
@@ -499,15 +504,14 @@ __device__ __forceinline__ void move_body(
   const double2 sp_d = snap_prev->dj_new;
   const int cnt = flushed ? 0 : (has_prev ? sp_cnt : mem_cnt);
   if (w < kGatherParts) {
-    const GatherElem el = gather_elem(g);
+    const GatherElem el = gather_elem(g, bx);
     const int64_t e = el.e, i = el.i, q = el.q;
     const bool mon = el.mon, live = el.live;
     // First batch, loads that need nothing else, in flight while wave 4 takes the
-    // pick: the lane's operand of every slot of its wave's terms (those past the
-    // term count are not used), then this lane's own values (its pixel, or its
-    // monitor's field)
+    // pick: the lane's operand of each slot below the hint of its wave's terms, then
+    // this lane's own values (its pixel, or its monitor's field)
     GatherPre<T, B> pre;
-    gather_prefetch_n<T, B>(g, kGatherParts * B, CUs, Vs, pre);
+    gather_prefetch_n<T, B>(g, hint, CUs, Vs, pre, bx);
     const int64_t qc = q < g.N ? q : g.N - 1;
     T Eown = zero, gq = zero;
     double2 dq = make_double2(0.0, 0.0);
@@ -518,6 +522,8 @@ __device__ __forceinline__ void move_body(
       curq = eps_idx[qc];
       gq = grow[qc];
     }
+    // (more terms than the host counts: a state changed behind its back)
+    if (cnt > hint) gather_prefetch_n<T, B>(g, kGatherParts * B, CUs, Vs, pre, bx);
     __syncthreads();
     // Second batch, every load that needs the pick, issued together: the terms'
     // entries at j (lane k of wave w holds its wave's term k: V_s[j] for monitor
@@ -602,7 +608,7 @@ __device__ __forceinline__ void move_body(
     int f = 0x7fffffff;
     if (live && q < g.N && bb > -INFINITY) f = first_at_least<NE>(g, (int)q, F, tie_threshold(bb, tau));
     const uint64_t votes = __ballot(f != 0x7fffffff);
-    const int64_t pb = (int64_t)blockIdx.x - gather_mpad(g) / kGatherElems;
+    const int64_t pb = (int64_t)bx - gather_mpad(g) / kGatherElems;
     if (lane == (votes ? __builtin_ctzll(votes) : 0) && pb * kGatherElems < g.N) {
       partial_next[pb] = bb;
       pfirst_next[pb] = f;
@@ -614,7 +620,7 @@ __device__ __forceinline__ void move_body(
   PickPre<PPL> pp;
   pick_wave_load(partial_prev, pfirst_prev, nblk_prev, pp);
   const T em0_prev = em_src[g.m0];
-  const int n_moves = blockIdx.x == 0 ? *n_flips : 0;
+  const int n_moves = bx == 0 ? *n_flips : 0;
   const double fom = cabs2(St<T>::to_d(em0_prev));
   const gfo_pick pk = pick_wave_take(g, fom, pp, scores_prev, tau, false, bpix_prev);
   const int jc = __builtin_amdgcn_readfirstlane(pk.pixel >= 0 && pk.pixel < g.N ? pk.pixel : 0);
@@ -625,7 +631,7 @@ __device__ __forceinline__ void move_body(
   double2 dj = diag64[jc];
   T Ej = E[jc], gm0j = grow[jc];
   double rec_fom = 0.0;
-  if (blockIdx.x == 0 && pk.pixel >= 0) rec_fom = scores_prev[pk.pixel * g.n_eps + pk.eps_idx];
+  if (bx == 0 && pk.pixel >= 0) rec_fom = scores_prev[pk.pixel * g.n_eps + pk.eps_idx];
   __builtin_amdgcn_sched_barrier(0);
   keep(dj);
   keep(Ej);
@@ -652,7 +658,7 @@ __device__ __forceinline__ void move_body(
     sh.e_new = sn.e_new;
   }
   __syncthreads();
-  if (blockIdx.x == 0 && lane == 0) {
+  if (bx == 0 && lane == 0) {
     *snap_out = sn;
     snap_out->cnt_after = moved ? cnt + 1 : cnt;
     if (moved) {
@@ -705,7 +711,7 @@ __global__ __launch_bounds__(kMoveThreads) void k_move(
     int32_t* __restrict__ n_flips, int32_t* __restrict__ status, T* __restrict__ CUs,
     T* __restrict__ Vs) {
   touch_lines<sizeof(Geo) + 27 * 8>((const int*)__builtin_amdgcn_kernarg_segment_ptr());
-  move_body<T, PPL, B, NE>(g, has_prev, flushed, snap_prev, snap_out, scores_prev, partial_prev,
+  move_body<T, PPL, B, NE>(g, (int)blockIdx.x, has_prev, flushed, kGatherParts * B, snap_prev, snap_out, scores_prev, partial_prev,
                            pfirst_prev, nblk_prev, bpix_prev, scores_next, partial_next, pfirst_next,
                            emon_prev, emon_next, mask, tau, pick_out, G, E, diag64, eps_idx, count,
                            flips, flip_cap, n_flips, status, CUs, Vs);
@@ -947,12 +953,19 @@ __global__ __launch_bounds__(kScoreThreads) void k_mon_score_table(const JobEntr
                     (double*)(w + je->partial), (int*)(w + je->pfirst), je->nblk0);
 }
 
+// One workgroup per kGatherElems elements of a job and no others (at 64 elements a
+// workgroup the launch of their waves is a bound: 12 jobs of 24 to 96 pixels a side,
+// 12 x 146 workgroups of which some 770 have work, 10.3 us, 8.4 us with those alone).
 template <typename T, int PPL, int B, int NE>
 __global__ __launch_bounds__(kMoveThreads) void k_move_table(const JobEntry* __restrict__ tab, int t,
-                                                    uint64_t flushed_mask) {
-  const JobEntry* je = tab + blockIdx.y;
+                                                    uint64_t flushed_mask, int hint, TableWgs wgs) {
+  // the job: the first whose workgroups end beyond this one (a lane per job)
+  const int lane = threadIdx.x & 63, end = wgs.end[lane];
+  const int job = __builtin_ctzll(__ballot((int)blockIdx.x < end));
+  const int first = job > 0 ? __builtin_amdgcn_readlane(end, job - 1) : 0, bx = (int)blockIdx.x - first;
+  const JobEntry* je = tab + job;
   touch_lines<sizeof(JobEntry)>((const int*)je);
-  if ((int)blockIdx.x >= je->n_move_wg) return;
+  if (bx >= je->n_move_wg) return;
   const Geo g = je->g;
   char* w = je->work;
   const int a = t & 1;
@@ -961,7 +974,7 @@ __global__ __launch_bounds__(kMoveThreads) void k_move_table(const JobEntry* __r
   const int64_t sc_a = a ? je->scores2 : je->scores, sc_b = a ? je->scores : je->scores2;
   const int64_t pa_a = a ? je->partial2 : je->partial, pa_b = a ? je->partial : je->partial2;
   const int64_t pf_a = a ? je->pfirst2 : je->pfirst, pf_b = a ? je->pfirst : je->pfirst2;
-  move_body<T, PPL, B, NE>(g, t > 0 ? 1 : 0, (int)((flushed_mask >> blockIdx.y) & 1u),
+  move_body<T, PPL, B, NE>(g, bx, t > 0 ? 1 : 0, (int)((flushed_mask >> job) & 1u), hint,
                        (const Snap*)(w + snap_b), (Snap*)(w + snap_a), (const double*)(w + sc_a),
                        (const double*)(w + pa_a), (const int*)(w + pf_a),
                        t == 0 ? je->nblk0 : je->nblkg, t == 0 ? kScoreThreads : kGatherElems,
@@ -992,9 +1005,9 @@ hipError_t launch_table_scores(const JobEntry* tab, int n_jobs, int max_wg, hipS
 }
 
 template <typename T>
-hipError_t launch_table_move(const JobEntry* tab, int n_jobs, int max_wg, int t, uint64_t flushed,
-                             bool small, int batch, bool two_eps, hipStream_t s) {
-  const dim3 grid((unsigned)max_wg, (unsigned)n_jobs);
+hipError_t launch_table_move(const JobEntry* tab, const TableWgs& wgs, int t, uint64_t flushed,
+                             bool small, int batch, bool two_eps, int hint, hipStream_t s) {
+  const dim3 grid((unsigned)wgs.end[kTableMaxJobs - 1]);
   const bool b16 = batch == 16;
   auto kern = [&](auto ne) {
     constexpr int NE = decltype(ne)::value;
@@ -1003,7 +1016,7 @@ hipError_t launch_table_move(const JobEntry* tab, int n_jobs, int max_wg, int t,
   };
   hipLaunchKernelGGL((two_eps ? kern(std::integral_constant<int, 2>{})
                               : kern(std::integral_constant<int, GFO_MAX_EPS>{})),
-                     grid, dim3(kMoveThreads), 0, s, tab, t, flushed);
+                     grid, dim3(kMoveThreads), 0, s, tab, t, flushed, hint, wgs);
   return note_hip(hipGetLastError());
 }
 
@@ -1016,9 +1029,9 @@ hipError_t launch_table_finish(const JobEntry* tab, int n_jobs, int max_wg, int 
 
 template hipError_t launch_table_scores<float2>(const JobEntry*, int, int, hipStream_t);
 template hipError_t launch_table_scores<double2>(const JobEntry*, int, int, hipStream_t);
-template hipError_t launch_table_move<float2>(const JobEntry*, int, int, int, uint64_t, bool, int, bool,
+template hipError_t launch_table_move<float2>(const JobEntry*, const TableWgs&, int, uint64_t, bool, int, bool, int,
                                               hipStream_t);
-template hipError_t launch_table_move<double2>(const JobEntry*, int, int, int, uint64_t, bool, int, bool,
+template hipError_t launch_table_move<double2>(const JobEntry*, const TableWgs&, int, uint64_t, bool, int, bool, int,
                                                hipStream_t);
 template hipError_t launch_table_finish<float2>(const JobEntry*, int, int, int, hipStream_t);
 template hipError_t launch_table_finish<double2>(const JobEntry*, int, int, int, hipStream_t);

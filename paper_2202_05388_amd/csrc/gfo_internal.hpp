@@ -645,14 +645,20 @@ struct JobEntry {
   int32_t nblkg;        // score summaries of the move kernel (kGatherElems pixels each)
   int32_t pad[3];
 };
+// The move kernel's workgroups over a table's jobs: those of job i end at end[i] (past
+// the last job: all of them).
+constexpr int kTableMaxJobs = 64;
+struct TableWgs {
+  int32_t end[kTableMaxJobs];
+};
 JobEntry make_job_entry(const Geo& g, const gfo_state* st, const Layout& L, uint32_t mask,
                         double tau);
 // the grouped kernels: every job of the table, one launch each
 template <typename T>
 hipError_t launch_table_scores(const JobEntry* tab, int n_jobs, int max_wg, hipStream_t s);
 template <typename T>
-hipError_t launch_table_move(const JobEntry* tab, int n_jobs, int max_wg, int t, uint64_t flushed,
-                             bool small, int batch, bool two_eps, hipStream_t s);
+hipError_t launch_table_move(const JobEntry* tab, const TableWgs& wgs, int t, uint64_t flushed,
+                             bool small, int batch, bool two_eps, int hint, hipStream_t s);
 template <typename T>
 hipError_t launch_table_finish(const JobEntry* tab, int n_jobs, int max_wg, int t, hipStream_t s);
 int gather_move_workgroups(const Geo& g);

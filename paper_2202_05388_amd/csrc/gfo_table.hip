@@ -4,11 +4,13 @@
 // device work), so their launches, not the device, bound a served burst.
 #include "gfo_internal.hpp"
 
+#include <algorithm>
+
 #include <vector>
 
 namespace gfo {
 
-constexpr int kTableMaxJobs = 64;   // the per-move "flushed" flags travel as one 64-bit word
+static_assert(kTableMaxJobs <= 64, "the per-move \"flushed\" flags travel as one 64-bit word");
 
 // Every job of a grouped call: valid, deferred, served by the one-kernel loop,
 // and alike in what selects the kernel instance (storage type, term batch,
@@ -81,15 +83,17 @@ extern "C" int gfo_greedy_steps_table(const gfo_problem* probs, gfo_state* state
   const bool c64 = g0.dtype == GFO_C64;
   const bool small = move_small_grid(g0);
   const int batch = states[0].delay <= 64 ? 16 : 32;
-  int wg_score = 0, wg_move = 0, wg_finish = 0;
+  int wg_score = 0, wg_finish = 0;
+  TableWgs wgs;
   bool two_eps = true;   // every job's table has two entries
   for (int i = 0; i < n_jobs; ++i) {
     const JobEntry je = make_job_entry(geos[i], &states[i], lays[i], 0, 0.0);
     wg_score = je.n_score_wg > wg_score ? je.n_score_wg : wg_score;
-    wg_move = je.n_move_wg > wg_move ? je.n_move_wg : wg_move;
+    wgs.end[i] = (i > 0 ? wgs.end[i - 1] : 0) + je.n_move_wg;
     wg_finish = je.n_finish_wg > wg_finish ? je.n_finish_wg : wg_finish;
     two_eps = two_eps && geos[i].n_eps == 2;
   }
+  std::fill(wgs.end + n_jobs, wgs.end + kTableMaxJobs, wgs.end[n_jobs - 1]);
   // the call's first scores, for every job
   if ((c64 ? launch_table_scores<float2>(tab, n_jobs, wg_score, stream)
            : launch_table_scores<double2>(tab, n_jobs, wg_score, stream)) != hipSuccess)
@@ -109,8 +113,10 @@ extern "C" int gfo_greedy_steps_table(const gfo_problem* probs, gfo_state* state
       st->pending_calls = 0;
       flushed |= (uint64_t)1 << i;
     }
-    if ((c64 ? launch_table_move<float2>(tab, n_jobs, wg_move, t, flushed, small, batch, two_eps, stream)
-             : launch_table_move<double2>(tab, n_jobs, wg_move, t, flushed, small, batch, two_eps, stream)) !=
+    int hint = 0;
+    for (int i = 0; i < n_jobs; ++i) hint = std::max(hint, (int)states[i].pending_calls);
+    if ((c64 ? launch_table_move<float2>(tab, wgs, t, flushed, small, batch, two_eps, hint, stream)
+             : launch_table_move<double2>(tab, wgs, t, flushed, small, batch, two_eps, hint, stream)) !=
         hipSuccess)
       return GFO_EHIP;
     for (int i = 0; i < n_jobs; ++i) ++states[i].pending_calls;
