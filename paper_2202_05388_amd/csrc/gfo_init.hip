@@ -33,41 +33,48 @@ __device__ __forceinline__ double2 self_term(const Geo& g) {
 
 // Design block: G[p, q] = table[|iy_p - iy_q|, |ix_p - ix_q|]; columns >= N zeroed.
 // A workgroup takes 256 x VN consecutive columns (VN = 16 / sizeof(T) per thread: one
-// 16-byte non-temporal store) and kFillRows consecutive rows of one grid row iy_p, so
-// that a thread's table rows are fixed, a matrix row costs it a column distance, VN
-// table reads (of lines its neighbours read too) and a store, and all rows' reads are
-// in flight together.  With `upper`, stores that lie wholly below the diagonal are
-// skipped (the caller marks the lower triangle out of date).
-// Bound by the stores: constants stored in the same pattern take 205 us for the 1.08 GB
-// upper triangle of 128 x 128 complex64; this takes 235 us with 4 rows (16 rows: 262 us,
-// 2: 278 us, one row in address order: 300 us; a form whose workgroups took every
-// 2048th row, with the divisions and products of each entry's address: 243 us).
-// 31 x 47: 4.4 us (16 rows, too few workgroups: 6.5 us).
+// 16-byte non-temporal store) and kFillRows consecutive rows of one grid row iy_p (a
+// segment), so that a thread's table rows are fixed, a matrix row costs it a column
+// distance, VN table reads (of lines its neighbours read too) and a store, and all
+// rows' reads are in flight together.  With `upper`, stores that lie wholly below the
+// diagonal are skipped (the caller marks the lower triangle out of date), and the
+// column blocks of segment y and of the last but y share one line of workgroups, so
+// that none starts without work: their waves' launch bounds this form.
+// 128 x 128 complex64, the 1.08 GB upper triangle: 185 us; 235 with a line of
+// workgroups per segment, half of them idle (16 rows per workgroup: 262, 2: 278, one
+// row in address order: 300; a form whose workgroups took every 2048th row, with the
+// divisions and products of each entry's address: 243).  The whole 2.15 GB: 335 us.
 constexpr int kFillRows = 4;
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_fill_design(Geo g, T* __restrict__ G, const double2* __restrict__ table,
-                                                     int upper, int nseg) {
+                                                     int upper, int nseg, int ncb) {
   constexpr int VN = 16 / (int)sizeof(T);
-  const int64_t q0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * VN;
-  if (q0 >= g.ld) return;
-  int iyq[VN], ixq[VN];
-  bool in[VN];
-#pragma unroll
-  for (int v = 0; v < VN; ++v) {
-    in[v] = q0 + v < g.N;
-    const int q = in[v] ? (int)(q0 + v) : 0;
-    iyq[v] = q / g.nx;
-    ixq[v] = q - iyq[v] * g.nx;
-  }
-  for (int yb = (int)blockIdx.y; yb < g.ny * nseg; yb += (int)gridDim.y) {
-    const int iyp = yb / nseg, x0 = (yb - iyp * nseg) * kFillRows;
+  const int Y = g.ny * nseg;          // segments
+  // first row of a segment; the first column block that reaches the diagonal there
+  auto row0 = [&](int y) { return y / nseg * g.nx + y % nseg * kFillRows; };
+  auto block0 = [&](int y) { return upper ? row0(y) / (256 * VN) : 0; };
+  for (int yy = (int)blockIdx.y; 2 * yy < Y; yy += (int)gridDim.y) {
+    int y = yy, bx = block0(y) + (int)blockIdx.x;
+    if (bx >= ncb) {
+      y = Y - 1 - yy;
+      bx += block0(y) - ncb;
+      if (bx >= ncb || y == yy) continue;
+    }
+    const int64_t q0 = ((int64_t)bx * 256 + threadIdx.x) * VN;
+    if (q0 >= g.ld) continue;
+    const int iyp = y / nseg, x0 = (y - iyp * nseg) * kFillRows;
     const int p0 = iyp * g.nx + x0, nr = min(kFillRows, g.nx - x0);
-    // rows past the workgroup's last column hold nothing to write
-    if (upper && p0 >= ((int64_t)blockIdx.x + 1) * 256 * VN) return;
     const double2* __restrict__ tab[VN];
+    int ixq[VN];
+    bool in[VN];
 #pragma unroll
-    for (int v = 0; v < VN; ++v) tab[v] = table + (int64_t)abs(iyp - iyq[v]) * g.nx;
+    for (int v = 0; v < VN; ++v) {
+      in[v] = q0 + v < g.N;
+      const int q = in[v] ? (int)(q0 + v) : 0, iyq = q / g.nx;
+      ixq[v] = q - iyq * g.nx;
+      tab[v] = table + (int64_t)abs(iyp - iyq) * g.nx;
+    }
     double2 d[kFillRows][VN];
 #pragma unroll
     for (int r = 0; r < kFillRows; ++r)
@@ -162,13 +169,17 @@ static hipError_t init_typed(const Geo& g, gfo_state* st, const Layout& L, hipSt
                        (T*)st->E, (double2*)st->diag64, st->eps_idx, (const double*)(w + L.mon_xy), table,
                        st->n_flips, st->status, (int32_t*)(w + L.dl_hdr), nv, nt, b0);
   constexpr int VN = 16 / (int)sizeof(T);
-  // narrow or very large grids: the workgroups walk the rows (at most 65535 of them over
-  // the rows, and 2^31 work-items in the launch)
   const int nseg = (g.nx + kFillRows - 1) / kFillRows;
-  const int64_t gx = (g.ld + 256 * VN - 1) / (256 * VN);
-  const int64_t gy = std::min({(int64_t)g.ny * nseg, (int64_t)65535, std::max<int64_t>(1, ((int64_t)1 << 31) / (gx * 256))});
+  const int64_t Y = (int64_t)g.ny * nseg, ncb = (g.ld + 256 * VN - 1) / (256 * VN);
+  // the column blocks of segments y and Y - 1 - y: their first rows add up to the same
+  // for every y, so at most this many
+  const int64_t sum = (int64_t)(g.ny - 1) * g.nx + (int64_t)(nseg - 1) * kFillRows;
+  const int64_t gx = g.upper ? 2 * ncb - sum / (256 * VN) + 1 : 2 * ncb;
+  // narrow or very large grids: the workgroups walk the segments (at most 65535 of them
+  // over the segments, and 2^31 work-items in the launch)
+  const int64_t gy = std::min({(Y + 1) / 2, (int64_t)65535, std::max<int64_t>(1, ((int64_t)1 << 31) / (gx * 256))});
   hipLaunchKernelGGL(k_fill_design<T>, dim3((unsigned)gx, (unsigned)gy), dim3(256), 0, s, g, G,
-                     (const double2*)table, g.upper, nseg);
+                     (const double2*)table, g.upper, nseg, (int)ncb);
   return note_hip(hipGetLastError());
 }
 
