@@ -229,13 +229,7 @@ int init_G0(const gfo_problem* prob, gfo_state* st, hipStream_t stream) {
   Layout L;
   if ((rc = validate_state(prob, st, &L))) return rc;
   const Geo g = make_geo(prob, st);
-  char* w = (char*)st->work;
-  // monitor coordinates travel with the call; wait for the copy so that the
-  // caller's host array need not outlive it
-  if (note_hip(hipMemcpyAsync(w + L.mon_xy, prob->h_mon_xy, (size_t)prob->n_mon * 2 * sizeof(double),
-                              hipMemcpyHostToDevice, stream)) != hipSuccess)
-    return GFO_EHIP;
-  if (launch_init(g, st, L, stream) != hipSuccess) return GFO_EHIP;
+  if (launch_init(g, st, L, prob->h_mon_xy, stream) != hipSuccess) return GFO_EHIP;
   st->pending_calls = 0;
   // deferred mode, or a caller that asked for it (lower_stale = 1 on entry),
   // keeps the upper triangle of the design block alone

@@ -11,6 +11,7 @@
 #include "gfo_internal.hpp"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace gfo {
 
@@ -98,6 +99,17 @@ __global__ __launch_bounds__(256) void k_fill_design(Geo g, T* __restrict__ G, c
   }
 }
 
+// Monitor coordinates as a kernel argument: up to kMonArgs monitors (1 KB) travel with
+// the launch, more through a copy of pageable memory to the device, a kernel of its own
+// behind a staging buffer (set-up at 24 x 24: 19.1 against 21.5 us; 12 grouped jobs,
+// set up one after the other, and their 32 moves: 953 against 990 us).
+constexpr int kMonArgs = 64;
+template <bool ARGS>
+struct MonArgs {
+  double xy[ARGS ? 2 * kMonArgs : 1];
+};
+static_assert(2 * kMonArgs <= 256, "the first workgroup writes them to the workspace");
+
 // Everything of the empty design that does not read the offset table, in one launch
 // (each part alone is a launch of 3 to 5 us; four were a fifth of the set-up of a
 // 24 x 24 job): workgroups [0, nv) the vectors, E = exp(i k0 y) on every row, diag64,
@@ -106,17 +118,22 @@ __global__ __launch_bounds__(256) void k_fill_design(Geo g, T* __restrict__ G, c
 // columns of one row each (packed 48 x 2048 with 256 monitors, 25 M kernel values: 291 us,
 // 365 us in a launch of their own that walked the rows).  Bound by the Bessel functions (48 registers with the one
 // evaluation that table and monitors share; 194 with one each and a loop over rows).
-template <typename T>
+template <typename T, bool ARGS>
 __global__ __launch_bounds__(256) void k_init_rest(Geo g, T* __restrict__ G, T* __restrict__ E,
                                                    double2* __restrict__ diag64, uint8_t* __restrict__ eps_idx,
-                                                   const double* __restrict__ mon_xy, double2* __restrict__ table,
+                                                   double* __restrict__ mon_xy, double2* __restrict__ table,
                                                    int32_t* n_flips, int32_t* status, int32_t* pending,
-                                                   int nv, int nt, int64_t b0) {
+                                                   int nv, int nt, int64_t b0, MonArgs<ARGS> args) {
   const int64_t b = b0 + blockIdx.x;
+  auto coord = [&](int i) {
+    if constexpr (ARGS) return args.xy[i];
+    else return mon_xy[i];
+  };
   if (b < nv) {
     const int i = (int)b * 256 + threadIdx.x;
+    if (ARGS && b == 0 && (int)threadIdx.x < 2 * g.nmon) mon_xy[threadIdx.x] = coord(threadIdx.x);   // for refresh_G
     if (i < g.R) {
-      const double y = i < g.N ? (i / g.nx - 0.5 * (g.ny - 1)) * g.h : mon_xy[2 * (i - g.N) + 1];
+      const double y = i < g.N ? (i / g.nx - 0.5 * (g.ny - 1)) * g.h : coord(2 * (i - g.N) + 1);
       double s, c;
       sincos(g.k0 * y, &s, &c);
       E[i] = St<T>::from_d(make_double2(c, s));
@@ -142,8 +159,8 @@ __global__ __launch_bounds__(256) void k_init_rest(Geo g, T* __restrict__ G, T* 
   if (!tab) {
     const double xq = (ix - 0.5 * (g.nx - 1)) * g.h;
     const double yq = (iy - 0.5 * (g.ny - 1)) * g.h;
-    dx = mon_xy[2 * m] - xq;
-    dy = mon_xy[2 * m + 1] - yq;
+    dx = coord(2 * m) - xq;
+    dy = coord(2 * m + 1) - yq;
   }
   double r = sqrt(dx * dx + dy * dy);
   if (tab) r = g.h * r;
@@ -157,17 +174,31 @@ __global__ __launch_bounds__(256) void k_init_rest(Geo g, T* __restrict__ G, T* 
 }
 
 template <typename T>
-static hipError_t init_typed(const Geo& g, gfo_state* st, const Layout& L, hipStream_t s) {
+static hipError_t init_typed(const Geo& g, gfo_state* st, const Layout& L, const double* mon_host, hipStream_t s) {
   char* w = (char*)st->work;
   double2* table = (double2*)(w + L.table);
   T* G = (T*)st->G;
   const int nv = (g.R + 255) / 256, nt = (g.N + 255) / 256;
   const int64_t nb = nv + nt + (g.ld + 255) / 256 * g.nmon;
+  double* mon = (double*)(w + L.mon_xy);
   constexpr int64_t kMaxBlocks = 1 << 22;   // per launch (2^30 work-items)
-  for (int64_t b0 = 0; b0 < nb; b0 += kMaxBlocks)
-    hipLaunchKernelGGL(k_init_rest<T>, dim3((unsigned)std::min(nb - b0, kMaxBlocks)), dim3(256), 0, s, g, G,
-                       (T*)st->E, (double2*)st->diag64, st->eps_idx, (const double*)(w + L.mon_xy), table,
-                       st->n_flips, st->status, (int32_t*)(w + L.dl_hdr), nv, nt, b0);
+  auto rest = [&](const auto& args) {
+    constexpr bool ARGS = std::is_same<std::decay_t<decltype(args)>, MonArgs<true>>::value;
+    for (int64_t b0 = 0; b0 < nb; b0 += kMaxBlocks)
+      hipLaunchKernelGGL((k_init_rest<T, ARGS>), dim3((unsigned)std::min(nb - b0, kMaxBlocks)), dim3(256), 0, s, g, G,
+                         (T*)st->E, (double2*)st->diag64, st->eps_idx, mon, table, st->n_flips, st->status,
+                         (int32_t*)(w + L.dl_hdr), nv, nt, b0, args);
+  };
+  if (g.nmon <= kMonArgs) {
+    MonArgs<true> args = {};
+    std::copy(mon_host, mon_host + 2 * g.nmon, args.xy);
+    rest(args);
+  } else {
+    // the caller waits for the stream, so that its array need not outlive the copy
+    if (hipError_t e = hipMemcpyAsync(mon, mon_host, (size_t)g.nmon * 2 * sizeof(double), hipMemcpyHostToDevice, s))
+      return note_hip(e);
+    rest(MonArgs<false>{});
+  }
   constexpr int VN = 16 / (int)sizeof(T);
   const int nseg = (g.nx + kFillRows - 1) / kFillRows;
   const int64_t Y = (int64_t)g.ny * nseg, ncb = (g.ld + 256 * VN - 1) / (256 * VN);
@@ -183,9 +214,9 @@ static hipError_t init_typed(const Geo& g, gfo_state* st, const Layout& L, hipSt
   return note_hip(hipGetLastError());
 }
 
-hipError_t launch_init(const Geo& g, gfo_state* st, const Layout& L, hipStream_t s) {
-  if (g.dtype == GFO_C64) return init_typed<float2>(g, st, L, s);
-  return init_typed<double2>(g, st, L, s);
+hipError_t launch_init(const Geo& g, gfo_state* st, const Layout& L, const double* mon_host, hipStream_t s) {
+  if (g.dtype == GFO_C64) return init_typed<float2>(g, st, L, mon_host, s);
+  return init_typed<double2>(g, st, L, mon_host, s);
 }
 
 }  // namespace gfo

@@ -505,7 +505,7 @@ int find_bg(const gfo_problem* p);
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // ------------------------------------------------------------------ launchers
-hipError_t launch_init(const Geo& g, gfo_state* st, const Layout& L, hipStream_t s);
+hipError_t launch_init(const Geo& g, gfo_state* st, const Layout& L, const double* mon_host, hipStream_t s);
 hipError_t launch_score(const Geo& g, const gfo_state* st, const Layout& L, uint32_t mask,
                         double tau, int topk, int spacing, gfo_pick* out, hipStream_t s);
 // Scratch of score_candidates: N x n_eps scores, then per score workgroup its

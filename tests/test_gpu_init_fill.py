@@ -45,3 +45,25 @@ def test_fill_taller_than_one_launch():
     N = p.n
     for r in (1, 3, 4, 511, 65023, 65027, 65028, 65534, 65535, 65536, N - 1):
         assert torch.equal(job.G[r, r:N], job.G[0, :N - r]), r
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("n_mon", [1, 63, 64, 65, 130])
+def test_monitor_counts(dtype, n_mon):
+    """Monitors as a kernel argument (up to 64) and through a copy: the matrix as above,
+    and the coordinates that a refresh of one flipped pixel reads afterwards."""
+    import torch
+    from paper_2202_05388_amd.job import Job
+    p = W.tiny(6, 9, n_mon=n_mon, dtype=dtype)
+    print(f"[case] n_mon {n_mon} {dtype}", flush=True)
+    job = Job(p, device="cuda:0", kmax=1)
+    job.init()
+    tol = 1e-11 if dtype == "c128" else 3e-7
+    assert rel_elem(job.host_state()[0], greens.build_G0(p)) <= tol
+    idx = np.zeros(p.n, np.uint8)
+    idx[17] = 1
+    job.eps_idx.copy_(torch.from_numpy(idx))
+    job.refresh()
+    G, E, _, _ = job.host_state()
+    Gd, Ed = ost.dense_state(p, ost.eps_of(p, idx))
+    assert rel_elem(G, Gd) <= tol and rel_elem(E, Ed) <= tol and job.status() == 0
