@@ -294,8 +294,16 @@ __global__ __launch_bounds__(512) void k_gj_panel(const double2* __restrict__ S,
   __shared__ GjBest cand[2][8];
   __shared__ double2 crow[2][8][PW];
   __shared__ int spiv[PW];
+  // a wave's 64 rows between memory, where a row is PW entries side by side, and the
+  // registers of a thread per row (one pad entry: a column's reads fall on all banks):
+  // whole lines per load instead of a part of 64 of them, 23.6 against 30 us at 1512
+  // rows; few rows, which the L1 holds, are read directly (184 rows of 16: 28.5 us
+  // either way)
+  constexpr bool kTile = RT > 1;
+  __shared__ double2 tile[kTile ? 8 : 1][kTile ? 64 : 1][PW + 1];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int nt = (int)blockDim.x;
+  const int er = lane / PW, ec = lane % PW;         // the entries a lane moves: rows er + (64 / PW) i
   if (threadIdx.x < 16) cand[threadIdx.x >> 3][threadIdx.x & 7] = GjBest{-2.0, 0x7fffffff, 0};   // waves not launched
   bool singular = false;
   double2 a[RT][PW];
@@ -305,7 +313,19 @@ __global__ __launch_bounds__(512) void k_gj_panel(const double2* __restrict__ S,
     const int r = (int)threadIdx.x + nt * q, rc = r < kp ? r : 0;
     open[q] = r < kp && used[rc] == 0;
 #pragma unroll
-    for (int i = 0; i < PW; ++i) a[q][i] = S[(int64_t)rc * lds + col0 + (i < qn ? i : 0)];
+    for (int i = 0; i < PW; ++i) {
+      const int re = kTile ? nt * q + 64 * w + er + 64 / PW * i : r, ce = kTile ? ec : i;
+      a[q][i] = S[(int64_t)(re < kp ? re : 0) * lds + col0 + (ce < qn ? ce : 0)];
+    }
+  }
+  if constexpr (kTile) {
+#pragma unroll
+    for (int q = 0; q < RT; ++q) {
+#pragma unroll
+      for (int i = 0; i < PW; ++i) tile[w][er + 64 / PW * i][ec] = a[q][i];
+#pragma unroll
+      for (int i = 0; i < PW; ++i) a[q][i] = tile[w][lane][i];
+    }
   }
   __syncthreads();
   // One step's code for all steps: column 0 is the step's, and the columns move one
@@ -396,12 +416,18 @@ __global__ __launch_bounds__(512) void k_gj_panel(const double2* __restrict__ S,
   if (threadIdx.x == 0 && singular) atomicOr(status, GFO_STATUS_SINGULAR);
 #pragma unroll
   for (int q = 0; q < RT; ++q) {
-    const int r = (int)threadIdx.x + nt * q;
-    if (r < kp)
+#pragma unroll
+    for (int i = 0; i < PW; ++i) {
+      const int r = (int)threadIdx.x + nt * q, col = i + qn < PW ? i + qn : i + qn - PW;   // the column now in place i
+      if constexpr (kTile) tile[w][lane][col] = a[q][i];
+      else if (r < kp && col < qn) T[(int64_t)r * PW + col] = a[q][i];
+    }
+    if constexpr (kTile)
 #pragma unroll
       for (int i = 0; i < PW; ++i) {
-        const int col = i + qn < PW ? i + qn : i + qn - PW;   // the column now in place i
-        if (col < qn) T[(int64_t)r * PW + col] = a[q][i];
+        const int re = nt * q + 64 * w + er + 64 / PW * i;
+        const double2 x = tile[w][er + 64 / PW * i][ec];
+        if (re < kp && ec < qn) T[(int64_t)re * PW + ec] = x;
       }
   }
 }
