@@ -43,10 +43,10 @@ PMC_TRAFFIC = [
     # complex64 flush records: one per term bucket (the launcher's kernel for up to 16, 32, 64
     # or 128 pending terms) of the default variant, each taken on flushes that fold the
     # bucket's full term count: the tile kernel, then the pack kernel
-    {"kernel": "k_flush_c64", "source": "paper_2202_05388_amd/csrc/gfo_flush.hip", "code_sha256": "467dc02667036d6a9a06a30b399e3413a41a0aeebbb56137dcf67f5f431dbc44", "workload": "square128_c64", "variant": "up_bandseg_s3", "bucket": 16, "tile_kernel": "k_flush_c64_pair<4, 4, true>", "fetch_kib": 539642.0 + 2065.0, "write_kib": 1060921.4 + 4104.0},
-    {"kernel": "k_flush_c64", "source": "paper_2202_05388_amd/csrc/gfo_flush.hip", "code_sha256": "467dc02667036d6a9a06a30b399e3413a41a0aeebbb56137dcf67f5f431dbc44", "workload": "square128_c64", "variant": "up_bandseg_s3", "bucket": 32, "tile_kernel": "k_flush_c64_s3<2>", "fetch_kib": 562021.2 + 4135.0, "write_kib": 1060888.1 + 12312.0},
-    {"kernel": "k_flush_c64", "source": "paper_2202_05388_amd/csrc/gfo_flush.hip", "code_sha256": "467dc02667036d6a9a06a30b399e3413a41a0aeebbb56137dcf67f5f431dbc44", "workload": "square128_c64", "variant": "up_bandseg_s3", "bucket": 64, "tile_kernel": "k_flush_c64_s3<4>", "fetch_kib": 620708.7 + 8237.0, "write_kib": 1060870.4 + 24624.0},
-    {"kernel": "k_flush_c64", "source": "paper_2202_05388_amd/csrc/gfo_flush.hip", "code_sha256": "467dc02667036d6a9a06a30b399e3413a41a0aeebbb56137dcf67f5f431dbc44", "workload": "square128_c64", "variant": "up_bandseg_s3", "bucket": 128, "tile_kernel": "k_flush_c64_s3<8>", "fetch_kib": 1014278.6 + 16452.1, "write_kib": 1060904.5 + 49248.0},
+    {"kernel": "k_flush_c64", "source": "paper_2202_05388_amd/csrc/gfo_flush.hip", "code_sha256": "3f0be79a23d3c24d420bb744b011ca270e5c0c93c5bb24933f9bb61c5ddcf0bb", "workload": "square128_c64", "variant": "up_bandseg_s3", "bucket": 16, "tile_kernel": "k_flush_c64_pair<4, 4, true>", "fetch_kib": 539628.7 + 2065.0, "write_kib": 1060883.0 + 4104.0},
+    {"kernel": "k_flush_c64", "source": "paper_2202_05388_amd/csrc/gfo_flush.hip", "code_sha256": "3f0be79a23d3c24d420bb744b011ca270e5c0c93c5bb24933f9bb61c5ddcf0bb", "workload": "square128_c64", "variant": "up_bandseg_s3", "bucket": 32, "tile_kernel": "k_flush_c64_s3<2>", "fetch_kib": 562701.8 + 4137.0, "write_kib": 1060876.5 + 12312.0},
+    {"kernel": "k_flush_c64", "source": "paper_2202_05388_amd/csrc/gfo_flush.hip", "code_sha256": "3f0be79a23d3c24d420bb744b011ca270e5c0c93c5bb24933f9bb61c5ddcf0bb", "workload": "square128_c64", "variant": "up_bandseg_s3", "bucket": 64, "tile_kernel": "k_flush_c64_s3<4>", "fetch_kib": 636615.9 + 8241.7, "write_kib": 1060866.9 + 24624.0},
+    {"kernel": "k_flush_c64", "source": "paper_2202_05388_amd/csrc/gfo_flush.hip", "code_sha256": "3f0be79a23d3c24d420bb744b011ca270e5c0c93c5bb24933f9bb61c5ddcf0bb", "workload": "square128_c64", "variant": "up_bandseg_s3", "bucket": 128, "tile_kernel": "k_flush_c64_s3_ring", "fetch_kib": 733853.3 + 16450.0, "write_kib": 1060880.3 + 49248.0},
 ]
 
 
