@@ -80,3 +80,30 @@ def test_rank_32_update_large(precision):
         assert _rel(G1 - G, Gd - G, floor=1.0) <= 1e-2
     assert _rel(E1, Ed) <= 5e-6
     assert _rel(d1, np.diagonal(Gd[:N])) <= 5e-6
+
+
+def test_records_of_32_with_repeats():
+    """32 records of which a pixel's first valid one counts (no-ops, sentinels and pixels or
+    materials out of range between them): the same bits as the counted ones alone."""
+    from paper_2202_05388_amd import _lib as L
+    p = W.tiny(12, 13, n_mon=5, dtype="c64").replace(eps_table=(1.0, 12.25, 4.0))
+    rng = np.random.default_rng(3)
+    recs, counted = [], []
+    for j in rng.choice(p.n, 14, replace=False):
+        e = int(rng.integers(1, 3))
+        recs += [(int(j), 0), (int(j), e)]                  # a no-op, then the move
+        counted.append((int(j), e))
+    recs = recs[:9] + [(-1, -1), (recs[3][0], 2), (p.n, 1), (recs[1][0], 3)] + recs[9:]
+    recs = recs[:31] + [(recs[1][0], 3 - recs[1][1])]       # the last: the first pixel once more
+    seen = {j for j, e in recs if 0 <= j < p.n and 0 < e < 3}
+    counted = [c for c in counted if c[0] in seen]
+    a, b = _job(p), _job(p)
+    for job, rs in ((a, recs), (b, counted)):
+        job.init()
+        for t, (j, e) in enumerate(rs):
+            job.set_pick(j, e, slot=t)
+        job.apply_rank_k(len(rs), precision=L.GFO_FP32)
+    assert len(recs) == 32 and np.array_equal(a.history(), b.history())
+    assert [tuple(x) for x in a.history()] == counted
+    for x, y in zip(a.host_state(), b.host_state()):
+        assert np.array_equal(x, y)
