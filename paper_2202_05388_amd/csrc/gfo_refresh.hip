@@ -434,13 +434,14 @@ __global__ __launch_bounds__(512) void k_gj_panel(const double2* __restrict__ S,
 
 // The panel's product on the other columns (the comment above): D[m][n] = S[m][n]
 // + sum_i T[m][i] S[piv[i]][n], without S[m][n] in the panel's pivot rows; columns
-// [col0, col0 + qn) take T.  S and D: kp x n_cols, ld lds; ranks up to 4 KQ.  A
+// [col0, col0 + qn) take T.  S and D: kp x n_cols, ld lds and ldd; ranks up to 4 KQ.  A
 // wave takes 16 TM x 16 TN outputs (tile operands as in k_zgemm_f64) and requests
 // every operand before its first product; bound by those loads at small kp, by
 // reading S and writing D beyond.
 template <int TM, int TN, int KQ>
 __global__ __launch_bounds__(256) void k_gj_update(int kp, int n_cols, int lds, const double2* __restrict__ S,
-                                                   double2* __restrict__ D, const double2* __restrict__ T, int ldt,
+                                                   double2* __restrict__ D, int ldd,
+                                                   const double2* __restrict__ T, int ldt,
                                                    const int32_t* __restrict__ piv, const int32_t* __restrict__ used,
                                                    int c0, int qn, int col0) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -497,7 +498,7 @@ __global__ __launch_bounds__(256) void k_gj_update(int kp, int n_cols, int lds, 
           out = v;
         else
           out = cadd(S[(int64_t)r * lds + n], v);
-        D[(int64_t)r * lds + n] = out;
+        D[(int64_t)r * ldd + n] = out;
       }
 }
 
@@ -901,13 +902,13 @@ hipError_t launch_refresh_overflow(gfo_state* st, hipStream_t s) {
 // is small enough that larger tiles would leave compute units idle (180 columns: 36
 // workgroups against 9), else 32 x 32.
 template <int KQ>
-static void launch_gj_update(int kp, int n_cols, int lds, const double2* S, double2* D, const double2* T, int ldt,
+static void launch_gj_update(int kp, int n_cols, int lds, const double2* S, double2* D, int ldd, const double2* T, int ldt,
                              const int32_t* piv, const int32_t* used, int c0, int qn, int col0, hipStream_t s) {
   const bool small = (int64_t)kp * n_cols <= 512 * 512;
   const int tile = small ? 32 : 64;
   hipLaunchKernelGGL((small ? k_gj_update<1, 1, KQ> : k_gj_update<2, 2, KQ>),
                      dim3((unsigned)((n_cols + tile - 1) / tile), (unsigned)((kp + tile - 1) / tile)), dim3(256), 0, s,
-                     kp, n_cols, lds, S, D, T, ldt, piv + c0, used, c0, qn, col0);
+                     kp, n_cols, lds, S, D, ldd, T, ldt, piv + c0, used, c0, qn, col0);
 }
 
 template <typename T>
@@ -947,29 +948,32 @@ static int refresh_typed(const Geo& g, gfo_state* st, const Layout& L, int32_t k
         const int qn = min(16, kp - c0);
         hipLaunchKernelGGL((k_gj_panel<1, 16>), dim3(1), dim3(nt), 0, s, (const double2*)W[cur], kp, c0, Tn, kp, c0, qn,
                            piv, used, st->status);
-        launch_gj_update<4>(kp, kp, kp, W[cur], W[cur ^ 1], Tn, 16, piv, used, c0, qn, c0, s);
+        launch_gj_update<4>(kp, kp, kp, W[cur], W[cur ^ 1], kp, Tn, 16, piv, used, c0, qn, c0, s);
       }
     } else {
       const unsigned np = (unsigned)(((int64_t)kp * kGjPanel + 255) / 256);
       const unsigned nt4 = (unsigned)((kp + 255) / 256 * 64);   // four rows per thread, kp <= 2048
       for (int c0 = 0; c0 < kp; c0 += kGjPanel, cur ^= 1) {
         const int qn = min(kGjPanel, kp - c0);
-        hipLaunchKernelGGL(k_gj_panel_copy, dim3(np), dim3(256), 0, s, (const double2*)W[cur], Pn[0], kp, c0, qn);
         int b = 0;                // Pn[b] holds the panel
         if (kp <= 2048) {
+          // the first subpanel and its update read the panel where it lies (copied first, as
+          // the steps of larger matrices want it: 0.6 ms of 27 at kp 1512)
           for (int s0 = 0; s0 < qn; s0 += 8, b ^= 1) {
-            const int sn = min(8, qn - s0);
-            hipLaunchKernelGGL((k_gj_panel<4, 8>), dim3(1), dim3(nt4), 0, s, (const double2*)Pn[b], kGjPanel, s0, Tn,
-                               kp, c0 + s0, sn, piv, used, st->status);
-            launch_gj_update<2>(kp, qn, kGjPanel, Pn[b], Pn[b ^ 1], Tn, 8, piv, used, c0 + s0, sn, s0, s);
+            const int sn = min(8, qn - s0), lds = s0 == 0 ? kp : kGjPanel;
+            const double2* src = s0 == 0 ? W[cur] + c0 : Pn[b];
+            hipLaunchKernelGGL((k_gj_panel<4, 8>), dim3(1), dim3(nt4), 0, s, src, lds, s0, Tn, kp, c0 + s0, sn, piv, used,
+                               st->status);
+            launch_gj_update<2>(kp, qn, lds, src, Pn[b ^ 1], kGjPanel, Tn, 8, piv, used, c0 + s0, sn, s0, s);
           }
         } else {
+          hipLaunchKernelGGL(k_gj_panel_copy, dim3(np), dim3(256), 0, s, (const double2*)W[cur], Pn[0], kp, c0, qn);
           for (int l = 0; l < qn; ++l, b ^= 1)
             hipLaunchKernelGGL(k_gj_panel_step, dim3((unsigned)nb), dim3(256), 0, s, (const double2*)Pn[b], Pn[b ^ 1],
                                kp, c0, qn, c0 + l, l == 0 ? (const GjPart*)nullptr : (const GjPart*)part[(l + 1) & 1],
                                nb, part[l & 1], piv, used, st->status);
         }
-        launch_gj_update<8>(kp, kp, kp, W[cur], W[cur ^ 1], Pn[b], kGjPanel, piv, used, c0, qn, c0, s);
+        launch_gj_update<8>(kp, kp, kp, W[cur], W[cur ^ 1], kp, Pn[b], kGjPanel, piv, used, c0, qn, c0, s);
       }
     }
     const double2* X = W[cur];    // the in-place result; M goes to the other buffer
