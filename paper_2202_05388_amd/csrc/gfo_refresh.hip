@@ -436,8 +436,10 @@ __global__ __launch_bounds__(512) void k_gj_panel(const double2* __restrict__ S,
 // + sum_i T[m][i] S[piv[i]][n], without S[m][n] in the panel's pivot rows; columns
 // [col0, col0 + qn) take T.  S and D: kp x n_cols, ld lds and ldd; ranks up to 4 KQ.  A
 // wave takes 16 TM x 16 TN outputs (tile operands as in k_zgemm_f64) and requests
-// every operand before its first product; bound by those loads at small kp, by
-// reading S and writing D beyond.
+// every operand and every entry that it changes before its first product; bound by
+// those loads at small kp, by reading S and writing D beyond (1512 x 1512, rank 32: 25.4
+// us, 39 with each entry's old value and pivot flag read behind a branch in the
+// epilogue; rank 8 on the panel's 32 columns 4.2 us, 5.2 before).
 template <int TM, int TN, int KQ>
 __global__ __launch_bounds__(256) void k_gj_update(int kp, int n_cols, int lds, const double2* __restrict__ S,
                                                    double2* __restrict__ D, int ldd,
@@ -465,6 +467,31 @@ __global__ __launch_bounds__(256) void k_gj_update(int kp, int n_cols, int lds, 
       b[s][u] = pick_of(k < qn, b[s][u], make_double2(0.0, 0.0));
     }
   }
+  // what the epilogue reads, requested behind the operands and without a branch per
+  // entry: the entry's old value, or in the panel's own columns its T
+  double2 old[TM][TN][4];
+  bool in_panel[TM][4];                          // a pivot row of this panel
+  bool own[TN];
+#pragma unroll
+  for (int u = 0; u < TN; ++u) {
+    const int n = n0 + 16 * u + li;
+    own[u] = n >= col0 && n < col0 + qn;
+  }
+#pragma unroll
+  for (int t = 0; t < TM; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = m0 + 16 * t + lk + 4 * e, rc = r < kp ? r : 0;
+      const int us = used[rc];
+      in_panel[t][e] = us > c0 && us <= c0 + qn;
+#pragma unroll
+      for (int u = 0; u < TN; ++u) {
+        const int n = n0 + 16 * u + li;
+        const double2* at = S + ((int64_t)rc * lds + (n < n_cols ? n : 0));
+        const double2* own_at = T + ((int64_t)rc * ldt + (own[u] ? n - col0 : 0));
+        old[t][u][e] = *(own[u] ? own_at : at);
+      }
+    }
   f64x4 re[TM][TN], im[TM][TN];
 #pragma unroll
   for (int t = 0; t < TM; ++t)
@@ -488,17 +515,9 @@ __global__ __launch_bounds__(256) void k_gj_update(int kp, int n_cols, int lds, 
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int r = m0 + 16 * t + lk + 4 * e, n = n0 + 16 * u + li;
-        if (r >= kp || n >= n_cols) continue;
-        const double2 v = make_double2(re[t][u][e], im[t][u][e]);
-        const int us = used[r];
-        double2 out;
-        if (n >= col0 && n < col0 + qn)
-          out = T[(int64_t)r * ldt + (n - col0)];
-        else if (us > c0 && us <= c0 + qn)
-          out = v;
-        else
-          out = cadd(S[(int64_t)r * lds + n], v);
-        D[(int64_t)r * ldd + n] = out;
+        const double2 v = make_double2(re[t][u][e], im[t][u][e]), o = old[t][u][e];
+        const double2 out = pick_of(own[u], o, pick_of(in_panel[t][e], v, cadd(o, v)));
+        if (r < kp && n < n_cols) D[(int64_t)r * ldd + n] = out;
       }
 }
 
