@@ -297,7 +297,7 @@ __global__ __launch_bounds__(512) void k_gj_panel(const double2* __restrict__ S,
   // a wave's 64 rows between memory, where a row is PW entries side by side, and the
   // registers of a thread per row (one pad entry: a column's reads fall on all banks):
   // whole lines per load instead of a part of 64 of them, 23.6 against 30 us at 1512
-  // rows; few rows, which the L1 holds, are read directly (184 rows of 16: 28.5 us
+  // rows, four per thread; few rows, which the L1 holds, are read directly (184 rows of 16: 28.5 us
   // either way)
   constexpr bool kTile = RT > 1;
   __shared__ double2 tile[kTile ? 8 : 1][kTile ? 64 : 1][PW + 1];
@@ -971,7 +971,10 @@ static int refresh_typed(const Geo& g, gfo_state* st, const Layout& L, int32_t k
       }
     } else {
       const unsigned np = (unsigned)(((int64_t)kp * kGjPanel + 255) / 256);
-      const unsigned nt4 = (unsigned)((kp + 255) / 256 * 64);   // four rows per thread, kp <= 2048
+      // the fewest rows per thread that 512 threads hold (panel at 1512 rows: 21.5 us with
+      // three rows on 512 threads, 23.8 with four on 384; at 1020 18.6 and 19.5)
+      const int rt = kp <= 1024 ? 2 : kp <= 1536 ? 3 : 4;
+      const unsigned nt = (unsigned)((kp + 64 * rt - 1) / (64 * rt) * 64);
       for (int c0 = 0; c0 < kp; c0 += kGjPanel, cur ^= 1) {
         const int qn = min(kGjPanel, kp - c0);
         int b = 0;                // Pn[b] holds the panel
@@ -981,7 +984,7 @@ static int refresh_typed(const Geo& g, gfo_state* st, const Layout& L, int32_t k
           for (int s0 = 0; s0 < qn; s0 += 8, b ^= 1) {
             const int sn = min(8, qn - s0), lds = s0 == 0 ? kp : kGjPanel;
             const double2* src = s0 == 0 ? W[cur] + c0 : Pn[b];
-            hipLaunchKernelGGL((k_gj_panel<4, 8>), dim3(1), dim3(nt4), 0, s, src, lds, s0, Tn, kp, c0 + s0, sn, piv, used,
+            hipLaunchKernelGGL((rt == 2 ? k_gj_panel<2, 8> : rt == 3 ? k_gj_panel<3, 8> : k_gj_panel<4, 8>), dim3(1), dim3(nt), 0, s, src, lds, s0, Tn, kp, c0 + s0, sn, piv, used,
                                st->status);
             launch_gj_update<2>(kp, qn, lds, src, Pn[b ^ 1], kGjPanel, Tn, 8, piv, used, c0 + s0, sn, s0, s);
           }

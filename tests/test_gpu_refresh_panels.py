@@ -1,6 +1,6 @@
 """The refresh's blocked inverse at the edges of its panel sizes: one row per thread
-up to 512 flipped pixels (panels of 16 columns), four per thread up to 2048
-(panels of 32 in subpanels of 8), one launch per column beyond; the last panel
+up to 512 flipped pixels (panels of 16 columns), two, three and four per thread up to
+1024, 1536 and 2048 (panels of 32 in subpanels of 8), one launch per column beyond; the last panel
 partial or whole, fewer rows than a wave and more.  A mirror-symmetric structure
 has rows of equal modulus, so pivots are chosen among exact ties.
 
@@ -28,9 +28,13 @@ pytestmark = pytest.mark.gpu
     (9, 9, 64, True),
     (9, 9, 66, True),          # a second wave with 4 rows
     (24, 24, 512, False),      # eight waves, the last of one row per thread
-    (24, 24, 513, True),       # four rows per thread, kp = 516: a last panel of 4 columns
+    (24, 24, 513, True),       # two rows per thread, kp = 516: a last panel of 4 columns
     (31, 32, 900, True),
-    (36, 35, 1153, False),     # five waves of four rows, kp = 1156
+    (33, 33, 1024, False),     # eight waves of two rows, all full
+    (33, 33, 1025, True),      # three rows per thread
+    (36, 35, 1153, False),     # seven waves of three rows, kp = 1156
+    (40, 39, 1536, False),
+    (40, 40, 1540, True),      # four rows per thread
     (47, 45, 2050, False),     # beyond 2048: one launch per column
 ])
 def test_refresh_panel_edges(ny, nx, k, mirror):
