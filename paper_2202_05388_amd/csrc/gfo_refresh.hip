@@ -437,9 +437,9 @@ __global__ __launch_bounds__(512) void k_gj_panel(const double2* __restrict__ S,
 // [col0, col0 + qn) take T.  S and D: kp x n_cols, ld lds and ldd; ranks up to 4 KQ.  A
 // wave takes 16 TM x 16 TN outputs (tile operands as in k_zgemm_f64) and requests
 // every operand and every entry that it changes before its first product; bound by
-// those loads at small kp, by reading S and writing D beyond (1512 x 1512, rank 32: 25.4
-// us, 39 with each entry's old value and pivot flag read behind a branch in the
-// epilogue; rank 8 on the panel's 32 columns 4.2 us, 5.2 before).
+// those loads at small kp, by reading S and writing D beyond (1512 x 1512, rank 32, TM =
+// TN = 2: 25.4 us, 39 with each entry's old value and pivot flag read behind a branch in
+// the epilogue; rank 8 on the panel's 32 columns 4.2 us, 5.2 before).
 template <int TM, int TN, int KQ>
 __global__ __launch_bounds__(256) void k_gj_update(int kp, int n_cols, int lds, const double2* __restrict__ S,
                                                    double2* __restrict__ D, int ldd,
@@ -917,15 +917,19 @@ hipError_t launch_refresh_overflow(gfo_state* st, hipStream_t s) {
   return note_hip(hipGetLastError());
 }
 
-// The panel's product (rank up to 4 KQ): 16 x 16 outputs per wave while the matrix
-// is small enough that larger tiles would leave compute units idle (180 columns: 36
-// workgroups against 9), else 32 x 32.
+// The panel's product (rank up to 4 KQ): 16 x 16 outputs per wave (76 registers, six
+// workgroups per compute unit), which is the faster while S comes from the caches: rank
+// 32 on 560 columns 6.1 against 9.7 us, 1512 18.2 against 25.4, 2040 29.8 against 38.9;
+// 32 x 32, which reads the operands half as often, beyond: 3000 78 against 86 us, 5000
+// 203 against 246.  (Ranks 8 and 16 have small matrices only.)
 template <int KQ>
 static void launch_gj_update(int kp, int n_cols, int lds, const double2* S, double2* D, int ldd, const double2* T, int ldt,
                              const int32_t* piv, const int32_t* used, int c0, int qn, int col0, hipStream_t s) {
-  const bool small = (int64_t)kp * n_cols <= 512 * 512;
+  const bool small = KQ < 8 || (int64_t)kp * n_cols <= 2048 * 2048;
   const int tile = small ? 32 : 64;
-  hipLaunchKernelGGL((small ? k_gj_update<1, 1, KQ> : k_gj_update<2, 2, KQ>),
+  auto* kernel = k_gj_update<1, 1, KQ>;
+  if constexpr (KQ == 8) kernel = small ? k_gj_update<1, 1, KQ> : k_gj_update<2, 2, KQ>;
+  hipLaunchKernelGGL(kernel,
                      dim3((unsigned)((n_cols + tile - 1) / tile), (unsigned)((kp + tile - 1) / tile)), dim3(256), 0, s,
                      kp, n_cols, lds, S, D, ldd, T, ldt, piv + c0, used, c0, qn, col0);
 }
