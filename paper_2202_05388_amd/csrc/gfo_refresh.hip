@@ -286,6 +286,13 @@ struct __attribute__((aligned(16))) GjBest {
   double m;
   int row, pad;
 };
+// Orders a wave's LDS accesses before and after it across its lanes (no instruction: a
+// wave's LDS operations complete in order, this keeps the compiler to it).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
 template <int RT, int PW>
 __global__ __launch_bounds__(512) void k_gj_panel(const double2* __restrict__ S, int lds, int col0,
                                                   double2* __restrict__ T, int kp, int c0, int qn,
@@ -323,8 +330,10 @@ __global__ __launch_bounds__(512) void k_gj_panel(const double2* __restrict__ S,
     for (int q = 0; q < RT; ++q) {
 #pragma unroll
       for (int i = 0; i < PW; ++i) tile[w][er + 64 / PW * i][ec] = a[q][i];
+      wave_lds_fence();
 #pragma unroll
       for (int i = 0; i < PW; ++i) a[q][i] = tile[w][lane][i];
+      wave_lds_fence();                             // the next rows' writes
     }
   }
   __syncthreads();
@@ -422,13 +431,16 @@ __global__ __launch_bounds__(512) void k_gj_panel(const double2* __restrict__ S,
       if constexpr (kTile) tile[w][lane][col] = a[q][i];
       else if (r < kp && col < qn) T[(int64_t)r * PW + col] = a[q][i];
     }
-    if constexpr (kTile)
+    if constexpr (kTile) {
+      wave_lds_fence();
 #pragma unroll
       for (int i = 0; i < PW; ++i) {
         const int re = nt * q + 64 * w + er + 64 / PW * i;
         const double2 x = tile[w][er + 64 / PW * i][ec];
         if (re < kp && ec < qn) T[(int64_t)re * PW + ec] = x;
       }
+      wave_lds_fence();                             // the next rows' writes
+    }
   }
 }
 

@@ -63,3 +63,24 @@ def test_refresh_panel_edges(ny, nx, k, mirror):
     assert job.status() == 0
     assert _rel(G, Gd) <= tol and _rel(E, Ed) <= tol
     assert _rel(d, np.diagonal(Gd[:N])) <= tol
+
+
+@pytest.mark.parametrize("k", [600, 1100, 1600])   # two, three and four rows per thread
+def test_refresh_panels_repeat(k):
+    """The panels pass a wave's rows between its lanes through LDS: the same structure
+    gives the same bits, whatever ran before on the same buffers."""
+    import torch
+    from paper_2202_05388_amd.job import Job
+    p = W.tiny(41, 43, n_mon=5, dtype="c128")
+    job = Job(p, device="cuda:0", kmax=k)
+    job.init()
+    runs = []
+    for seed in (1, 2, 1):
+        idx = np.zeros(p.n, np.uint8)
+        idx[np.random.default_rng(seed).choice(p.n, k, replace=False)] = 1
+        job.eps_idx.copy_(torch.from_numpy(idx))
+        print(f"[case] repeat k={k}, structure {seed}", flush=True)
+        job.refresh()
+        runs.append([x.clone() for x in (job.G, job.E, job.diag64)])
+    assert job.status() == 0
+    assert all(torch.equal(a, b) for a, b in zip(runs[0], runs[2]))
