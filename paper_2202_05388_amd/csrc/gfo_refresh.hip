@@ -609,7 +609,7 @@ struct EpiG0 {
   __device__ void put(const RowAt& r, const Pixel& c, bool diag, double2 g0, double2 v) const {
     const double2 val = make_double2(g0.x + v.x, g0.y + v.y);
     G[r.base + c.p] = St<T>::from_d(val);
-    if (diag && diag64 != nullptr && r.at.p == c.p) diag64[c.p] = val;
+    if (diag && r.at.p == c.p) diag64[c.p] = val;
   }
 };
 
@@ -712,32 +712,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 // workgroup.  Bound by the FP64 matrix cores (72.6 TFLOP/s in a large library
 // product on the same card).
 //
-// M3: three real products per complex one (X = sum Ar Br, Y = sum Ai Bi, S = sum
-// (Ar + Ai)(Br + Bi); re = X - Y, im = S - X - Y), a quarter fewer matrix
-// instructions.  Its product's error is 1.4 times that of four products (against
-// long double, 70 to 900 flipped pixels), so it is taken where the result is
-// rounded to FP32, which hides both: complex64 storage, whose FP64 diagonal
-// k_rf_field computes with four.  The whole refresh at 128 x 128, 180 flipped
-// pixels, with one epilogue for all rows: M3 on 64 x 64 tiles (2 x 2 per wave, 162
-// registers, three workgroups per compute unit whose epilogues overlap other
-// products) 3.95 ms, M3 on 128 x 64 4.23, four products on 64 x 64 4.50, on 128 x 64
-// 4.60, on 128 x 128 4.74.  complex128, 96 x 131, 1509 flipped: 128 x 64 tiles (4 x 2
-// per wave) 29.3, 64 x 64 29.4, 128 x 128 29.5 ms.
+// Tiles of the main product: complex64 storage 64 x 64 (2 x 2 per wave), whose stores are
+// half as wide: the whole refresh at 128 x 128 with 180 flipped pixels 3.89 ms, 3.95 with
+// 128 x 64; at 64 x 64 with 180 0.69 and 0.73, with 1500 8.97 and 9.15 (from some 400
+// flipped pixels on at 128 x 128 128 x 64 is 1 to 2 % ahead).  complex128, 96 x 131, 1509
+// flipped: 128 x 64 (4 x 2 per wave) 29.3, 64 x 64 29.4, 128 x 128 29.5 ms, each with one
+// epilogue for all rows.
 //
 // A FP64 matrix step shares its unit with the vector instructions, so what the loads
-// and the epilogue take is added to the product.  The product alone at those two
-// sizes: 3.10 and 15.85 ms with a test of row and k per load and, in the epilogue, a
-// branch per entry between the table and the monitors' Bessel functions (each entry's
-// read waited for by itself); 2.86 and 15.0 with the loads through buffers, 2.80 and
-// 14.4 with the branch once per tile (2.03 and 13.3 for the matrix steps).
+// and the epilogue take is added to the product.  The product alone at 96 x 131: 15.85 ms
+// with a test of row and k per load and, in the epilogue, a branch per entry between
+// the table and the monitors' Bessel functions (each entry's read waited for by itself);
+// 15.0 with the loads through buffers, 14.4 with the branch once per tile (13.3 for the
+// matrix steps).
 //
-// Without M3 every accumulator takes the same instructions on the same operands in
-// the same order as in k_zgemm_f64, whatever the tile, and the epilogue covers the
-// same entries (the 64 x 64 tiles wholly below the diagonal within rows <
-// skip_below are left alone), so the results are bitwise equal.
+// Every accumulator takes the same instructions on the same operands in the same order
+// as in k_zgemm_f64, whatever the tile, and the epilogue covers the same entries (the 64 x
+// 64 tiles wholly below the diagonal within rows < skip_below are left alone), so the
+// results are bitwise equal, and those of complex64 storage are those of complex128
+// rounded once.  (Three real products per complex one, for complex64 storage alone, took
+// 0.5 ms less at 128 x 128 and 180 flipped; their products' error is 1.4 times that of four,
+// which now and then rounds an entry to another FP32 number.)
 constexpr int kZgT = 128, kZgKC = 8;
 
-template <bool BT, bool M3, int GM, int GN, int TM, int TU, typename Epi>
+template <bool BT, int GM, int GN, int TM, int TU, typename Epi>
 __global__ __launch_bounds__(GM * GN / (4 * TM * TU), 2) void k_zgemm_f64_lds(int M, int N, int K, const double2* __restrict__ A,
                                                        int64_t lda, const double2* __restrict__ B,
                                                        int64_t ldb, Epi epi, int skip_below) {
@@ -757,15 +755,11 @@ __global__ __launch_bounds__(GM * GN / (4 * TM * TU), 2) void k_zgemm_f64_lds(in
   static_assert(TM <= 4 && TU <= 4, "a wave's outputs lie in one 64 x 64 tile");
   const int ty = (tm0 + wm) >> 6, tx = (tn0 + wn) >> 6;
   const bool idle = skip_below > 0 && ty > tx && ((int64_t)ty + 1) * 64 <= skip_below;
-  // X, Y: re and im, or with M3 sum Ar Br and sum Ai Bi; S: sum (Ar + Ai)(Br + Bi)
-  f64x4 X[TM][TU], Y[TM][TU], S[M3 ? TM : 1][M3 ? TU : 1];
+  f64x4 re[TM][TU], im[TM][TU];
 #pragma unroll
   for (int t = 0; t < TM; ++t)
 #pragma unroll
-    for (int u = 0; u < TU; ++u) {
-      X[t][u] = Y[t][u] = (f64x4){0.0, 0.0, 0.0, 0.0};
-      if constexpr (M3) S[t][u] = (f64x4){0.0, 0.0, 0.0, 0.0};
-    }
+    for (int u = 0; u < TU; ++u) re[t][u] = im[t][u] = (f64x4){0.0, 0.0, 0.0, 0.0};
   // staging: thread tid moves elements tid, tid + NT, ... of each operand's chunk,
   // consecutive threads along the operand's contiguous index, through buffers that end
   // at the operand's last row, so that a load costs one scalar addition.  (A last chunk
@@ -824,15 +818,10 @@ __global__ __launch_bounds__(GM * GN / (4 * TM * TU), 2) void k_zgemm_f64_lds(in
         for (int t = 0; t < TM; ++t)
 #pragma unroll
           for (int u = 0; u < TU; ++u) {
-            X[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].x, b[u].x, X[t][u], 0, 0, 0);
-            if constexpr (M3) {
-              Y[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].y, b[u].y, Y[t][u], 0, 0, 0);
-              S[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].x + a[t].y, b[u].x + b[u].y, S[t][u], 0, 0, 0);
-            } else {
-              X[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[t].y, b[u].y, X[t][u], 0, 0, 0);
-              Y[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].x, b[u].y, Y[t][u], 0, 0, 0);
-              Y[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].y, b[u].x, Y[t][u], 0, 0, 0);
-            }
+            re[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].x, b[u].x, re[t][u], 0, 0, 0);
+            re[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[t].y, b[u].y, re[t][u], 0, 0, 0);
+            im[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].x, b[u].y, im[t][u], 0, 0, 0);
+            im[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].y, b[u].x, im[t][u], 0, 0, 0);
           }
       }
     }
@@ -841,8 +830,7 @@ __global__ __launch_bounds__(GM * GN / (4 * TM * TU), 2) void k_zgemm_f64_lds(in
   }
   if (idle) return;
   auto entry = [&](int t, int u, int e) __attribute__((always_inline)) {
-    if constexpr (M3) return make_double2(X[t][u][e] - Y[t][u][e], S[t][u][e] - X[t][u][e] - Y[t][u][e]);
-    else return make_double2(X[t][u][e], Y[t][u][e]);
+    return make_double2(re[t][u][e], im[t][u][e]);
   };
   decltype(epi.col(0)) ca[TU];
 #pragma unroll
@@ -884,31 +872,19 @@ __global__ __launch_bounds__(GM * GN / (4 * TM * TU), 2) void k_zgemm_f64_lds(in
 
 // E = Einc + Z x with x = Einc[V] (Z = U M), one wave per row.  (As x = M Einc[V]
 // and then U x, one thread per row each, the two took 0.8 ms at 1500 flipped
-// pixels.)  DIAG: also diag64[r] = G0[r, r] + Z[r, :] U[r, :] of the design rows.
-template <typename T, bool DIAG>
+// pixels.)
+template <typename T>
 __global__ __launch_bounds__(256) void k_rf_field(Geo g, const double* __restrict__ mon_xy,
-                                                  const double2* __restrict__ table,
-                                                  const double2* __restrict__ Z, const double2* __restrict__ U,
-                                                  const double2* __restrict__ x, int k, int kp, T* __restrict__ E,
-                                                  double2* __restrict__ diag64) {
+                                                  const double2* __restrict__ Z, const double2* __restrict__ x,
+                                                  int k, int kp, T* __restrict__ E) {
   const int r = blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (r >= g.R) return;
-  double2 s = make_double2(0.0, 0.0), d = s;
+  double2 s = make_double2(0.0, 0.0);
 #pragma unroll 4
-  for (int i = lane; i < k; i += 64) {
-    const double2 z = Z[(int64_t)r * kp + i];
-    s = cadd(s, cmul(z, x[i]));
-    if (DIAG && r < g.N) d = cadd(d, cmul(z, U[(int64_t)r * kp + i]));
-  }
+  for (int i = lane; i < k; i += 64) s = cadd(s, cmul(Z[(int64_t)r * kp + i], x[i]));
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    s = cadd(s, make_double2(__shfl_xor(s.x, o, 64), __shfl_xor(s.y, o, 64)));
-    if (DIAG) d = cadd(d, make_double2(__shfl_xor(d.x, o, 64), __shfl_xor(d.y, o, 64)));
-  }
-  if (lane == 0) {
-    E[r] = St<T>::from_d(cadd(incident(g, mon_xy, r), s));
-    if (DIAG && r < g.N) diag64[r] = cadd(table[0], d);
-  }
+  for (int o = 32; o > 0; o >>= 1) s = cadd(s, make_double2(__shfl_xor(s.x, o, 64), __shfl_xor(s.y, o, 64)));
+  if (lane == 0) E[r] = St<T>::from_d(cadd(incident(g, mon_xy, r), s));
 }
 
 // Flipped list V (in the workspace) and its length k, read back to the host
@@ -1024,27 +1000,24 @@ static int refresh_typed(const Geo& g, gfo_state* st, const Layout& L, int32_t k
     // them the 64 x 64 kernel fills the chip better
     const int zx = (kp + kZgT - 1) / kZgT, zy = (g.R + kZgT - 1) / kZgT;
     if ((int64_t)zx * zy >= 1024)
-      hipLaunchKernelGGL((k_zgemm_f64_lds<false, false, kZgT, kZgT, 4, 2, EpiStoreZ>), dim3(zx, zy), dim3(512), 0, s, g.R, kp, kp,
+      hipLaunchKernelGGL((k_zgemm_f64_lds<false, kZgT, kZgT, 4, 2, EpiStoreZ>), dim3(zx, zy), dim3(512), 0, s, g.R, kp, kp,
                          (const double2*)U, (int64_t)kp, (const double2*)M, (int64_t)kp, ez, 0);
     else
       hipLaunchKernelGGL((k_zgemm_f64<false, false, EpiStoreZ>), dim3((kp + 63) / 64, (g.R + 63) / 64), dim3(256), 0, s,
                          g.R, kp, kp, (const double2*)U, (int64_t)kp, (const double2*)M, (int64_t)kp,
                          (const int32_t*)nullptr, ez, 0);
   }
-  hipLaunchKernelGGL((k_rf_field<T, std::is_same<T, float2>::value>), dim3((unsigned)((g.R + 3) / 4)), dim3(256), 0, s,
-                     g, mon, table, (const double2*)Z, (const double2*)U, (const double2*)x, k, kp, (T*)st->E,
-                     (double2*)st->diag64);
+  hipLaunchKernelGGL(k_rf_field<T>, dim3((unsigned)((g.R + 3) / 4)), dim3(256), 0, s, g, mon, (const double2*)Z,
+                     (const double2*)x, k, kp, (T*)st->E);
   // G = G0 + Z U_D^T over the N design columns (padding columns stay zero):
   // the monitor rows whole and the design block on and above its diagonal (the
   // block is symmetric); when the caller keeps the whole block, its lower
   // triangle is then the mirror of the upper one (half the product's work)
-  EpiG0<T> eg{g, table, mon, (T*)st->G, g.dtype == GFO_C64 ? nullptr : (double2*)st->diag64, 1.0f / (float)g.nx};
-  // complex64: three real products per complex one (the result is rounded to FP32
-  // once, and diag64 comes from k_rf_field); complex128: four
+  EpiG0<T> eg{g, table, mon, (T*)st->G, (double2*)st->diag64, 1.0f / (float)g.nx};
   constexpr bool c64 = std::is_same<T, float2>::value;
   constexpr int GM = c64 ? 64 : 128, GN = 64, TM = c64 ? 2 : 4, TU = 2;
   const int ty = (g.R + GM - 1) / GM, tx = (g.N + GN - 1) / GN;
-  hipLaunchKernelGGL((k_zgemm_f64_lds<true, c64, GM, GN, TM, TU, EpiG0<T>>),
+  hipLaunchKernelGGL((k_zgemm_f64_lds<true, GM, GN, TM, TU, EpiG0<T>>),
                      dim3((unsigned)ut_group_count(ty, tx, g.N / GM, GM, GN)), dim3(GM * GN / (4 * TM * TU)), 0, s,
                      g.R, g.N, kp, (const double2*)Z, (int64_t)kp, (const double2*)U, (int64_t)kp, eg, g.N);
   if (note_hip(hipGetLastError()) != hipSuccess) return GFO_EHIP;

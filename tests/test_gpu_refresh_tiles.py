@@ -41,3 +41,26 @@ def test_refresh_tiles(dtype, ny, nx, n_mon, flips, kw):
     assert rel_elem(G, Gd) <= tol and rel_elem(E, Ed) <= tol
     assert rel_elem(d, np.diagonal(Gd[:p.n])) <= tol64
     assert np.array_equal(idx, idx2) and job.status() == 0
+
+
+@pytest.mark.parametrize("ny,nx,n_mon,flips", [(64, 64, 33, 180), (83, 77, 5, 300)])
+def test_c64_refresh_is_c128_rounded_once(ny, nx, n_mon, flips):
+    """The refresh computes in FP64 with the same instructions for either storage type:
+    complex64 storage holds the complex128 result rounded once, entry for entry, and the
+    same FP64 diagonal."""
+    import torch
+    from paper_2202_05388_amd.job import Job
+    print(f"[case] {ny}x{nx} n_mon {n_mon} {flips} flipped", flush=True)
+    idx = np.zeros(ny * nx, np.uint8)
+    idx[np.random.default_rng(flips).choice(ny * nx, flips, replace=False)] = 1
+    jobs = []
+    for dtype in ("c128", "c64"):
+        job = Job(W.tiny(ny, nx, n_mon=n_mon, dtype=dtype), device="cuda:0", kmax=flips)
+        job.init()
+        job.eps_idx.copy_(torch.from_numpy(idx))
+        job.refresh()
+        jobs.append(job)
+    a, b = jobs
+    assert torch.equal(a.diag64, b.diag64)
+    assert torch.equal(a.E.to(torch.complex64), b.E)
+    assert int((a.G.to(torch.complex64) != b.G).sum()) == 0
