@@ -92,7 +92,9 @@ typedef struct {
   int32_t kmax;                 /* largest flipped set refresh_G supports */
   void* work; size_t work_bytes;/* scratch, at least gfo_workspace_size() bytes, 256-B aligned */
   int32_t* status;              /* 1 int32 device status word (GFO_STATUS_* bits) */
-  int32_t delay;                /* 0: eager rank-1 updates; 1..GFO_MAX_DELAY: deferred (see apply_flip) */
+  int32_t delay;                /* 0: eager rank-1 updates; 1..GFO_MAX_DELAY: deferred (see apply_flip),
+                                   for fewer than 2^21 rows (and ldG) of GFO_C64 storage, 2^20
+                                   of GFO_C128 (terabytes of G), else GFO_EINVAL */
   int32_t pending_calls;        /* host counter kept by the library; set 0 before init_G0 */
   int32_t lower_stale;          /* host flag kept by the library: 1 while the strict lower
                                    triangle of the design block is out of date (see

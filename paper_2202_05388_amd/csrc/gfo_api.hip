@@ -125,6 +125,11 @@ int validate_state_fields(const gfo_problem* p, const gfo_state* st) {
   if (st->packed != 0 && st->packed != 1) return GFO_EINVAL;
   if (st->packed && st->delay == 0) return GFO_EINVAL;
   if (st->ldG < min_ld(p) || st->ldG % 64 != 0) return GFO_EINVAL;
+  // deferred mode addresses the term buffers, the tiles of G and their parts with 32-bit
+  // byte offsets (checked here for every kernel of it: two million complex64 rows, one
+  // million complex128, whose G takes terabytes)
+  const int64_t rows = (int64_t)p->ny * p->nx + p->n_mon, span = rows > st->ldG ? rows : st->ldG;
+  if (st->delay > 0 && span >= ((int64_t)1 << 31) / (GFO_MAX_DELAY * (p->dtype == GFO_C64 ? 8 : 16))) return GFO_EINVAL;
   if (((uintptr_t)st->G & 15) != 0) return GFO_EINVAL;
   return GFO_OK;
 }

@@ -1243,15 +1243,7 @@ hipError_t launch_flush(const Geo& g, gfo_state* st, const Layout& L, hipStream_
     if (hipError_t er = record_event(before, s)) return note_hip(er);
     int fv = flush_get_variant();
     bool monitors_done = false;
-    // the pair and band forms address the term buffers with 32-bit byte offsets
-    const bool off32 = (int64_t)GFO_MAX_DELAY * (g.ld > g.R ? g.ld : g.R) * 8 < ((int64_t)1 << 31);
-    if (fv >= 1 && !off32) fv = 0;
-    // band-packed storage: the pair and band forms only (they address tiles
-    // through tile_at); sizes beyond their 32-bit offsets are refused
-    if (g.packed) {
-      if (!off32) return note_hip(hipErrorInvalidValue);
-      if (fv == 0) fv = 1;
-    }
+    if (g.packed && fv == 0) fv = 1;   // band-packed storage: the forms that address tiles through tile_at
     const float2* cu = (const float2*)(w + L.dl_CUs);
     const float2* vv = (const float2*)(w + L.dl_Vs);
     float2* G = (float2*)st->G;

@@ -275,3 +275,19 @@ def test_one_hip_runtime_when_the_library_loads_first():
     r = subprocess.run([sys.executable, "-c", script], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stderr[-2000:]
     assert r.stdout.strip().splitlines()[-1] == "1"
+
+
+@pytest.mark.parametrize("dtype,ny,small", [("c64", 2200, 2000), ("c128", 1100, 1000)])
+def test_deferred_mode_refuses_rows_beyond_its_offsets(dtype, ny, small):
+    """Deferred mode addresses its term buffers with 32-bit byte offsets: a state of more
+    rows is refused; in eager mode, and with fewer rows, the next check (the workspace's
+    size) answers.  Host checks only."""
+    lib = L.lib()
+    fake = 1 << 20
+    for rows, delay, rc in ((ny, 16, L.GFO_EINVAL), (ny, 0, L.GFO_ENOSPC), (small, 16, L.GFO_ENOSPC)):
+        pr, keep = _problem(W.tiny(rows, 1000), L.GFO_C64 if dtype == "c64" else L.GFO_C128)
+        st = L.State(G=fake, ldG=L.min_ld(pr), E=fake, diag64=fake, eps_idx=fake, flips=fake, flip_cap=4,
+                     n_flips=fake, kmax=0, work=fake, work_bytes=16, status=fake, delay=delay)
+        assert lib.init_G0(C.byref(pr), C.byref(st), None) == rc
+        assert lib.gfo_flush(C.byref(pr), C.byref(st), None) == rc
+        assert lib.score_regions(C.byref(pr), C.byref(st), 2, 3, 1e-9, C.c_void_p(256), None) == rc
