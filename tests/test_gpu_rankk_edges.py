@@ -107,3 +107,11 @@ def test_records_of_32_with_repeats():
     assert [tuple(x) for x in a.history()] == counted
     for x, y in zip(a.host_state(), b.host_state()):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("n_eps", [3, 4, 5, 7])
+def test_topk_selection_materials(n_eps):
+    """A kernel for each of two, three and four materials, one for more (its loads clamped
+    to the table's last entry)."""
+    test_topk_selection_edges(21, 37, n_eps, 14, 4, 1e-9)
+    test_topk_selection_edges(21, 37, n_eps, 9, 3, 0.02)
