@@ -28,6 +28,66 @@ __device__ __forceinline__ double2 cdiv(double2 a, double2 b) {
   return make_double2((a.x * b.x + a.y * b.y) / n, (a.y * b.x - a.x * b.y) / n);
 }
 
+// E'_m0 - E_m0 of a region move: the system of one material solved in FP64 by Gaussian
+// elimination with partial pivoting; b = 0 where a pixel already has the material.
+__device__ __forceinline__ double2 region_field(const double (&b)[kRegionPix], const double2 (&Gvv)[kRegionPix][kRegionPix],
+                                                const double2 (&EV)[kRegionPix], const double2 (&gm)[kRegionPix]) {
+  // A = I - G_VV B, augmented with E_V
+  double2 A[kRegionPix][kRegionPix + 1];
+#pragma unroll
+  for (int i = 0; i < kRegionPix; ++i) {
+#pragma unroll
+    for (int j = 0; j < kRegionPix; ++j)
+      A[i][j] = make_double2((i == j ? 1.0 : 0.0) - Gvv[i][j].x * b[j], -Gvv[i][j].y * b[j]);
+    A[i][kRegionPix] = EV[i];
+  }
+#pragma unroll
+  for (int c = 0; c < kRegionPix; ++c) {
+    int piv = c;
+    double pmax = cabs2(A[c][c]);
+#pragma unroll
+    for (int r = c + 1; r < kRegionPix; ++r) {
+      const double m = cabs2(A[r][c]);
+      if (m > pmax) {
+        pmax = m;
+        piv = r;
+      }
+    }
+    if (piv != c) {
+#pragma unroll
+      for (int j = 0; j <= kRegionPix; ++j) {
+        // swap rows c and piv without dynamic register indexing
+#pragma unroll
+        for (int r = c + 1; r < kRegionPix; ++r) {
+          if (r == piv) {
+            const double2 t = A[c][j];
+            A[c][j] = A[r][j];
+            A[r][j] = t;
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int r = c + 1; r < kRegionPix; ++r) {
+      const double2 f = cdiv(A[r][c], A[c][c]);
+#pragma unroll
+      for (int j = c; j <= kRegionPix; ++j) A[r][j] = cadd(A[r][j], cmul(make_double2(-f.x, -f.y), A[c][j]));
+    }
+  }
+  double2 x[kRegionPix];
+#pragma unroll
+  for (int i = kRegionPix - 1; i >= 0; --i) {
+    double2 acc = A[i][kRegionPix];
+#pragma unroll
+    for (int j = i + 1; j < kRegionPix; ++j) acc = cadd(acc, cmul(make_double2(-A[i][j].x, -A[i][j].y), x[j]));
+    x[i] = cdiv(acc, A[i][i]);
+  }
+  double2 d = make_double2(0.0, 0.0);
+#pragma unroll
+  for (int i = 0; i < kRegionPix; ++i) d = cadd(d, cmul(gm[i], cscale(b[i], x[i])));
+  return d;
+}
+
 // Scores of 16 regions at a time, on 12 x 16 threads.  Thread (w, r) sums one
 // off-diagonal entry (i, j) of the 4 x 4 block of G of region r: the entry read from G,
 // plus, in deferred mode, the `count` pending terms cu_s[p] v_s[q] in term order (the
@@ -39,6 +99,7 @@ __device__ __forceinline__ double2 cdiv(double2 a, double2 b) {
 // a compute unit keeps few lines of them in flight, so the regions are spread over all:
 // 4096 regions, 0 to 60 pending terms, 11.1 us (64 regions a workgroup with 12 entry
 // waves 15.9, with a wave per row 15.1; a thread per region, 16 workgroups, 20.8 us).
+// Few terms or many regions: k_score_regions_1.
 constexpr int kRegionLanes = 16;
 constexpr int kRegionWaves = kRegionPix * (kRegionPix - 1);
 constexpr int kRegionThreads = kRegionLanes * kRegionWaves;
@@ -127,60 +188,7 @@ __global__ __launch_bounds__(kRegionThreads) void k_score_regions(
         for (int i = 0; i < kRegionPix; ++i)
 #pragma unroll
           for (int j = 0; j < kRegionPix; ++j) Gvv[i][j] = Gs[i][j][lane];
-        // A = I - G_VV B, augmented with E_V
-        double2 A[kRegionPix][kRegionPix + 1];
-#pragma unroll
-        for (int i = 0; i < kRegionPix; ++i) {
-#pragma unroll
-          for (int j = 0; j < kRegionPix; ++j)
-            A[i][j] = make_double2((i == j ? 1.0 : 0.0) - Gvv[i][j].x * b[j], -Gvv[i][j].y * b[j]);
-          A[i][kRegionPix] = EV[i];
-        }
-#pragma unroll
-        for (int c = 0; c < kRegionPix; ++c) {
-          int piv = c;
-          double pmax = cabs2(A[c][c]);
-#pragma unroll
-          for (int r = c + 1; r < kRegionPix; ++r) {
-            const double m = cabs2(A[r][c]);
-            if (m > pmax) {
-              pmax = m;
-              piv = r;
-            }
-          }
-          if (piv != c) {
-#pragma unroll
-            for (int j = 0; j <= kRegionPix; ++j) {
-              // swap rows c and piv without dynamic register indexing
-#pragma unroll
-              for (int r = c + 1; r < kRegionPix; ++r) {
-                if (r == piv) {
-                  const double2 t = A[c][j];
-                  A[c][j] = A[r][j];
-                  A[r][j] = t;
-                }
-              }
-            }
-          }
-#pragma unroll
-          for (int r = c + 1; r < kRegionPix; ++r) {
-            const double2 f = cdiv(A[r][c], A[c][c]);
-#pragma unroll
-            for (int j = c; j <= kRegionPix; ++j) A[r][j] = cadd(A[r][j], cmul(make_double2(-f.x, -f.y), A[c][j]));
-          }
-        }
-        double2 x[kRegionPix];
-#pragma unroll
-        for (int i = kRegionPix - 1; i >= 0; --i) {
-          double2 acc = A[i][kRegionPix];
-#pragma unroll
-          for (int j = i + 1; j < kRegionPix; ++j) acc = cadd(acc, cmul(make_double2(-A[i][j].x, -A[i][j].y), x[j]));
-          x[i] = cdiv(acc, A[i][i]);
-        }
-        double2 d = make_double2(0.0, 0.0);
-#pragma unroll
-        for (int i = 0; i < kRegionPix; ++i) d = cadd(d, cmul(gm[i], cscale(b[i], x[i])));
-        Fe = cabs2(cadd(Em0, d));
+        Fe = cabs2(cadd(Em0, region_field(b, Gvv, EV, gm)));
         if (!isfinite(Fe)) {
           bad = true;
           Fe = -INFINITY;
@@ -208,6 +216,95 @@ __global__ __launch_bounds__(kRegionThreads) void k_score_regions(
   if (bad) atomicOr(status, GFO_STATUS_NONFINITE);
 }
 
+// The same scores (and bits) with a thread per region: an eighth of the reads' instructions
+// and no exchange, where the regions alone fill the chip or there are few terms to read
+// (region_per_thread).  Workgroup b covers the regions [256 b, 256 b + 256).
+// NE: 2 when the table has two entries, else GFO_MAX_EPS.
+template <typename T, int NE>
+__global__ __launch_bounds__(kScoreThreads) void k_score_regions_1(
+    Geo g, int n_regions, const T* __restrict__ G, const T* __restrict__ E,
+    const double2* __restrict__ diag64, const uint8_t* __restrict__ eps_idx,
+    const int32_t* __restrict__ count, const T* __restrict__ CUs, const T* __restrict__ Vs,
+    uint32_t mask, double tau, double* __restrict__ scores, double* __restrict__ partial,
+    int* __restrict__ pfirst, int32_t* __restrict__ status) {
+  __shared__ double sh[kScoreThreads / 64];
+  __shared__ int shi[kScoreThreads / 64];
+  const int k = blockIdx.x * kScoreThreads + threadIdx.x;
+  double best = -INFINITY, F[NE];
+  bool bad = false;
+  if (k < n_regions) {
+    int V[kRegionPix], cur[kRegionPix];
+    region_pixels(g, k, V);
+    double2 Gvv[kRegionPix][kRegionPix], EV[kRegionPix], gm[kRegionPix];
+    const T* __restrict__ grow = G + g_off(g, g.N + g.m0, 0);
+#pragma unroll
+    for (int i = 0; i < kRegionPix; ++i) {
+      cur[i] = eps_idx[V[i]];
+      EV[i] = St<T>::to_d(E[V[i]]);
+      gm[i] = St<T>::to_d(grow[V[i]]);
+#pragma unroll
+      for (int j = 0; j < kRegionPix; ++j)
+        Gvv[i][j] = i == j ? diag64[V[i]] : St<T>::to_d(G[g_at(g, V[i], V[j])]);
+    }
+    const int K = count ? *count : 0;
+    // terms in groups of kTermBatch, every load of a group issued before its first use
+    constexpr int kTermBatch = 4;
+    for (int s0 = 0; s0 < K; s0 += kTermBatch) {
+      T cu[kTermBatch][kRegionPix], v[kTermBatch][kRegionPix];
+#pragma unroll
+      for (int u = 0; u < kTermBatch; ++u)
+#pragma unroll
+        for (int i = 0; i < kRegionPix; ++i)
+          if (s0 + u < K) {
+            cu[u][i] = CUs[(int64_t)(s0 + u) * g.R + V[i]];
+            v[u][i] = Vs[(int64_t)(s0 + u) * g.ld + V[i]];
+          }
+#pragma unroll
+      for (int u = 0; u < kTermBatch; ++u) {
+        if (s0 + u >= K) break;
+#pragma unroll
+        for (int i = 0; i < kRegionPix; ++i)
+#pragma unroll
+          for (int j = 0; j < kRegionPix; ++j)
+            if (i != j) Gvv[i][j] = cadd(Gvv[i][j], cmul(St<T>::to_d(cu[u][i]), St<T>::to_d(v[u][j])));
+      }
+    }
+    const double2 Em0 = St<T>::to_d(E[g.N + g.m0]);
+    double eps_cur[kRegionPix];
+#pragma unroll
+    for (int i = 0; i < kRegionPix; ++i) eps_cur[i] = eps_of<NE>(g, cur[i]);
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+      F[e] = -INFINITY;
+      if (NE > 2 && e >= g.n_eps) continue;
+      bool changes = false;
+#pragma unroll
+      for (int i = 0; i < kRegionPix; ++i) changes |= cur[i] != e;
+      if (((mask >> e) & 1u) && changes) {
+        double b[kRegionPix];
+#pragma unroll
+        for (int i = 0; i < kRegionPix; ++i) b[i] = g.k0sq * (g.eps[e] - eps_cur[i]);
+        F[e] = cabs2(cadd(Em0, region_field(b, Gvv, EV, gm)));
+        if (!isfinite(F[e])) {
+          bad = true;
+          F[e] = -INFINITY;
+        }
+        best = fmax(best, F[e]);
+      }
+      scores[(int64_t)k * g.n_eps + e] = F[e];
+    }
+  }
+  const double bb = block_max(best, sh);
+  int f = 0x7fffffff;
+  if (bb > -INFINITY && k < n_regions) f = first_at_least<NE>(g, k, F, tie_threshold(bb, tau));
+  f = block_min(f, shi);
+  if (threadIdx.x == 0) {
+    partial[blockIdx.x] = bb;
+    pfirst[blockIdx.x] = f;
+  }
+  if (bad) atomicOr(status, GFO_STATUS_NONFINITE);
+}
+
 // Regions per workgroup of the scores, in 16s: one, or what keeps the workgroups
 // within the summaries (more than 16384 regions).
 static int region_span(int n_regions) {
@@ -221,13 +318,13 @@ __global__ __launch_bounds__(256) void k_region_pick(Geo g, int n_regions, const
                                                     const double* __restrict__ scores,
                                                     const double* __restrict__ partial,
                                                     const int* __restrict__ pfirst, double tau,
-                                                    gfo_pick* __restrict__ out, int per) {
+                                                    gfo_pick* __restrict__ out, int span) {
   __shared__ double shd[4];
   __shared__ int shi[4];
   Geo gr = g;
   gr.N = n_regions;
   const double fom = cabs2(St<T>::to_d(E[g.N + g.m0]));
-  const int span = kRegionLanes * per, nblk = (n_regions + span - 1) / span;
+  const int nblk = (n_regions + span - 1) / span;
   const gfo_pick pk = greedy_pick_block(gr, fom, scores, partial, pfirst, nblk, tau, shd, shi, span);
   if (threadIdx.x == 0) *out = pk;
 }
@@ -259,34 +356,49 @@ __global__ void k_region_pixels(Geo g, const gfo_pick* __restrict__ region,
 
 int region_side() { return kRegion; }
 
-hipError_t launch_score_regions(const Geo& g, const gfo_state* st, const Layout& L, uint32_t mask,
-                                double tau, gfo_pick* out, hipStream_t s) {
+// The thread-per-region form, where it measured faster: its time does not grow with the
+// regions up to 16384 (fewer than one per thread of the chip), so few terms decide there
+// (complex64, two materials: 72 x 72 regions, one term 10.9 against 13.0 us; 128 x 128, 5
+// terms 12.4 against 17.5, 60 terms 35.2 against 26.4), fewer for complex128, whose terms
+// it reads in twice the lines; with eight materials a thread solves eight systems and it is
+// no faster (18.3 against 17.6).  Beyond, the other form's workgroups take several
+// sixteens each (200 x 200, 40 terms: 31.0 against 53.7 us).
+static bool region_per_thread(int n_regions, int pending, int n_eps, bool c64) {
+  if (n_regions > 24576) return true;
+  if (n_regions > 16 * kScoreMaxBlocks) return 100 * (n_eps + 1) * pending <= n_regions;
+  return n_eps <= 3 && n_regions > 4096 && (c64 ? 800 : 2400) * pending <= n_regions;
+}
+
+template <typename T>
+static hipError_t score_regions_typed(const Geo& g, const gfo_state* st, const Layout& L, uint32_t mask, double tau,
+                                      gfo_pick* out, hipStream_t s) {
   char* w = (char*)st->work;
   const int n_regions = (g.ny / kRegion) * (g.nx / kRegion);
-  const int per = region_span(n_regions);
-  const int nblk = (n_regions + kRegionLanes * per - 1) / (kRegionLanes * per);
+  const bool one = region_per_thread(n_regions, st->delay > 0 ? st->pending_calls : 0, g.n_eps, sizeof(T) == 8);
+  const int per = region_span(n_regions), span = one ? kScoreThreads : kRegionLanes * per;
+  const int nblk = (n_regions + span - 1) / span;
   const int32_t* count = st->delay > 0 ? (const int32_t*)(w + L.dl_hdr) : nullptr;
+  const T *G = (const T*)st->G, *E = (const T*)st->E, *CUs = (const T*)(w + L.dl_CUs), *Vs = (const T*)(w + L.dl_Vs);
+  const double2* diag64 = (const double2*)st->diag64;
   double* scores = (double*)(w + L.scores);
   double* partial = (double*)(w + L.partial);
   int* pfirst = (int*)(w + L.pfirst);
-  if (g.dtype == GFO_C64) {
-    hipLaunchKernelGGL(k_score_regions<float2>, dim3(nblk), dim3(kRegionThreads), 0, s, g, n_regions,
-                       (const float2*)st->G, (const float2*)st->E, (const double2*)st->diag64,
-                       (const uint8_t*)st->eps_idx, count, (const float2*)(w + L.dl_CUs),
-                       (const float2*)(w + L.dl_Vs), mask, tau, scores, partial, pfirst, st->status, per);
-    hipLaunchKernelGGL(k_region_pick<float2>, dim3(1), dim3(256), 0, s, g, n_regions,
-                       (const float2*)st->E, (const double*)scores, (const double*)partial,
-                       (const int*)pfirst, tau, out, per);
-  } else {
-    hipLaunchKernelGGL(k_score_regions<double2>, dim3(nblk), dim3(kRegionThreads), 0, s, g, n_regions,
-                       (const double2*)st->G, (const double2*)st->E, (const double2*)st->diag64,
-                       (const uint8_t*)st->eps_idx, count, (const double2*)(w + L.dl_CUs),
-                       (const double2*)(w + L.dl_Vs), mask, tau, scores, partial, pfirst, st->status, per);
-    hipLaunchKernelGGL(k_region_pick<double2>, dim3(1), dim3(256), 0, s, g, n_regions,
-                       (const double2*)st->E, (const double*)scores, (const double*)partial,
-                       (const int*)pfirst, tau, out, per);
-  }
+  if (one)
+    hipLaunchKernelGGL((g.n_eps == 2 ? k_score_regions_1<T, 2> : k_score_regions_1<T, GFO_MAX_EPS>), dim3(nblk),
+                       dim3(kScoreThreads), 0, s, g, n_regions, G, E, diag64,
+                       (const uint8_t*)st->eps_idx, count, CUs, Vs, mask, tau, scores, partial, pfirst, st->status);
+  else
+    hipLaunchKernelGGL(k_score_regions<T>, dim3(nblk), dim3(kRegionThreads), 0, s, g, n_regions, G, E, diag64,
+                       (const uint8_t*)st->eps_idx, count, CUs, Vs, mask, tau, scores, partial, pfirst, st->status, per);
+  hipLaunchKernelGGL(k_region_pick<T>, dim3(1), dim3(one ? 64 : 256), 0, s, g, n_regions, E, (const double*)scores,
+                     (const double*)partial, (const int*)pfirst, tau, out, span);
   return note_hip(hipGetLastError());
+}
+
+hipError_t launch_score_regions(const Geo& g, const gfo_state* st, const Layout& L, uint32_t mask,
+                                double tau, gfo_pick* out, hipStream_t s) {
+  if (g.dtype == GFO_C64) return score_regions_typed<float2>(g, st, L, mask, tau, out, s);
+  return score_regions_typed<double2>(g, st, L, mask, tau, out, s);
 }
 
 hipError_t launch_region_pixels(const Geo& g, const gfo_state* st, const gfo_pick* region,
