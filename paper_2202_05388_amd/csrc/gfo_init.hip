@@ -12,6 +12,7 @@
 
 #include <algorithm>
 #include <type_traits>
+#include <utility>
 
 namespace gfo {
 
@@ -40,22 +41,25 @@ __device__ __forceinline__ double2 self_term(const Geo& g) {
 // rows' reads are in flight together.  With `upper`, stores that lie wholly below the
 // diagonal are skipped (the caller marks the lower triangle out of date), and the
 // column blocks of segment y and of the last but y share one line of workgroups, so
-// that none starts without work: their waves' launch bounds this form.
+// that none starts without work: their waves' launch bounds this form.  The whole matrix
+// is written in the order of its rows (`lines`: the lines of workgroups).
 // 128 x 128 complex64, the 1.08 GB upper triangle: 185 us; 235 with a line of
 // workgroups per segment, half of them idle (16 rows per workgroup: 262, 2: 278, one
 // row in address order: 300; a form whose workgroups took every 2048th row, with the
-// divisions and products of each entry's address: 243).  The whole 2.15 GB: 335 us.
+// divisions and products of each entry's address: 243).  The whole 2.15 GB: 329 us, 350 in
+// pairs of segments as well (complex128 671 and 713).  One time in two processes differs by
+// up to a tenth, as the memory lies elsewhere.
 constexpr int kFillRows = 4;
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_fill_design(Geo g, T* __restrict__ G, const double2* __restrict__ table,
-                                                     int upper, int nseg, int ncb) {
+                                                     int upper, int nseg, int ncb, int lines) {
   constexpr int VN = 16 / (int)sizeof(T);
   const int Y = g.ny * nseg;          // segments
   // first row of a segment; the first column block that reaches the diagonal there
   auto row0 = [&](int y) { return y / nseg * g.nx + y % nseg * kFillRows; };
   auto block0 = [&](int y) { return upper ? row0(y) / (256 * VN) : 0; };
-  for (int yy = (int)blockIdx.y; 2 * yy < Y; yy += (int)gridDim.y) {
+  for (int yy = (int)blockIdx.y; yy < lines; yy += (int)gridDim.y) {
     int y = yy, bx = block0(y) + (int)blockIdx.x;
     if (bx >= ncb) {
       y = Y - 1 - yy;
@@ -200,17 +204,21 @@ static hipError_t init_typed(const Geo& g, gfo_state* st, const Layout& L, const
     rest(MonArgs<false>{});
   }
   constexpr int VN = 16 / (int)sizeof(T);
-  const int nseg = (g.nx + kFillRows - 1) / kFillRows;
-  const int64_t Y = (int64_t)g.ny * nseg, ncb = (g.ld + 256 * VN - 1) / (256 * VN);
+  // a grid of one column is filled as one of one row (its table is the same list of
+  // offsets), whose segments have kFillRows rows
+  Geo gf = g;
+  if (g.nx == 1) std::swap(gf.ny, gf.nx);
+  const int nseg = (gf.nx + kFillRows - 1) / kFillRows;
+  const int64_t Y = (int64_t)gf.ny * nseg, ncb = (g.ld + 256 * VN - 1) / (256 * VN);
   // the column blocks of segments y and Y - 1 - y: their first rows add up to the same
-  // for every y, so at most this many
-  const int64_t sum = (int64_t)(g.ny - 1) * g.nx + (int64_t)(nseg - 1) * kFillRows;
-  const int64_t gx = g.upper ? 2 * ncb - sum / (256 * VN) + 1 : 2 * ncb;
+  // for every y, so at most this many; the whole matrix is written in the order of its rows
+  const int64_t sum = (int64_t)(gf.ny - 1) * gf.nx + (int64_t)(nseg - 1) * kFillRows;
+  const int64_t gx = g.upper ? 2 * ncb - sum / (256 * VN) + 1 : ncb, lines = g.upper ? (Y + 1) / 2 : Y;
   // narrow or very large grids: the workgroups walk the segments (at most 65535 of them
   // over the segments, and 2^31 work-items in the launch)
-  const int64_t gy = std::min({(Y + 1) / 2, (int64_t)65535, std::max<int64_t>(1, ((int64_t)1 << 31) / (gx * 256))});
-  hipLaunchKernelGGL(k_fill_design<T>, dim3((unsigned)gx, (unsigned)gy), dim3(256), 0, s, g, G,
-                     (const double2*)table, g.upper, nseg, (int)ncb);
+  const int64_t gy = std::min({lines, (int64_t)65535, std::max<int64_t>(1, ((int64_t)1 << 31) / (gx * 256))});
+  hipLaunchKernelGGL(k_fill_design<T>, dim3((unsigned)gx, (unsigned)gy), dim3(256), 0, s, gf, G,
+                     (const double2*)table, g.upper, nseg, (int)ncb, (int)lines);
   return note_hip(hipGetLastError());
 }
 

@@ -67,3 +67,41 @@ def test_monitor_counts(dtype, n_mon):
     G, E, _, _ = job.host_state()
     Gd, Ed = ost.dense_state(p, ost.eps_of(p, idx))
     assert rel_elem(G, Gd) <= tol and rel_elem(E, Ed) <= tol and job.status() == 0
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("ny,nx", [(1, 1025), (257, 1), (513, 1), (2, 511), (3, 171), (512, 2)])
+@pytest.mark.parametrize("kw", [{}, {"delay": 16}, {"delay": 16, "packed": True}])
+def test_fill_block_edges(dtype, ny, nx, kw):
+    """Around the ends of a workgroup's columns (complex64 512, complex128 256), and a grid
+    of one column (filled as one of one row).  Tolerance as above."""
+    from paper_2202_05388_amd.job import Job
+    p = W.tiny(ny, nx, n_mon=2, dtype=dtype)
+    print(f"[case] {ny}x{nx} {dtype} {kw}", flush=True)
+    job = Job(p, device="cuda:0", **kw)
+    job.init()
+    assert rel_elem(job.host_state()[0], greens.build_G0(p)) <= (1e-11 if dtype == "c128" else 2e-7)
+
+
+def test_fill_walks_the_segments():
+    """53,334 rows of three pixels, band-packed (102 GB): more pairs of segments than the
+    launch has lines of workgroups.  G[p, q] of pixels the same distance apart comes from the
+    same table entry: equal bits."""
+    import torch
+    from paper_2202_05388_amd.job import Job
+    p = W.tiny(53334, 3, n_mon=1, dtype="c64")
+    torch.cuda.empty_cache()
+    job = Job(p, device="cuda:0", delay=16, packed=True)
+    job.init()
+    torch.cuda.synchronize()
+    bands = job._bands()
+
+    def row(r, n):                       # entries [r, r + n) of design row r
+        r0, _, c0, off, stride = bands[r // 64]
+        at = off + (r - r0) * stride + r - c0
+        return job.G[at: at + n]
+    N = p.n
+    for iy in (0, 1, 2, 12345, 26626, 26627, 26666, 26667, 26668, 26706, 26707, 40000, 53332, 53333):
+        for ix in range(3):
+            n = N - 3 * iy - ix
+            assert torch.equal(row(3 * iy + ix, n), row(ix, n)), (iy, ix)
