@@ -1233,6 +1233,22 @@ static int band_workgroups(int per_cu = 2) {
   return n < 8 ? 8 : n;
 }
 
+// Whether a complex128 flush of at most `bound` terms takes the tiled product (k_zgemm_f64,
+// a workgroup per tile, same bits) and not k_flush_c128, by the tiles T that the
+// persistent form's P workgroups share.  Up to 3/4 P every tile has a workgroup of its own
+// (36 x 37 at 8 terms 15 against 18 us tiled), and beyond 12 P a workgroup's tiles hide its
+// start (128 x 128: 826 us tiled and 841 at one term, 1434 and 1289 at 64).  Between them,
+// few terms do not: 64 x 64 (4.2 P) at one term 52 and 58 us, at 16 62 and 64, 79 x 80 (9.9
+// P) at one 126 and 142.  Up to 8 P with more terms the share decides: 52 x 53 (2.02 P,
+// three tiles for some) at 64 terms 66 and 70 us, 49 x 50 (1.6 P, two) 58 and 52.
+static bool c128_tiled(const Geo& g, int bound) {
+  const int64_t nb = (g.N + 63) / 64, T = nb * (nb + 1) / 2 + (g.nmon + 63) / 64 * (g.ld / 64), P = band_workgroups(2);
+  if (4 * T <= 3 * P || T > 12 * P) return false;
+  if (bound <= 8) return true;
+  if (T <= P || T > 8 * P) return false;
+  return bound <= 20 || 10 * P * ((T + P - 1) / P) > 13 * T;
+}
+
 hipError_t launch_flush(const Geo& g, gfo_state* st, const Layout& L, hipStream_t s) {
   char* w = (char*)st->work;
   const int32_t* count = (const int32_t*)(w + L.dl_hdr);
@@ -1356,19 +1372,16 @@ hipError_t launch_flush(const Geo& g, gfo_state* st, const Layout& L, hipStream_
     }
   } else {
     if (hipError_t er = record_event(before, s)) return note_hip(er);
-    // 32-bit offsets into the term buffers and the G tiles; beyond (a million rows) the
-    // tiled product, which addresses each entry in full
-    const int64_t nx = g.R > g.ld ? (int64_t)g.R : g.ld;
-    if ((int64_t)GFO_MAX_DELAY * nx * 16 < ((int64_t)1 << 31)) {
+    if (c128_tiled(g, st->pending_calls)) {
+      e = launch_zgemm_update_f64(g, count, (const double2*)(w + L.dl_CUs), (const double2*)(w + L.dl_Vs),
+                                  (double2*)st->G, s);
+    } else {
       constexpr int kSegTiles = 16;
       const int nb = (g.N + 63) / 64;
       hipLaunchKernelGGL(k_flush_c128, dim3((unsigned)band_workgroups(2)), dim3(256), 0, s, g.N, g.R, g.ld, count,
                          (const double2*)(w + L.dl_CUs), (const double2*)(w + L.dl_Vs), (double2*)st->G, nb, g.packed,
                          g.mon_base, kSegTiles);
       e = note_hip(hipGetLastError());
-    } else {
-      e = launch_zgemm_update_f64(g, count, (const double2*)(w + L.dl_CUs), (const double2*)(w + L.dl_Vs),
-                                  (double2*)st->G, s);
     }
     if (e == hipSuccess) e = record_event(after, s);
     if (e != hipSuccess) return note_hip(e);

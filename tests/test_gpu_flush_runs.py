@@ -79,3 +79,27 @@ def test_c128_flush_equals_eager(ny, nx, n_mon, steps, delay, packed):
     Ga, Ea, da, ia = a.host_state()
     assert np.array_equal(ia, ib) and np.array_equal(a.history(), b.history())
     assert rel_elem(Gb, Ga, floor=1.0) <= 8 * steps * 2.0 ** -53
+
+
+@pytest.mark.parametrize("ny,nx,n_mon,steps,packed", [
+    (43, 44, 1, 8, False), (46, 47, 70, 33, True), (49, 50, 3, 20, False), (58, 59, 65, 33, False),
+    (79, 80, 1, 5, True)])
+def test_c128_tiled_flush_equals_eager(ny, nx, n_mon, steps, packed):
+    """complex128 between one tile per workgroup of the persistent form and many: few
+    terms, or an uneven share, a workgroup per tile.  Tolerance as above."""
+    import numpy as np
+    from paper_2202_05388_amd.job import Job
+    from parity import rel_elem
+    p = W.tiny(ny, nx, n_mon=n_mon, dtype="c128", cand_mask=W.MASK_BOTH, tau=1e-9)
+    print(f"[case] c128 {ny}x{nx} n_mon {n_mon}: {steps} moves, packed {packed}", flush=True)
+    a = Job(p, device="cuda:0")
+    a.init()
+    a.run_greedy(steps, poll_every=steps)
+    b = Job(p, device="cuda:0", delay=64, packed=packed)
+    b.init()
+    b.run_greedy(steps, poll_every=steps)
+    assert b.state.pending_calls == steps
+    Gb, _, _, ib = b.host_state()
+    Ga, _, _, ia = a.host_state()
+    assert np.array_equal(ia, ib) and np.array_equal(a.history(), b.history())
+    assert rel_elem(Gb, Ga, floor=1.0) <= 8 * steps * 2.0 ** -53
