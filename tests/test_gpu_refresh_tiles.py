@@ -64,3 +64,36 @@ def test_c64_refresh_is_c128_rounded_once(ny, nx, n_mon, flips):
     assert torch.equal(a.diag64, b.diag64)
     assert torch.equal(a.E.to(torch.complex64), b.E)
     assert int((a.G.to(torch.complex64) != b.G).sum()) == 0
+
+
+def test_refresh_large_panel_product():
+    """14,762 pixels, 1,034 of them flipped: Z = U M on the 128 x 128 tiles (1,044 of them),
+    with ragged rows and columns and a last chunk of four k.  Every 100th design row and
+    the monitor rows against G0 + G0[:, V] M G0[V, :] from the device's own G0.
+    Tolerance as above: 100 u kappa."""
+    import torch
+    from paper_2202_05388_amd.job import Job
+    p = W.tiny(122, 121, n_mon=5, dtype="c128")
+    N, k = p.n, 1034
+    idx = np.zeros(N, np.uint8)
+    idx[np.random.default_rng(7).choice(N, k, replace=False)] = 1
+    V = np.flatnonzero(idx)
+    rows = np.concatenate([np.arange(3, N, 100), np.arange(N, N + 5)])
+    print(f"[case] 122x121 c128, {k} flipped, {len(rows)} rows compared", flush=True)
+    job = Job(p, device="cuda:0", kmax=k)
+    job.init()
+    at = torch.from_numpy(rows).cuda()
+    G0V = job.G[torch.from_numpy(V).cuda(), :N].cpu().numpy()         # k x N, and its transpose by symmetry
+    G0r, Einc = job.G[at, :N].cpu().numpy(), job.E.cpu().numpy()
+    job.eps_idx.copy_(torch.from_numpy(idx))
+    job.refresh()
+    G, E, d = job.G[at, :N].cpu().numpy(), job.E.cpu().numpy()[rows], job.diag64.cpu().numpy()
+    alpha = greens.alpha_of(p, ost.eps_of(p, idx))[V]
+    core = np.diag(1.0 / alpha) - G0V[:, V]
+    Z = np.linalg.solve(core.T, G0r[:, V].T).T
+    Gd, Ed = G0r + Z @ G0V, Einc[rows] + Z @ Einc[V]
+    tol = max(1e-12, 100 * 2.0 ** -53 * np.linalg.cond(core))
+    own = rows[rows < N]
+    err = [rel_elem(G, Gd), rel_elem(E, Ed), rel_elem(d[own], Gd[np.arange(len(own)), own])]
+    print("G, E, diag64", *("%.3g" % e for e in err), "bound %.3g" % tol, flush=True)
+    assert max(err) <= tol and job.status() == 0
