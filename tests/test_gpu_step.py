@@ -248,3 +248,19 @@ def test_invalid_arguments_are_refused_before_any_launch(delay):
     assert job.n_flips() == 0 and job.status() == 0
     assert job.state.pending_calls == 0
     assert bool((job.E.cpu() == E0).all())
+
+
+@pytest.mark.parametrize("raw", [True, False])
+def test_calls_use_the_current_stream(raw, monkeypatch):
+    """The handle that a call without a stream argument takes is the current stream's, with
+    and without torch's raw-handle function."""
+    import torch
+    from paper_2202_05388_amd import job as J
+    assert J._raw_stream is not None
+    if not raw:
+        monkeypatch.setattr(J, "_raw_stream", None)
+    side = torch.cuda.Stream()
+    assert J._stream_handle() == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert J._stream_handle() == side.cuda_stream
+    assert J._stream_handle(side) == side.cuda_stream
