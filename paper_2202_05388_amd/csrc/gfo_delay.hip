@@ -146,9 +146,6 @@ __device__ __forceinline__ void gather_prefetch(const Geo& g, const int32_t* __r
 // it count as zero (adding +0 leaves the sum's bits), so that four terms' products
 // are in flight without a branch each.
 template <typename T, int B>
-__device__ __forceinline__ double2 sum_terms(const GatherPre<T, B>& pre, T yl, int s0, int cnt);
-
-template <typename T, int B>
 __device__ __forceinline__ double2 sum_terms(const GatherPre<T, B>& pre, T yl, int s0, int cnt) {
   const T zero = St<T>::from_d(make_double2(0.0, 0.0));
   const T y = pick_of(s0 + (int)(threadIdx.x & 63) < cnt, yl, zero);
@@ -889,10 +886,11 @@ hipError_t launch_move_scores(const Geo& g, gfo_state* st, const Layout& L, uint
 }
 
 // ------------------------------------------------------------------ grouped launches
-// The one-kernel loop of many jobs at once: workgroup (x, y) runs workgroup x
-// of job y's own kernel with job y's arguments from the table (the same bodies,
-// so every job's moves and state are bit for bit those of its own calls);
-// workgroups past a job's count return at once.
+// The one-kernel loop of many jobs at once, with each job's arguments from the table (the
+// same bodies, so every job's moves and state are bit for bit those of its own calls).
+// Scores and finish: workgroup (x, y) runs workgroup x of job y's own kernel, those past
+// the job's count return at once.  Moves: a line of workgroups dealt out over the jobs
+// (TableWgs).
 int gather_move_workgroups(const Geo& g) {
   const int64_t n = (int64_t)gather_mpad(g) + g.ld;
   return (int)((n + kGatherElems - 1) / kGatherElems);

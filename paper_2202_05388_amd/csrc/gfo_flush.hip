@@ -937,11 +937,11 @@ __global__ __launch_bounds__(256, 1) void k_flush_c64_s3_ring(int M, int R, int6
     int64_t stride;
     unsigned vo;
   };
-  auto out_of = [&](const SegTile& c, bool none) __attribute__((always_inline)) {
+  auto out_of = [&](const SegTile& c) __attribute__((always_inline)) {
     const int rows = c.lim - c.rbase < 64 ? c.lim - c.rbase : 64;
     const TileAt ta = tile_at(packed, M, ld, mon_base, c.rbase, c.bx);
     return Out{__builtin_amdgcn_make_buffer_rsrc((void*)(G + ta.base), (short)0,
-                                                 none ? 0 : (int)((int64_t)rows * ta.stride * 8), kBufferDword3),
+                                                 (int)((int64_t)rows * ta.stride * 8), kBufferDword3),
                ta.stride, (unsigned)((int64_t)lrow * ta.stride + cc) * 8u};
   };
   auto row_off = [&](int64_t stride, int e) { return (int)((int64_t)(8 * (e >> 2) + (e & 3)) * stride * 8); };
@@ -982,7 +982,7 @@ __global__ __launch_bounds__(256, 1) void k_flush_c64_s3_ring(int M, int R, int6
       load_S(nxt.bx, p, j);
     }
   {
-    const Out o = out_of(cur, false);
+    const Out o = out_of(cur);
 #pragma unroll
     for (int e = 0; e < 16; ++e) load_G(o, e);
   }
@@ -1019,7 +1019,7 @@ __global__ __launch_bounds__(256, 1) void k_flush_c64_s3_ring(int M, int R, int6
         }
       }
       if (p == 3) {
-        const Out out = out_of(cur, false), on = out_of(nxt, false);
+        const Out out = out_of(cur), on = out_of(nxt);
 #pragma unroll
         for (int e = 0; e < 16; ++e) finish(out, a, e);
         __builtin_amdgcn_sched_barrier(0);
@@ -1201,8 +1201,8 @@ __global__ __launch_bounds__(256, 2) void k_flush_c128(int M, int R, int64_t ld,
 
 // flush variants for complex64 storage (selected by the autotuner; all give the
 // eager results to FP32 rounding, tests/test_gpu_deferred.py).  The default,
-// up_bandseg_s3: the split-product band flush for 17 to 64 terms, the pair
-// flush in XCD tile order otherwise.
+// up_bandseg_s3: the split-product flush for 17 to 128 terms (from 65 on with a ring
+// of operand slots), the pair flush in XCD tile order for fewer.
 static const char* const kFlushNames[] = {"w32_3m", "up_pair4_3m_nt", "up_pair4_3m_nt_x8", "up_band4_3m_nt",
                                           "up_bandseg4_3m_nt", "up_bandseg_s3"};
 constexpr int kFlushCount = (int)(sizeof(kFlushNames) / sizeof(kFlushNames[0]));

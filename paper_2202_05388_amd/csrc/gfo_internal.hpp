@@ -622,7 +622,8 @@ __host__ __device__ inline bool xcd_tile(int b, int nb, int nbx, int nmb, int* b
 // One entry per job of a grouped launch (gfo_greedy_steps_table): its geometry,
 // its buffers and the workspace offsets the one-kernel loop uses, and the
 // workgroup counts of its kernels.  Built on the host, read by the table
-// kernels (workgroup (x, y) works for job y as workgroup x of its own launch).
+// kernels (workgroup (x, y) works for job y as workgroup x of its own launch; the move
+// kernel's are in one line, TableWgs).
 struct JobEntry {
   Geo g;
   void* G;

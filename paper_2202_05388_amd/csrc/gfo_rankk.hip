@@ -174,8 +174,9 @@ __global__ __launch_bounds__(256) void k_rk_prepare(Geo g, const gfo_pick* __res
 // U = G[:, S] (R rows) and W = M G[S, :] (ld columns) with the O(R) and O(N)
 // updates, one pass: index q < N is design row q and design column q, the later
 // ones monitor rows (U) or padding columns (W = 0).  A workgroup of four waves
-// takes 64 indices, one per lane; wave w computes the rows a = w, w + 4, ... of
-// W and the entries a of U, and the partial sums of U y and U W meet in LDS.
+// takes 64 indices, one per lane; wave w computes a quarter of the rows of W, a in
+// [w KP / 4, (w + 1) KP / 4), and those entries of U, and the partial sums of U y and U W
+// meet in LDS.
 //   A operand, row-major [r][kappa]: kappa < KP: Re U, kappa >= KP: Im U;
 //   B operands per column [q][out][kappa]: out 0 (real part of the product):
 //   [Re W ; -Im W], out 1 (imaginary part): [Im W ; Re W]; FP32 or BF16.
@@ -195,7 +196,7 @@ __global__ __launch_bounds__(256) void k_rk_panels(Geo g, const RkHdr* __restric
                                                    int bf16) {
   const int s = hdr->s;
   if (s == 0 || hdr->kp != KP) return;
-  constexpr int NA = KP / 4;   // entries per wave: a = 4 i4 + ..., see below
+  constexpr int NA = KP / 4;   // entries per wave
   __shared__ double2 pe[3][64], pd[3][64];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t q = (int64_t)blockIdx.x * 64 + lane;
@@ -281,15 +282,10 @@ __global__ __launch_bounds__(256) void k_rk_panels(Geo g, const RkHdr* __restric
 }
 
 // ------------------------------------------------------------------ RK4: MFMA update
-// A workgroup of rows [r0, r0 + nr) and columns below c_end is left out when it
-// lies wholly in design rows (r0 + nr <= skip_below = N) and strictly below the
-// diagonal tiles (c_end <= r0, r0 a multiple of 64): with the design block's
-// upper triangle kept alone (deferred mode, or state.lower_stale), those
-// entries are never read.  skip_below = 0 updates every entry.
-__device__ __forceinline__ bool rk_below_diagonal(int r0, int nr, int64_t c_end, int skip_below) {
-  return skip_below > 0 && r0 + nr <= skip_below && c_end <= r0;
-}
-
+// With the design block's upper triangle kept alone (deferred mode, or
+// state.lower_stale) the forms launch no workgroup that lies wholly in design rows
+// and strictly below the diagonal (ut_group; skip_below = N): those entries are never
+// read.  skip_below = 0 updates every entry.
 
 // ------------------------------------------------------------------ RK4': streaming MFMA update
 // Workgroup: 4 waves side by side over 128 columns (wave w: columns
