@@ -43,10 +43,10 @@ PMC_TRAFFIC = [
     # complex64 flush records: one per term bucket (the launcher's kernel for up to 16, 32, 64
     # or 128 pending terms) of the default variant, each taken on flushes that fold the
     # bucket's full term count: the tile kernel, then the pack kernel
-    {"kernel": "k_flush_c64", "source": "paper_2202_05388_amd/csrc/gfo_flush.hip", "code_sha256": "3f0be79a23d3c24d420bb744b011ca270e5c0c93c5bb24933f9bb61c5ddcf0bb", "workload": "square128_c64", "variant": "up_bandseg_s3", "bucket": 16, "tile_kernel": "k_flush_c64_pair<4, 4, true>", "fetch_kib": 539628.7 + 2065.0, "write_kib": 1060883.0 + 4104.0},
-    {"kernel": "k_flush_c64", "source": "paper_2202_05388_amd/csrc/gfo_flush.hip", "code_sha256": "3f0be79a23d3c24d420bb744b011ca270e5c0c93c5bb24933f9bb61c5ddcf0bb", "workload": "square128_c64", "variant": "up_bandseg_s3", "bucket": 32, "tile_kernel": "k_flush_c64_s3<2>", "fetch_kib": 562701.8 + 4137.0, "write_kib": 1060876.5 + 12312.0},
-    {"kernel": "k_flush_c64", "source": "paper_2202_05388_amd/csrc/gfo_flush.hip", "code_sha256": "3f0be79a23d3c24d420bb744b011ca270e5c0c93c5bb24933f9bb61c5ddcf0bb", "workload": "square128_c64", "variant": "up_bandseg_s3", "bucket": 64, "tile_kernel": "k_flush_c64_s3<4>", "fetch_kib": 636615.9 + 8241.7, "write_kib": 1060866.9 + 24624.0},
-    {"kernel": "k_flush_c64", "source": "paper_2202_05388_amd/csrc/gfo_flush.hip", "code_sha256": "3f0be79a23d3c24d420bb744b011ca270e5c0c93c5bb24933f9bb61c5ddcf0bb", "workload": "square128_c64", "variant": "up_bandseg_s3", "bucket": 128, "tile_kernel": "k_flush_c64_s3_ring", "fetch_kib": 733853.3 + 16450.0, "write_kib": 1060880.3 + 49248.0},
+    {"kernel": "k_flush_c64", "source": "paper_2202_05388_amd/csrc/gfo_flush.hip", "code_sha256": "538db2adf2b7be021bae27758d29f33c3fc278709dcf827aceb8a0a863d8456a", "workload": "square128_c64", "variant": "up_bandseg_s3", "bucket": 16, "tile_kernel": "k_flush_c64_pair<4, 4, true>", "fetch_kib": 539629.0 + 2065.0, "write_kib": 1060903.7 + 4104.0},
+    {"kernel": "k_flush_c64", "source": "paper_2202_05388_amd/csrc/gfo_flush.hip", "code_sha256": "538db2adf2b7be021bae27758d29f33c3fc278709dcf827aceb8a0a863d8456a", "workload": "square128_c64", "variant": "up_bandseg_s3", "bucket": 32, "tile_kernel": "k_flush_c64_s3<2>", "fetch_kib": 562532.7 + 4137.0, "write_kib": 1060873.0 + 12312.0},
+    {"kernel": "k_flush_c64", "source": "paper_2202_05388_amd/csrc/gfo_flush.hip", "code_sha256": "538db2adf2b7be021bae27758d29f33c3fc278709dcf827aceb8a0a863d8456a", "workload": "square128_c64", "variant": "up_bandseg_s3", "bucket": 64, "tile_kernel": "k_flush_c64_s3<4>", "fetch_kib": 637280.4 + 8241.0, "write_kib": 1060868.2 + 24624.0},
+    {"kernel": "k_flush_c64", "source": "paper_2202_05388_amd/csrc/gfo_flush.hip", "code_sha256": "538db2adf2b7be021bae27758d29f33c3fc278709dcf827aceb8a0a863d8456a", "workload": "square128_c64", "variant": "up_bandseg_s3", "bucket": 128, "tile_kernel": "k_flush_c64_s3_ring", "fetch_kib": 734298.6 + 16450.0, "write_kib": 1060880.5 + 49248.0},
 ]
 
 

@@ -1053,7 +1053,7 @@ __global__ __launch_bounds__(256, 1) void k_flush_c64_s3_ring(int M, int R, int6
 //     through the buffers' ranges and take no matrix steps.
 //   - G(t+1) is read into registers after tile t's entries are stored, a tile ahead.
 // Bound by the FP64 matrix cores (64 cycles per step; 0.98 ms at the 2.16 GHz this load
-// leaves) at 64 terms, by the stream of G at few: 128 x 128, 2.15 GB of G, 1.29 ms at 64
+// leaves) at 64 terms, by the stream of G at few: 128 x 128, 2.15 GB of G, 1.31 to 1.34 ms at 64
 // terms and 0.86 at 17; the tiled product of k_zgemm_f64, four waves per SIMD without
 // LDS, 1.45 and 0.86 (32 x 32 at 48 terms 16 and 25 us, 21 x 21 at 16 8.3 and 14.7).
 // Each workgroup on a stretch of 16-tile rows of its own: 36 instead of 20 million

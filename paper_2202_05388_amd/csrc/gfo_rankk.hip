@@ -465,9 +465,11 @@ __global__ __launch_bounds__(256, (!BF16 && TM == 1 && KP == 16 && RB <= 4) ? 3 
 // loop.  A wave requests the next block's G before the current block's products,
 // which need theirs: the loads are in flight during the products of the block
 // before.  Bound by HBM (G read and written once, non-temporal).  128 x 128, whole
-// matrix, 4.31 GB: FP32 763 us at rank 16, 872 us at rank 32; BF16 746 and 734 us;
-// with one 64 x 64 tile per workgroup and step and G waited for in each (the same
-// bits) 916, 1711, 838 and 827 us.
+// matrix, 4.31 GB, update after update: FP32 771 us at rank 16, 872 us at rank 32; BF16
+// 753 and 734 us; with one 64 x 64 tile per workgroup and step and G waited for in each
+// (the same bits) 916, 1711, 838 and 827 us.  In calls with the selection between them 0.80
+// and 0.90 ms at rank 16.  lds128_r4 (k_rk_stream, G in 16-byte pieces) takes 752 us, with
+// another rounding.
 template <int KP, bool BF16, int RB>
 __global__ __launch_bounds__(256, KP == 16 ? 3 : 2) void k_rk_accum(int R, int64_t ld, int skip_below,
                                                   const int32_t* __restrict__ gate_count,
