@@ -216,7 +216,7 @@ __global__ __launch_bounds__(kRegionThreads) void k_score_regions(
   if (bad) atomicOr(status, GFO_STATUS_NONFINITE);
 }
 
-// The same scores (and bits) with a thread per region: an eighth of the reads' instructions
+// The same scores (and bits) with a thread per region: a third of the loads per term
 // and no exchange, where the regions alone fill the chip or there are few terms to read
 // (region_per_thread).  Workgroup b covers the regions [256 b, 256 b + 256).
 // NE: 2 when the table has two entries, else GFO_MAX_EPS.
